@@ -320,7 +320,8 @@ enum mlmc_smooth_flags {
  * of their coordinates, first colour (even) first; flags: enum
  * mlmc_smooth_flags), run in the working precision by the V-cycle's own kernels
  * and sweep grouping (2D Poisson levels: passes of up to two fused sweeps, an
- * odd remainder first for forward sweeps, last for reverse ones; the Wilson
+ * odd remainder first for forward sweeps, last for reverse ones -- on grids of
+ * side <= 128, whose V-cycle is one launch, these passes run here only; the Wilson
  * level: both colours of a sweep in one out-of-place pass).  With rc_dev
  * non-NULL (forward sweeps only) also Rc = R_l (B - A_l X) of the final X, as
  * the last pre-smoothing pass of the V-cycle writes it (fused into that pass
@@ -455,7 +456,9 @@ int mlmc_set_timing(mlmc_ctx* ctx, int mask, int stride);
  * element size e; each operator kind reports its own smoother, residual and
  * transfer kernels under the same ids): 0 red-black Gauss-Seidel sweep (2e from a zero start:
  * b in, x out; 3e with an input iterate; +0.25e with the folded coarse
- * correction), 1 fused residual + restriction (2.25e), 2 prolongation +
+ * correction; on 2D Poisson grids of side <= 128 above a coarsest side <= 64 the
+ * V-cycle and the solves are one launch each, reported here as 2e, and 16 bytes
+ * for a whole solve), 1 fused residual + restriction (2.25e), 2 prolongation +
  * correction when there is no post-smoothing (2.25e), 3 Krylov direction update
  * fused with the operator apply and its dot (4e: z, p in; p, q out), 4 CG x/r
  * update with |r|^2 (6e), 5 learned-smoother network (counts FLOPs, not

@@ -12,6 +12,7 @@ BUILD_DIR = os.path.join(os.path.dirname(HERE), "_build")
 SOURCES = [
     "kernels_vec.hip",
     "kernels_poisson.hip",
+    "kernels_small.hip",
     "kernels_wilson.hip",
     "kernels_krylov.hip",
     "kernels_varcoef.hip",

@@ -294,7 +294,97 @@ void Context::build_poisson() {
   }
   MLMC_REQUIRE(lv_[Ls_ - 1].n <= 16384, MLMC_EINVAL, "coarsest solver level larger than 128^2");
   finish_real_build();
+  build_small();
   tune_poisson();
+}
+
+// the sine basis of the coarsest level (side m): A = S diag(lambda) S with
+// S_jk = sqrt(2 / (m + 1)) sin(jk pi / (m + 1)) on both axes and eigenvalues
+// d - 2c (cos + cos), rows and columns padded with zeros to a multiple of 16
+void Context::build_small() {
+  const Level& C = lv_[Ls_ - 1];
+  const int m = C.side, mp = (m + 15) / 16 * 16;
+  if (m > kSmallCoarse) return;
+  std::vector<double> basis((size_t)mp * mp, 0.0), ilam((size_t)mp * mp, 0.0);
+  const double h = M_PI / (m + 1);
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < m; ++j) {
+      basis[(size_t)i * mp + j] = std::sqrt(2.0 / (m + 1)) * std::sin(h * ((i + 1) * (j + 1) % (2 * (m + 1))));
+      ilam[(size_t)i * mp + j] =
+          1.0 / (C.d - 2.0 * C.c * (std::cos(h * (i + 1)) + std::cos(h * (j + 1))));
+    }
+  const double* src[2] = {basis.data(), ilam.data()};
+  for (int i = 0; i < 2; ++i) {
+    small_basis_[i] = dalloc_n<double>((int64_t)mp * mp);
+    MLMC_HIP(hipMemcpyAsync(small_basis_[i], src[i], sizeof(double) * mp * mp,
+                            hipMemcpyHostToDevice, s_));
+    if (opt_.precision == MLMC_FP32_IR64) {
+      small_basis32_[i] = dalloc_n<float>((int64_t)mp * mp);
+      vec_convert<float, double>(small_basis_[i], small_basis32_[i], (int64_t)mp * mp, 1, nullptr,
+                                 s_);
+    }
+  }
+  MLMC_HIP(hipStreamSynchronize(s_));
+  small_setup();
+  small_level_ = Ls_;
+  while (small_level_ > 1 && lv_[small_level_ - 2].side <= kSmallSide) --small_level_;
+}
+
+template <typename T>
+SmallGrid<T> Context::small_grid(int l) const {
+  SmallGrid<T> q = {};
+  q.nl = Ls_ - l + 1;
+  q.pre = opt_.nu_pre;
+  q.post = opt_.nu_post;
+  q.wh = (T)(0.5 * omega_);
+  int off = 0;
+  for (int j = 0; j < q.nl; ++j) {
+    const Level& L = lv_[l - 1 + j];
+    q.side[j] = L.side;
+    q.d[j] = (T)L.d;
+    q.c[j] = (T)L.c;
+    q.dinv[j] = (T)(1.0 / L.d);
+    q.off[j] = off;
+    if (j > 0 && j < q.nl - 1) off += 2 * L.side * L.side;
+  }
+  q.mp = (lv_[Ls_ - 1].side + 15) / 16 * 16;
+  if constexpr (sizeof(T) == 8) {
+    q.basis = small_basis_[0];
+    q.ilam = small_basis_[1];
+  } else {
+    q.basis = small_basis32_[0];
+    q.ilam = small_basis32_[1];
+  }
+  return q;
+}
+
+void Context::small_solve(int l, const double* b, double* y, int nb, double tol, c64* err) {
+  const Level& L = lv_[l - 1];
+  const double en = 16.0 * (double)L.n;  // b in, y out
+  if (opt_.precision == MLMC_FP64 || fp64_batch(nb)) {
+    timed<double>(l, kTimGs, en, nullptr, nb, [&] {
+      small_pcg<double>(b, y, w64_.p, w64_.r, small_grid<double>(l), top_cycles_, tol,
+                        opt_.max_iter, nb, scal_[kRres], scal_[kBb], err, s_);
+    });
+  } else {
+    timed<float>(l, kTimGs, en, nullptr, nb, [&] {
+      small_refined(b, y, w32_.p, d32_, small_grid<float>(l), top_cycles_, L.d, L.c, tol,
+                    opt_.inner_tol, opt_.max_iter * opt_.max_refine, nb, scal_[kRres], scal_[kBb],
+                    err, s_);
+    });
+  }
+}
+
+// the counters of a small solve, from the host copies of rres and bb
+void Context::count_small(int l, int nb) {
+  int it = 0, refs = 0;
+  for (int k = 0; k < nb; ++k) {
+    it = std::max(it, (int)host_c64_[k].im);
+    refs = std::max(refs, (int)host_c64_[nb + k].im);
+  }
+  counters[0] += it;
+  counters[1] += std::max(refs, 1);
+  if (l == 1) counters[2] += it;
 }
 
 // Autotuner of the fused Poisson sweep: per smoothed level with N >= 64, time
@@ -340,7 +430,7 @@ void Context::tune_poisson() {
     }
     L.gs_rows[slot] = best < 0.90f * t_dflt ? best_rows : dflt;
   };
-  for (int l = 1; l < Ls_; ++l) {
+  for (int l = 1; l < Ls_ && !small(l); ++l) {
     Level& L = lv_[l - 1];
     if (L.side < 64) continue;
     if (opt_.precision == MLMC_FP32_IR64) tune(float(), L, 0, l);
@@ -631,6 +721,7 @@ void Context::op_restrict(int l, const T* x, T* xc, int nb, const int* act) {
 template <typename T>
 void Context::second_coarse_cycle(int l, const T* bc, T* ec, int nb, const int* act, bool top) {
   if (!top || top_cycles_ != 2 || l + 1 >= Ls_) return;
+  if (small(l + 1)) return;  // vcycle ran both cycles in one launch
   if (!varcoef_ && !csr_) {
     vcycle<T>(l + 1, bc, ec, nb, act, nullptr, false, ec);
     return;
@@ -748,7 +839,7 @@ void Context::vcycle_vc(int l, const T* b, T* x, int nb, const int* act, c64* rz
 // ---------------------------------------------------------------------------
 template <typename T>
 void Context::vcycle(int l, const T* b, T* x, int nb, const int* act, c64* rz_partials,
-                     bool top, const T* x0) {
+                     bool top, const T* x0, int cycles) {
   MLMC_REQUIRE(!x0 || (!varcoef_ && !csr_ && l < Ls_), MLMC_EINVAL,
                "a V-cycle from a given iterate is the 2D Poisson smoothed levels' only");
   if (varcoef_) {
@@ -763,6 +854,13 @@ void Context::vcycle(int l, const T* b, T* x, int nb, const int* act, c64* rz_pa
   if (l == 1) counters[2] += 1;
   const int64_t n = lv_[l - 1].n;
   const double en = (double)sizeof(T) * (double)n;
+  if (small(l)) {
+    // a solve's top level never gets here (small_solve), except the coarsest
+    timed<T>(l, kTimGs, en * 2.0, act, nb, [&] {
+      small_vcycle<T>(b, x, x0, small_grid<T>(l), cycles, nb, act, rz_partials, s_);
+    });
+    return;
+  }
   if (l == Ls_) {
     dense_apply<T>(w.ainvT, b, x, (int)n, nb, act, s_, w.ld);
     if (rz_partials) vec_dot_partials<T>(b, x, n, nb, act, rz_partials, s_);
@@ -803,7 +901,10 @@ void Context::vcycle(int l, const T* b, T* x, int nb, const int* act, c64* rz_pa
   else if (!restricted)
     timed<T>(l, kTimResRestrict, 2.25 * en, act, nb,
              [&] { op_res_restrict<T>(l, b, u, bc, nb, act); });
-  vcycle<T>(l + 1, bc, ec, nb, act, nullptr);
+  // both coarse-grid cycles of a top level in one launch where the next level is
+  // small (the coarsest level is solved exactly: once)
+  vcycle<T>(l + 1, bc, ec, nb, act, nullptr, false, nullptr,
+            top && top_cycles_ == 2 && small(l + 1) && l + 1 < Ls_ ? 2 : 1);
   second_coarse_cycle<T>(l, bc, ec, nb, act, top);
   if (post == 0) {
     if (u == nullptr) {
@@ -1239,14 +1340,19 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
     finish_sums(partials_, nblk, nb, bb, s_);
   } else {
   const bool refined = l != Ls_ && opt_.precision != MLMC_FP64 && !fp64_batch(nb);
-  if (!(refined && b32_)) {  // else pcg_refined forms |b|^2 with the FP32 copy of b
+  const bool whole = small(l) && l != Ls_;  // the kernel forms |b|^2 and the residual
+  if (!whole && !(refined && b32_)) {  // else pcg_refined forms |b|^2 with the FP32 copy of b
     vec_dot_partials<double>(b, b, n, nb, nullptr, partials_, s_);
     finish_sums(partials_, nblk, nb, bb, s_);
   }
   set_all_active(act_outer_, nb, s_);
   vec_zero<c64>(err, 1, nb, nullptr, s_);
   const double tol = opt_.solve_tol;
-  if (l == Ls_) {
+  if (whole) {
+    small_solve(l, b, y, nb, tol, err);
+  } else if (l == Ls_ && small(l)) {
+    small_vcycle<double>(b, y, nullptr, small_grid<double>(l), 1, nb, nullptr, nullptr, s_);
+  } else if (l == Ls_) {
     dense_apply<double>(w64_.ainvT, b, y, (int)n, nb, nullptr, s_, w64_.ld);
   } else if (opt_.precision == MLMC_FP64 || fp64_batch(nb)) {
     MLMC_HIP(hipMemcpyAsync(act_inner_, act_outer_, sizeof(int) * nb,
@@ -1258,7 +1364,7 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
   }
   // final FP64 relative residuals (the refined solver ends on a true FP64
   // residual already, kept in rres)
-  if (l == Ls_ || opt_.precision == MLMC_FP64 || fp64_batch(nb)) {
+  if (!whole && (l == Ls_ || opt_.precision == MLMC_FP64 || fp64_batch(nb))) {
     op_residual<double, double, double>(l, b, y, r64_, nb, nullptr, partials_);
     finish_sums(partials_, nblk_pts, nb, rres, s_);
   }
@@ -1267,6 +1373,7 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
   MLMC_HIP(hipMemcpyAsync(host_c64_, rres, sizeof(c64) * nb, hipMemcpyDeviceToHost, s_));
   MLMC_HIP(hipMemcpyAsync(host_c64_ + nb, bb, sizeof(c64) * nb, hipMemcpyDeviceToHost, s_));
   MLMC_HIP(hipStreamSynchronize(s_));
+  if (!complex_ && small(l) && l != Ls_) count_small(l, nb);
   bool ok = true;
   col_ok_.assign((size_t)nb, 1);
   for (int k = 0; k < nb; ++k) {
@@ -1704,8 +1811,8 @@ template void Context::second_coarse_cycle<float>(int, const float*, float*, int
 template void Context::second_coarse_cycle<double>(int, const double*, double*, int, const int*,
                                                    bool);
 template void Context::vcycle<float>(int, const float*, float*, int, const int*, c64*, bool,
-                                      const float*);
+                                      const float*, int);
 template void Context::vcycle<double>(int, const double*, double*, int, const int*, c64*, bool,
-                                       const double*);
+                                       const double*, int);
 
 }  // namespace mlmc

@@ -299,12 +299,26 @@ class Context {
   template <typename T> void vcycle_vc(int l, const T* b, T* x, int nb, const int* act,
                                        c64* rz_partials, bool top = false);
   template <typename T> Work<T>& work();
+  // POISSON2D: levels from small_level_ on (sides up to kSmallSide above a
+  // coarsest side of at most kSmallCoarse) run as one workgroup per column:
+  // whole V-cycles below larger levels, whole solves on the smoothed levels
+  void build_small();
+  bool small(int l) const { return l >= small_level_; }
+  template <typename T> SmallGrid<T> small_grid(int l) const;
+  // whole solve; counts its iterations and refinements from the host copies of
+  // rres and bb (see small_pcg) once solve() has them
+  void small_solve(int l, const double* b, double* y, int nb, double tol, c64* err);
+  void count_small(int l, int nb);
+  int small_level_ = 1 << 30;
+  double* small_basis_[2] = {nullptr, nullptr};  // basis, reciprocal eigenvalues
+  float* small_basis32_[2] = {nullptr, nullptr};
   // top: l is the solve's top level (top_cycles_ coarse-grid cycles there).
   // x0 (POISSON2D, not the coarsest level; nullable): the pre-smoothing starts
-  // from x0 instead of 0 (x0 may be x), which gives x0 + V(b - A x0)
+  // from x0 instead of 0 (x0 may be x), which gives x0 + V(b - A x0).
+  // cycles (small levels only): 2 runs a second V-cycle started from the first's
   template <typename T> void vcycle(int l, const T* b, T* x, int nb, const int* act,
                                     c64* rz_partials, bool top = false,
-                                    const T* x0 = nullptr);
+                                    const T* x0 = nullptr, int cycles = 1);
   // with top and top_cycles_ == 2 (and level l + 1 not the coarsest): a second
   // coarse-grid cycle on level l + 1 on the residual of the first, ec += V(bc - A ec)
   template <typename T> void second_coarse_cycle(int l, const T* bc, T* ec, int nb,

@@ -197,6 +197,39 @@ template <typename T>
 void dense_transpose(const T* in, T* out, int n, hipStream_t s);
 
 // ----- 2D Poisson stencil: A = d I - c (grid neighbours), N x N Dirichlet -----
+// ----- small 2D Poisson grids (one workgroup per right-hand side) -------------
+constexpr int kSmallSide = 128;   // largest top side
+constexpr int kSmallCoarse = 64;  // largest coarsest side
+constexpr int kSmallPad = 4;      // row padding of the coarsest level's LDS planes
+// levels from a top level (index 0) down to the coarsest (index nl - 1)
+template <typename T>
+struct SmallGrid {
+  int nl, pre, post;
+  int side[8], off[8];      // off: LDS elements of the levels 1 .. nl - 2 (b, then x)
+  T d[8], c[8], dinv[8];
+  T wh;                     // omega / 2
+  int mp;                   // coarsest side rounded up to 16
+  const T *basis, *ilam;    // its sine basis and reciprocal eigenvalues, mp x mp, zero padded
+};
+// bytes of LDS of a workgroup (refined: small_refined's)
+template <typename T> size_t small_lds(const SmallGrid<T>& q, bool refined);
+// lets the kernels use the device's whole LDS (once per device and context)
+void small_setup();
+// z = `cycles` V-cycles for b, from z0 (nullable: zero); partials (nullable): b^T z, one
+// per column; nl == 1: the coarsest solve alone
+template <typename T>
+void small_vcycle(const T* b, T* z, const T* z0, const SmallGrid<T>& q, int cycles, int nb,
+                  const int* active, c64* partials, hipStream_t s);
+// whole solves: CG in precision T, and FP32 CG with FP64 refinement; rres: final
+// |b - A x|^2 (re) and iterations (im), bb: |b|^2 (re) and refinements (im);
+// pbuf, rbuf, xbuf: planes of nb columns
+template <typename T>
+void small_pcg(const T* b, T* x, T* pbuf, T* rbuf, const SmallGrid<T>& q, int child_cycles, double tol,
+               int max_iter, int nb, c64* rres, c64* bb, c64* lastcorr, hipStream_t s);
+void small_refined(const double* b, double* y, float* pbuf, float* xbuf,
+                   const SmallGrid<float>& q, int child_cycles, double d, double c, double tol, double inner_tol, int max_it, int nb,
+                   c64* rres, c64* bb, c64* err, hipStream_t s);
+
 // partial-sum counts per column of the tiled kernels
 int poisson_march_tiles(int N);   // apply / residual
 // fused Gauss-Seidel pass of `sweeps` (1 or 2) sweeps, `rows` per segment
