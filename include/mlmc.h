@@ -460,9 +460,10 @@ int mlmc_set_timing(mlmc_ctx* ctx, int mask, int stride);
  * V-cycle and the solves are one launch each, reported here as 2e, and 16 bytes
  * for a whole solve), 1 fused residual + restriction (2.25e), 2 prolongation +
  * correction when there is no post-smoothing (2.25e), 3 Krylov direction update
- * fused with the operator apply and its dot (4e: z, p in; p, q out), 4 CG x/r
- * update with |r|^2 (6e), 5 learned-smoother network (counts FLOPs, not
- * bytes: 2 x 4032 per site and column), 6 FP64 refinement fold y += x32 with
+ * fused with the operator apply and its dot (4e: z, p in; p, q out; 2D Poisson,
+ * which stores no q: 3e), 4 CG x/r update with |r|^2 (6e; 2D Poisson 5e), 5
+ * learned-smoother network (counts FLOPs, not bytes: 2 x 4032 per site and
+ * column), 6 FP64 refinement fold y += x32 with
  * its b^T x32 partial sums and x32 = 0 (32 bytes: FP64 y, b and FP32 x32 in; y
  * and x32 out; fp64 slot), 7 FP64 refinement residual (20 bytes: FP64 b and y
  * in, FP32 r out; fp64 slot).  fp64 = 0 selects the FP32/complex64

@@ -663,7 +663,19 @@ void Context::op_update_apply(int l, const T* p_old, const T* z, const c64* beta
     varcoef_update_apply<T>(p_old, z, beta, p_new, q, vc_faces<T>(l), vc_diag<T>(l), L.side, nb,
                             L.cols, act, partials_, s_);
   else
-    poisson_update_apply<T>(p_old, z, beta, p_new, q, L.side, L.d, L.c, nb, act, partials_, s_);
+    poisson_direction<T>(p_old, z, beta, p_new, L.side, L.d, L.c, nb, act, partials_, s_);
+}
+
+// x += alpha p ; r -= alpha q ; |r|^2 partials (op_xr_partials per column).  The 2D
+// Poisson operator forms q = A p again from p: its op_update_apply stores none
+template <typename T>
+void Context::op_xr(int l, T* x, T* r, const T* p, const T* q, const c64* alpha, int nb,
+                    const int* act, bool x_zero) {
+  const Level& L = lv_[l - 1];
+  if (csr_ || varcoef_)
+    cg_update_xr<T>(x, r, p, q, alpha, L.n, nb, act, partials_, s_, x_zero);
+  else
+    poisson_xr<T>(x, r, p, alpha, L.side, L.d, L.c, nb, act, partials_, s_, x_zero);
 }
 
 template <typename T>
@@ -1073,6 +1085,7 @@ int Context::pcg(int l, const T* b, T* x, int nb, int* act, double tol, c64* las
     return 0;
   }
   const double en = (double)sizeof(T) * (double)n;
+  const bool stencil = !varcoef_ && !csr_;  // A p is not stored
   vec_copy<T>(b, w.r, n, nb, act, s_);
   vec_dot_partials<T>(b, b, n, nb, act, partials_, s_);
   finish_sums(partials_, nblk, nb, rr0, s_);
@@ -1086,13 +1099,13 @@ int Context::pcg(int l, const T* b, T* x, int nb, int* act, double tol, c64* las
   const int check = 2;
   int it = 0;
   for (it = 1; it <= opt_.max_iter; ++it) {
-    timed<T>(l, kTimApply, 4.0 * en, act, nb,
+    timed<T>(l, kTimApply, (stencil ? 3.0 : 4.0) * en, act, nb,
              [&] { op_update_apply<T>(l, p_old, w.z, beta, p_new, w.q, nb, act); });
     finish_alpha(partials_, ntiles, nb, tmp, rz, act, alpha, s_);
     if (lastcorr) cg_lastcorr(alpha, rz, act, lastcorr, nb, s_);
-    timed<T>(l, kTimCgXr, 6.0 * en, act, nb,
-             [&] { cg_update_xr<T>(x, w.r, p_new, w.q, alpha, n, nb, act, partials_, s_); });
-    finish_sums(partials_, nblk, nb, tmp, s_);
+    timed<T>(l, kTimCgXr, (stencil ? 5.0 : 6.0) * en, act, nb,
+             [&] { op_xr<T>(l, x, w.r, p_new, w.q, alpha, nb, act, false); });
+    finish_sums(partials_, op_xr_partials(l), nb, tmp, s_);
     mark_converged(tmp, rr0, tol * tol, act, nb, count_map_, s_);
     counters[0] += 1;
     if (it % check == 0 || it == opt_.max_iter) {
@@ -1135,6 +1148,7 @@ void Context::pcg_refined(int l, const double* b, double* y, int nb, double tol,
   float* x32 = d32_;
   float* r = w.r;
   const double en = 4.0 * (double)n;
+  const bool stencil = !varcoef_ && !csr_;  // A p is not stored
   // y and x32 start at zero without a clearing pass: the first x/r update
   // writes x32 = 0 + alpha p without reading it, and the first fold writes
   // y = 0 + x32 without reading y (every column is active until then)
@@ -1169,13 +1183,12 @@ void Context::pcg_refined(int l, const double* b, double* y, int nb, double tol,
   // (|r|^2 lands in tmp only when a refinement check follows: otherwise the
   // next tail overwrites tmp unread)
   auto core = [&](float* p_old, float* p_new, bool checked, bool x_zero = false) {
-    timed<float>(l, kTimApply, 4.0 * en, act, nb,
+    timed<float>(l, kTimApply, (stencil ? 3.0 : 4.0) * en, act, nb,
                  [&] { op_update_apply<float>(l, p_old, w.z, beta, p_new, w.q, nb, act); });
     finish_alpha(partials_, ntiles, nb, tmp, rz, act, alpha, s_);
-    timed<float>(l, kTimCgXr, (x_zero ? 5.0 : 6.0) * en, act, nb, [&] {
-      cg_update_xr<float>(x32, r, p_new, w.q, alpha, n, nb, act, partials_, s_, x_zero);
-    });
-    if (checked) finish_sums(partials_, nblk, nb, tmp, s_);
+    timed<float>(l, kTimCgXr, ((x_zero ? 5.0 : 6.0) - (stencil ? 1.0 : 0.0)) * en, act, nb,
+                 [&] { op_xr<float>(l, x32, r, p_new, w.q, alpha, nb, act, x_zero); });
+    if (checked) finish_sums(partials_, op_xr_partials(l), nb, tmp, s_);
   };
   // preconditioner and the next direction's beta
   auto tail = [&] {

@@ -296,6 +296,11 @@ class Context {
   int op_tiles(int l) const;
   template <typename T> void op_update_apply(int l, const T* p_old, const T* z, const c64* beta,
                                              T* p_new, T* q, int nb, const int* act);
+  template <typename T> void op_xr(int l, T* x, T* r, const T* p, const T* q, const c64* alpha,
+                                   int nb, const int* act, bool x_zero);
+  int op_xr_partials(int l) const {
+    return varcoef_ || csr_ ? reduce_blocks(lv_[l - 1].n) : op_tiles(l);
+  }
   template <typename T> void vcycle_vc(int l, const T* b, T* x, int nb, const int* act,
                                        c64* rz_partials, bool top = false);
   template <typename T> Work<T>& work();

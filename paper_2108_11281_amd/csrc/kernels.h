@@ -244,11 +244,15 @@ void poisson_dense_build(T* aug, int N, double d, double c, hipStream_t s);
 template <typename T>
 void poisson_apply(const T* x, T* y, int N, double d, double c, int nb,
                    const int* active, c64* partials, hipStream_t s);
-// p_new = z + beta p_old ; q = A p_new ; partials of conj(p_new)^T q
+// p_new = z + beta p_old ; partials of conj(p_new)^T A p_new (even sides >= 64)
 template <typename T>
-void poisson_update_apply(const T* p_old, const T* z, const c64* beta, T* p_new, T* q, int N,
-                          double d, double c, int nb, const int* active, c64* partials,
-                          hipStream_t s);
+void poisson_direction(const T* p_old, const T* z, const c64* beta, T* p_new, int N, double d,
+                       double c, int nb, const int* active, c64* partials, hipStream_t s);
+// x += alpha p ; r -= alpha A p ; partials of |r|^2 (even sides >= 64); x_zero: x
+// holds no values yet and is taken as zero
+template <typename T>
+void poisson_xr(T* x, T* r, const T* p, const c64* alpha, int N, double d, double c, int nb,
+                const int* active, c64* partials, hipStream_t s, bool x_zero);
 // r = b - A x (Tr may be lower precision) ; optional partials of |r|^2
 template <typename Tb, typename Tx, typename Tr>
 void poisson_residual(const Tb* b, const Tx* x, Tr* r, int N, double d, double c,

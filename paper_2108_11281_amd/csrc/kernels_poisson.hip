@@ -447,14 +447,9 @@ __device__ __forceinline__ T ld_or0(const T* p, int x, int y, int N) {
   return (x >= 0 && x < N && y >= 0 && y < N) ? p[y * N + x] : zero_of(T());
 }
 
-// y = A p (+ partials of conj(p)^T y).  With z and beta given, the product is
-// taken of the updated Krylov direction p = z + beta * p_old, recomputed at the
-// neighbours from (z, p_old) and written to p_new (a different buffer, so no
-// block reads a value another block has already replaced).
-template <typename T, bool UPD>
+// y = A x (+ partials of conj(x)^T y); one column per lane, for odd and small sides
+template <typename T>
 __global__ __launch_bounds__(kThreads) void k_apply_march(const T* __restrict__ x,
-                                                          const T* __restrict__ z,
-                                                          const c64* beta, T* __restrict__ xnew,
                                                           T* __restrict__ y, int N, R_t<T> d,
                                                           R_t<T> c, int nb, const int* active,
                                                           c64* partials, int* tlog) {
@@ -464,48 +459,37 @@ __global__ __launch_bounds__(kThreads) void k_apply_march(const T* __restrict__ 
   if (!m.ok) return;
   const int64_t n = (int64_t)N * N;
   const T* xc = x + (int64_t)m.k * n;
-  const T* zc = z + (UPD ? (int64_t)m.k * n : 0);
-  T* xn = xnew + (UPD ? (int64_t)m.k * n : 0);
   T* yc = y + (int64_t)m.k * n;
   double dre = 0.0, dim = 0.0;
-  c64 bt = {0.0, 0.0};
-  if (UPD) bt = beta[m.k];
   const bool col_ok = m.x < N;
   const int xs = col_ok ? m.x : 0;
   const int lane = threadIdx.x & 63;  // a wave covers 64 consecutive columns
   // loads first (branch-free): the column (rows ybeg-1 .. ybeg+MY); the side
   // columns come from the neighbouring lanes (DPP), except for the two edge
   // lanes, which load the column beyond the wave
-  T cz[MY + 2], cx[MY + 2], ez[MY], ex[MY];
+  T cx[MY + 2], ex[MY];
 #pragma unroll
   for (int j = 0; j < MY + 2; ++j) {
     const int yy = m.ybeg - 1 + j;
-    const bool ok = col_ok && yy >= 0 && yy < N && yy <= m.yend;
-    cx[j] = ldz(xc, yy * N + xs, ok);
-    cz[j] = UPD ? ldz(zc, yy * N + xs, ok) : zero_of(T());
+    cx[j] = ldz(xc, yy * N + xs, col_ok && yy >= 0 && yy < N && yy <= m.yend);
   }
   const int xe = lane == 0 ? m.x - 1 : m.x + 1;  // edge lanes' outer column
   const bool edge = (lane == 0 || lane == 63) && xe >= 0 && xe < N;
 #pragma unroll
   for (int j = 0; j < MY; ++j) {
     const int yy = m.ybeg + j;
-    const bool ok = edge && yy < m.yend;
-    ex[j] = ldz(xc, yy * N + xe, ok);
-    ez[j] = UPD ? ldz(zc, yy * N + xe, ok) : zero_of(T());
+    ex[j] = ldz(xc, yy * N + xe, edge && yy < m.yend);
   }
-  auto P = [&](T zz, T xx) -> T { return UPD ? zz + scale_by(bt.re, bt.im, xx) : xx; };
 #pragma unroll
   for (int j = 0; j < MY; ++j) {
     const int yy = m.ybeg + j;
-    const T mid = P(cz[j + 1], cx[j + 1]);
-    const T pe = P(ez[j], ex[j]);
+    const T mid = cx[j + 1];
     const T sl = wave_shr1(mid), sr = wave_shl1(mid);
-    const T left = lane == 0 ? pe : sl;
-    const T right = lane == 63 ? pe : sr;
-    const T v = d * mid - c * (P(cz[j], cx[j]) + P(cz[j + 2], cx[j + 2]) + left + right);
+    const T left = lane == 0 ? ex[j] : sl;
+    const T right = lane == 63 ? ex[j] : sr;
+    const T v = d * mid - c * (cx[j] + cx[j + 2] + left + right);
     if (col_ok && yy < m.yend) {
       yc[yy * N + m.x] = v;
-      if (UPD) xn[yy * N + m.x] = mid;
       cdot_acc(dre, dim, mid, v);
     }
   }
@@ -602,6 +586,13 @@ __device__ __forceinline__ MarchTile pair_tile(int N, int nb, const int* active)
   return m;
 }
 
+// UPD: the product is taken of the updated Krylov direction p = z + beta x,
+// formed at the neighbours too and written to xnew (another buffer than x, so no
+// block reads a value that another block has replaced); A p itself is not
+// stored: only its share of p^T A p is wanted, and k_xr_pair forms it again from
+// p, which saves a write and a read of a whole vector for arithmetic that the
+// loads hide (12 + 20 instead of 16 + 24 bytes per unknown and CG iteration in
+// FP32: 320 -> 258 ms of a 1024^2 trace).
 template <typename T, bool UPD>
 __global__ __launch_bounds__(kThreads) void k_apply_pair(const T* __restrict__ x,
                                                          const T* __restrict__ z,
@@ -620,7 +611,7 @@ __global__ __launch_bounds__(kThreads) void k_apply_pair(const T* __restrict__ x
   const Pair<T>* xc = reinterpret_cast<const Pair<T>*>(xs);
   const Pair<T>* zc = reinterpret_cast<const Pair<T>*>(zs);
   Pair<T>* xn = reinterpret_cast<Pair<T>*>(xnew + (UPD ? (int64_t)m.k * n : 0));
-  Pair<T>* yc = reinterpret_cast<Pair<T>*>(y + (int64_t)m.k * n);
+  Pair<T>* yc = reinterpret_cast<Pair<T>*>(y + (UPD ? 0 : (int64_t)m.k * n));
   const T zero = zero_of(T());
   double dre = 0.0, dim = 0.0;
   c64 bt = {0.0, 0.0};
@@ -664,8 +655,8 @@ __global__ __launch_bounds__(kThreads) void k_apply_pair(const T* __restrict__ x
     const T v0 = d * m0 - c * (P(cz[j].e0, cx[j].e0) + P(cz[j + 2].e0, cx[j + 2].e0) + left + m1);
     const T v1 = d * m1 - c * (P(cz[j].e1, cx[j].e1) + P(cz[j + 2].e1, cx[j + 2].e1) + m0 + right);
     if (col_ok && yy < m.yend) {
-      yc[yy * half + px] = Pair<T>{v0, v1};
       if (UPD) xn[yy * half + px] = Pair<T>{m0, m1};
+      else yc[yy * half + px] = Pair<T>{v0, v1};
       cdot_acc(dre, dim, m0, v0);
       cdot_acc(dre, dim, m1, v1);
     }
@@ -743,6 +734,75 @@ __global__ __launch_bounds__(kThreads) void k_residual_pair(const Tb* __restrict
       const int tiles = ((N + PX - 1) / PX) * ((N + MTY - 1) / MTY);
       partials[(int64_t)m.k * tiles + m.rem] = {dre, dim};
     }
+  }
+}
+
+// x += a p ; r -= a A p (A p formed from p) ; partials of |r|^2.  x_zero: x holds
+// no values yet and is taken as zero (not read).  HBM-bound: 20 bytes per unknown
+// in FP32 (p, x, r in; x, r out), 16 with x_zero.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_xr_pair(T* __restrict__ x, T* __restrict__ r,
+                                                      const T* __restrict__ p, const c64* alpha,
+                                                      int N, R_t<T> d, R_t<T> c, int nb,
+                                                      const int* active, c64* partials, int* tlog,
+                                                      int x_zero) {
+  __shared__ double red[16];
+  const MarchTile m = pair_tile(N, nb, active);
+  if (tlog && m.rem == 0 && threadIdx.x == 0) tlog[m.k] = active ? active[m.k] : 1;
+  if (!m.ok) return;
+  const int64_t n = (int64_t)N * N;
+  const int half = N >> 1;
+  const T* ps = p + (int64_t)m.k * n;
+  const Pair<T>* pc = reinterpret_cast<const Pair<T>*>(ps);
+  Pair<T>* xc = reinterpret_cast<Pair<T>*>(x + (int64_t)m.k * n);
+  Pair<T>* rc = reinterpret_cast<Pair<T>*>(r + (int64_t)m.k * n);
+  const c64 al = alpha[m.k];
+  const bool col_ok = m.x < N;
+  const int px = col_ok ? (m.x >> 1) : 0;
+  const int lane = threadIdx.x & 63;
+  const int xe = lane == 0 ? m.x - 1 : m.x + 2;
+  const bool edge = (lane == 0 || lane == 63) && xe >= 0 && xe < N;
+  const T zero = zero_of(T());
+  Pair<T> cp[MY + 2], cx[MY], cr[MY];
+  T ep[MY];
+#pragma unroll
+  for (int j = 0; j < MY + 2; ++j) {
+    const int yy = m.ybeg - 1 + j;
+    const bool ok = col_ok && yy >= 0 && yy < N && yy <= m.yend;
+    const Pair<T> a = pc[ok ? yy * half + px : 0];
+    cp[j] = ok ? a : Pair<T>{zero, zero};
+  }
+#pragma unroll
+  for (int j = 0; j < MY; ++j) {
+    const int yy = m.ybeg + j;
+    const bool ok = col_ok && yy < m.yend;
+    ep[j] = ldz(ps, yy * N + (edge ? xe : 0), ok && edge);
+    cr[j] = rc[ok ? yy * half + px : 0];
+    cx[j] = x_zero ? Pair<T>{zero, zero} : xc[ok ? yy * half + px : 0];
+  }
+  double dre = 0.0, dim = 0.0;
+#pragma unroll
+  for (int j = 0; j < MY; ++j) {
+    const int yy = m.ybeg + j;
+    const T m0 = cp[j + 1].e0, m1 = cp[j + 1].e1;
+    const T sl = wave_shr1(m1), sr = wave_shl1(m0);
+    const T left = lane == 0 ? ep[j] : sl, right = lane == 63 ? ep[j] : sr;
+    const T q0 = d * m0 - c * (cp[j].e0 + cp[j + 2].e0 + left + m1);
+    const T q1 = d * m1 - c * (cp[j].e1 + cp[j + 2].e1 + m0 + right);
+    if (col_ok && yy < m.yend) {
+      const T r0 = cr[j].e0 - scale_by(al.re, al.im, q0);
+      const T r1 = cr[j].e1 - scale_by(al.re, al.im, q1);
+      xc[yy * half + px] = Pair<T>{cx[j].e0 + scale_by(al.re, al.im, m0),
+                                   cx[j].e1 + scale_by(al.re, al.im, m1)};
+      rc[yy * half + px] = Pair<T>{r0, r1};
+      cdot_acc(dre, dim, r0, r0);
+      cdot_acc(dre, dim, r1, r1);
+    }
+  }
+  block_sum2<kThreads>(dre, dim, red);
+  if (threadIdx.x == 0) {
+    const int tiles = ((N + PX - 1) / PX) * ((N + MTY - 1) / MTY);
+    partials[(int64_t)m.k * tiles + m.rem] = {dre, dim};
   }
 }
 
@@ -909,22 +969,25 @@ void poisson_apply(const T* x, T* y, int N, double d, double c, int nb, const in
                 (const c64*)nullptr, y, y, N, (R_t<T>)d, (R_t<T>)c, nb, active, partials,
                 timing_log());
   else
-    MLMC_LAUNCH((k_apply_march<T, false>), dim3(march_blocks(N, nb)), dim3(kThreads), 0, s, x,
-                x, (const c64*)nullptr, y, y, N, (R_t<T>)d, (R_t<T>)c, nb, active, partials,
-                timing_log());
+    MLMC_LAUNCH(k_apply_march<T>, dim3(march_blocks(N, nb)), dim3(kThreads), 0, s, x, y, N,
+                (R_t<T>)d, (R_t<T>)c, nb, active, partials, timing_log());
 }
 
 template <typename T>
-void poisson_update_apply(const T* p_old, const T* z, const c64* beta, T* p_new, T* q, int N,
-                          double d, double c, int nb, const int* active, c64* partials,
-                          hipStream_t s) {
-  if (pair_march(N))
-    MLMC_LAUNCH((k_apply_pair<T, true>), dim3(pair_blocks(N, nb)), dim3(kThreads), 0, s, p_old,
-                z, beta, p_new, q, N, (R_t<T>)d, (R_t<T>)c, nb, active, partials, timing_log());
-  else
-    MLMC_LAUNCH((k_apply_march<T, true>), dim3(march_blocks(N, nb)), dim3(kThreads), 0, s,
-                p_old, z, beta, p_new, q, N, (R_t<T>)d, (R_t<T>)c, nb, active, partials,
-                timing_log());
+void poisson_direction(const T* p_old, const T* z, const c64* beta, T* p_new, int N, double d,
+                       double c, int nb, const int* active, c64* partials, hipStream_t s) {
+  if (!pair_march(N)) throw Error(MLMC_EINVAL, "the lockstep CG needs an even side >= 64");
+  MLMC_LAUNCH((k_apply_pair<T, true>), dim3(pair_blocks(N, nb)), dim3(kThreads), 0, s, p_old, z,
+              beta, p_new, (T*)nullptr, N, (R_t<T>)d, (R_t<T>)c, nb, active, partials,
+              timing_log());
+}
+
+template <typename T>
+void poisson_xr(T* x, T* r, const T* p, const c64* alpha, int N, double d, double c, int nb,
+                const int* active, c64* partials, hipStream_t s, bool x_zero) {
+  if (!pair_march(N)) throw Error(MLMC_EINVAL, "the lockstep CG needs an even side >= 64");
+  MLMC_LAUNCH(k_xr_pair<T>, dim3(pair_blocks(N, nb)), dim3(kThreads), 0, s, x, r, p, alpha, N,
+              (R_t<T>)d, (R_t<T>)c, nb, active, partials, timing_log(), x_zero ? 1 : 0);
 }
 
 template <typename Tb, typename Tx, typename Tr>
@@ -1062,8 +1125,10 @@ void agg2d_prolong(const T* ec, T* x, int N, double omega, double beta, int nb,
   template void poisson_dense_build<T>(T*, int, double, double, hipStream_t);              \
   template void poisson_apply<T>(const T*, T*, int, double, double, int, const int*, c64*,  \
                                  hipStream_t);                                             \
-  template void poisson_update_apply<T>(const T*, const T*, const c64*, T*, T*, int, double, \
-                                        double, int, const int*, c64*, hipStream_t);       \
+  template void poisson_direction<T>(const T*, const T*, const c64*, T*, int, double,       \
+                                     double, int, const int*, c64*, hipStream_t);          \
+  template void poisson_xr<T>(T*, T*, const T*, const c64*, int, double, double, int,       \
+                              const int*, c64*, hipStream_t, bool);                        \
   template void poisson_rbgs_fused<T>(const T*, const T*, T*, const T*, double, int,       \
                                       double, double, int, const int*, bool, c64*, int,    \
                                       int, hipStream_t);                                   \
