@@ -255,6 +255,7 @@ void Context::alloc_common() {
   for (int i = 0; i < kNumScalars; ++i) scal_[i] = sc + (int64_t)i * nb_;
   act_outer_ = dalloc_n<int>(nb_);
   act_inner_ = dalloc_n<int>(nb_);
+  y_plane_ = dalloc_n<int>(nb_);
   count_dev_ = dalloc_n<int>(8);
   MLMC_HIP(hipHostMalloc((void**)&count_host_, 8 * sizeof(int), hipHostMallocMapped));
   MLMC_HIP(hipHostGetDevicePointer((void**)&count_map_, count_host_, 0));
@@ -1101,14 +1102,13 @@ int Context::pcg(int l, const T* b, T* x, int nb, int* act, double tol, c64* las
   for (it = 1; it <= opt_.max_iter; ++it) {
     timed<T>(l, kTimApply, (stencil ? 3.0 : 4.0) * en, act, nb,
              [&] { op_update_apply<T>(l, p_old, w.z, beta, p_new, w.q, nb, act); });
-    finish_alpha(partials_, ntiles, nb, tmp, rz, act, alpha, s_);
-    if (lastcorr) cg_lastcorr(alpha, rz, act, lastcorr, nb, s_);
+    finish_alpha(partials_, ntiles, nb, tmp, rz, act, alpha, s_, lastcorr);
     timed<T>(l, kTimCgXr, (stencil ? 5.0 : 6.0) * en, act, nb,
              [&] { op_xr<T>(l, x, w.r, p_new, w.q, alpha, nb, act, false); });
-    finish_sums(partials_, op_xr_partials(l), nb, tmp, s_);
-    mark_converged(tmp, rr0, tol * tol, act, nb, count_map_, s_);
+    finish_mark(partials_, op_xr_partials(l), nb, tmp, rr0, tol * tol, act, s_);
     counters[0] += 1;
     if (it % check == 0 || it == opt_.max_iter) {
+      count_active(act, nb, count_map_, s_);
       if (read_count() == 0) break;
     }
     vcycle<T>(l, w.r, w.z, nb, act, partials_, true);
@@ -1151,8 +1151,11 @@ void Context::pcg_refined(int l, const double* b, double* y, int nb, double tol,
   const bool stencil = !varcoef_ && !csr_;  // A p is not stored
   // y and x32 start at zero without a clearing pass: the first x/r update
   // writes x32 = 0 + alpha p without reading it, and the first fold writes
-  // y = 0 + x32 without reading y (every column is active until then)
-  bool y_written = false;
+  // y = 0 + x32 without reading y (every column is active until then).  The 2D
+  // Poisson fold does not clear x32 either: the update after a fold writes it
+  // without reading.
+  int folds = 0;
+  int* dst = y_plane_;  // 2D Poisson: the plane (y or r64_) of each column's y
   // The refinements read b from an FP32 copy when every entry of b is an FP32
   // number (the 2D Poisson probes and their 2x2 restrictions, multiples of 1/2
   // of small integers): the same values for 4 instead of 8 bytes per unknown
@@ -1200,86 +1203,105 @@ void Context::pcg_refined(int l, const double* b, double* y, int nb, double tol,
   auto due = [&] {
     refine_due(tmp, rr_upd, bb, delta2, tol * tol, act, nb, count_map_ + 1, s_);
   };
+  bool folded = false;  // since the last x/r update
   // after due(): refine in FP64 if needed; true when every column converged
   auto refine = [&](bool force) {
     MLMC_HIP(hipStreamSynchronize(s_));
     if (count_host_[1] == 0 && !force) return false;
     const bool b_fp32 = try32 && count_host_[4] == 0;
     const double bbytes = b_fp32 ? 4.0 : 8.0;
-    // y += x32, bd = b^T x32, x32 = 0 in one pass (FP64 y, b and FP32 x32 in;
-    // y, x32 out: 32 bytes per unknown, 28 with b in FP32; 8 fewer on the
-    // first fold, which does not read y)
-    const bool y_zero = !y_written;
-    timed<double>(l, kTimIrFold, ((y_zero ? 16.0 : 24.0) + bbytes) * (double)n, act, nb, [&] {
-      if (b_fp32)
-        ir_fold(y, x32, b32_, n, nb, act, partials_, s_, y_zero);
-      else
-        ir_fold(y, x32, b, n, nb, act, partials_, s_, y_zero);
-    });
-    y_written = true;
-    finish_sums(partials_, nblk, nb, bd, s_);
-    timed<double>(l, kTimIrResidual, (12.0 + bbytes) * (double)n, act, nb, [&] {
-      if (b_fp32)
-        poisson_residual<float, double, float>(b32_, y, r, L.side, L.d, L.c, nb, act, partials_,
-                                               s_);
-      else
-        op_residual<double, double, float>(l, b, y, r, nb, act, partials_);
-    });
-    finish_sums(partials_, ntiles, nb, rr_new, s_);
-    ir_stated_error(bd, rr_upd, rr_new, act, err, nb, s_);
+    folded = true;
+    const c64 *pbd = nullptr, *prr = partials_;
+    int nsums = ntiles;
+    if (stencil) {
+      // y += x32, bd = b^T x32 and r = b - A y in one pass, y alternating between
+      // y and r64_
+      const int to = folds % 2;
+      double* planes[2] = {y, r64_};
+      const double* from = folds ? planes[1 - to] : nullptr;
+      nsums = poisson_fold_tiles(L.side);
+      c64* pr = partials_ + (int64_t)nsums * nb;
+      timed<double>(l, kTimIrResidual, ((folds ? 24.0 : 16.0) + bbytes) * (double)n, act, nb, [&] {
+        if (b_fp32)
+          poisson_fold_residual<float>(b32_, from, x32, planes[to], r, L.side, L.d, L.c, nb, act,
+                                       partials_, pr, dst, to, s_);
+        else
+          poisson_fold_residual<double>(b, from, x32, planes[to], r, L.side, L.d, L.c, nb, act,
+                                        partials_, pr, dst, to, s_);
+      });
+      pbd = partials_;
+      prr = pr;
+    } else {
+      // y += x32, bd = b^T x32, x32 = 0 in one pass (FP64 y, b and FP32 x32 in;
+      // y, x32 out: 32 bytes per unknown, 8 fewer on the first fold, which does
+      // not read y)
+      timed<double>(l, kTimIrFold, (folds ? 32.0 : 24.0) * (double)n, act, nb,
+                    [&] { ir_fold(y, x32, b, n, nb, act, partials_, s_, folds == 0); });
+      finish_sums(partials_, nblk, nb, bd, s_);
+      timed<double>(l, kTimIrResidual, 20.0 * (double)n, act, nb,
+                    [&] { op_residual<double, double, float>(l, b, y, r, nb, act, partials_); });
+    }
+    ++folds;
     // the kept direction stays only while the recursion's residual (tmp, from
     // the last x/r update) still describes the true one; when the recursion has
     // run far below FP32 accuracy (a nearly exact preconditioner) restart it
-    cg_restart_on_drift(rr_new, tmp, rz, act, 100.0, nb, s_);
-    select_active(rr_upd, rr_new, act, nb, s_);
-    mark_converged(rr_new, bb, tol * tol, act, nb, count_map_, s_);
+    refine_finish(pbd, prr, nsums, nb, bd, rr_upd, rr_new, tmp, rz, err, bb, tol * tol, 100.0,
+                  act, count_map_, s_);
     counters[1] += 1;
     return read_count() == 0;
   };
   // iterations 1 and 2 directly (the first direction is z itself), then pairs of
   // iterations between refinement checks: (p2 -> p), (p -> p2), which repeat
-  // with fixed pointers and can be replayed from a graph
-  int it = 1;
-  core(w.z, P1, it == max_it, true);
-  counters[0] += 1;
-  if (it == max_it) {
-    due();
-    refine(true);
-    return;
-  }
-  tail();
-  core(P1, P2, true);
-  counters[0] += 1;
-  it = 2;
-  due();
-  if (refine(it == max_it)) return;
-  const bool use_graph = opt_.graphs && !timing_;
-  while (it < max_it) {
-    if (it + 2 <= max_it) {
-      auto pair = [&] {
-        tail();
-        core(P2, P1, false);
-        tail();
-        core(P1, P2, true);
-        due();
-      };
-      if (use_graph)
-        replay({0, l, nb, 0}, pair);
-      else
-        pair();
-      counters[0] += 2;
-      it += 2;
-      if (refine(it == max_it)) return;
-    } else {
-      tail();
-      core(P2, P1, true);
-      counters[0] += 1;
-      it += 1;
+  // with fixed pointers and can be replayed from a graph (one for the pairs that
+  // follow a fold without a cleared x32, one for the others)
+  auto run = [&] {
+    int it = 1;
+    core(w.z, P1, it == max_it, true);
+    counters[0] += 1;
+    if (it == max_it) {
       due();
       refine(true);
       return;
     }
-  }
+    tail();
+    core(P1, P2, true);
+    counters[0] += 1;
+    it = 2;
+    due();
+    if (refine(it == max_it)) return;
+    const bool use_graph = opt_.graphs && !timing_;
+    while (it < max_it) {
+      const bool x_zero = stencil && folded;
+      folded = false;
+      if (it + 2 <= max_it) {
+        auto pair = [&] {
+          tail();
+          core(P2, P1, false, x_zero);
+          tail();
+          core(P1, P2, true);
+          due();
+        };
+        if (use_graph)
+          replay({0, l, nb, x_zero ? 1 : 0}, pair);
+        else
+          pair();
+        counters[0] += 2;
+        it += 2;
+        if (refine(it == max_it)) return;
+      } else {
+        tail();
+        core(P2, P1, true, x_zero);
+        counters[0] += 1;
+        it += 1;
+        due();
+        refine(true);
+        return;
+      }
+    }
+  };
+  run();
+  // columns whose last fold went to the second plane
+  if (stencil && folds > 1) poisson_collect(y, r64_, dst, n, nb, s_);
 }
 
 void Context::replay(const std::array<int, 4>& key, const std::function<void()>& body) {

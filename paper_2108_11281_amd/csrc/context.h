@@ -338,7 +338,7 @@ class Context {
   // Launches the HIP graph of `body`, captured on the context stream at the
   // key's first use; the host-side counters the body advances (recorded while
   // capturing) advance by the same amounts at every launch.  Keys: {0, level,
-  // batch width, 0} the refined CG's iteration pairs; {1 (complex64) or 2
+  // batch width, first update takes x32 as zero} the refined CG's pairs; {1 (complex64) or 2
   // (complex128), level, batch width, iteration + 64 (learned smoother on)}
   // the FGMRES iterations.
   void replay(const std::array<int, 4>& key, const std::function<void()>& body);
@@ -444,6 +444,7 @@ class Context {
          kNn, kNumScalars };
   c64* scal_[kNumScalars] = {};
   int *act_outer_ = nullptr, *act_inner_ = nullptr, *count_dev_ = nullptr;  // count_dev_: 8 ints
+  int* y_plane_ = nullptr;  // refined 2D Poisson CG: which plane holds each column's y
   // pinned host counts (8 ints) and their device address: the single-thread
   // count kernels whose results the host tests store there directly, so a
   // check needs no copy, only the stream synchronisation

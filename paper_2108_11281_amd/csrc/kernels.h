@@ -73,15 +73,23 @@ void vec_dot_partials(const T* x, const T* y, int64_t n, int nb, const int* acti
                       c64* partials, hipStream_t s);
 // out[k] = fixed-order sum of column k's nblk partials
 void finish_sums(const c64* partials, int nblk, int nb, c64* out, hipStream_t s);
-// refined CG: rz = 0 (so the next beta is 0) for active columns whose FP64
-// residual after a refinement exceeds factor x the recursion's own residual
-void cg_restart_on_drift(const c64* rr_new, const c64* rr_rec, c64* rz, const int* active,
-                         double factor, int nb, hipStream_t s);
 
 // ----- Krylov scalars (one thread per column) --------------------------------
-// finish_sums into pq, then cg_alpha from it, in one launch (same values)
+// finish_sums into pq, then cg_alpha from it, in one launch (same values);
+// lastcorr (nullable): alpha rz of active columns (the CG step's share of b^H x)
 void finish_alpha(const c64* partials, int nblk, int nb, c64* pq, const c64* rz,
-                  const int* active, c64* alpha, hipStream_t s);
+                  const int* active, c64* alpha, hipStream_t s, c64* lastcorr = nullptr);
+// finish_sums into rr of the active columns, then their convergence test
+// (mark_converged's, without the count)
+void finish_mark(const c64* partials, int nblk, int nb, c64* rr, const c64* ref, double tol2,
+                 int* active, hipStream_t s);
+// the scalars of a refinement of the refined CG, active columns: bd = sums of pbd
+// (nullable: bd is given), rr_new = rr_upd = sums of prr, the stated error, rz = 0
+// (so the next beta is 0) where rr_new exceeds factor x the recursion's own
+// residual rr_rec, the convergence test and the count of columns left
+void refine_finish(const c64* pbd, const c64* prr, int nblk, int nb, c64* bd, c64* rr_upd,
+                   c64* rr_new, const c64* rr_rec, c64* rz, c64* err, const c64* bb, double tol2,
+                   double factor, int* active, int* count, hipStream_t s);
 // finish_sums into rz_new, then cg_beta from it, in one launch (same values)
 void finish_beta(const c64* partials, int nblk, int nb, c64* rz_new, c64* rz, const int* active,
                  c64* beta, hipStream_t s);
@@ -105,10 +113,6 @@ void ir_stated_error(const c64* bd, const c64* rr_old, const c64* rr_new, const 
                      c64* err, int nb, hipStream_t s);
 // dst[k] = active[k] ? src[k] : dst[k]
 void select_active(c64* dst, const c64* src, const int* active, int nb, hipStream_t s);
-// lastcorr[k] = alpha[k]*rz[k] for active columns (CG step's share of b^H x)
-void cg_lastcorr(const c64* alpha, const c64* rz, const int* active, c64* lastcorr, int nb,
-                 hipStream_t s);
-
 // x += alpha p ; r -= alpha q ; partials of |r|^2.  x_zero: x is taken as zero
 // and not read (the first update of a solve), x = alpha p
 template <typename T>
@@ -123,9 +127,6 @@ void cg_update_p(T* p, const T* z, const c64* beta, int64_t n, int nb,
 // blocks per column, as vec_dot_partials(b, d)), d = 0.  y_zero: y is taken as
 // zero and not read (the first fold of a solve), y = 0 + d
 void ir_fold(double* y, float* d, const double* b, int64_t n, int nb, const int* active,
-             c64* partials, hipStream_t s, bool y_zero = false);
-// the same with b given in FP32 (exactly: the values of the FP64 b)
-void ir_fold(double* y, float* d, const float* b, int64_t n, int nb, const int* active,
              c64* partials, hipStream_t s, bool y_zero = false);
 // r = b32 = b rounded to FP32 (nb columns of n); *inexact = 0 when every entry of
 // b is an FP32 number (b32 then holds b exactly), else 1; partials of b^T b as
@@ -253,6 +254,17 @@ void poisson_direction(const T* p_old, const T* z, const c64* beta, T* p_new, in
 template <typename T>
 void poisson_xr(T* x, T* r, const T* p, const c64* alpha, int N, double d, double c, int nb,
                 const int* active, c64* partials, hipStream_t s, bool x_zero);
+// y_out = y_in + x32 (y_in nullptr: zero), r = b - A y_out in FP32, partials of
+// b^T x32 and |r|^2 (poisson_fold_tiles per column); y_in and y_out are different
+// planes, dst[k] = which for the active columns (even sides >= 64)
+int poisson_fold_tiles(int N);
+template <typename Tb>
+void poisson_fold_residual(const Tb* b, const double* yin, const float* x, double* yout, float* r,
+                           int N, double d, double c, int nb, const int* active, c64* pbd,
+                           c64* prr, int* dst, int which, hipStream_t s);
+// y[k] = alt[k] where dst[k] != 0
+void poisson_collect(double* y, const double* alt, const int* dst, int64_t n, int nb,
+                     hipStream_t s);
 // r = b - A x (Tr may be lower precision) ; optional partials of |r|^2
 template <typename Tb, typename Tx, typename Tr>
 void poisson_residual(const Tb* b, const Tx* x, Tr* r, int N, double d, double c,

@@ -8,6 +8,8 @@
 // 8 XCDs, so block b is mapped to the logical tile range owned by XCD b % 8 and
 // each XCD sweeps a contiguous run of tiles (neighbouring tiles share halo
 // cache lines in that XCD's L2).
+#include <algorithm>
+
 #include "kernels.h"
 #include "lanes.h"
 
@@ -571,8 +573,10 @@ __global__ __launch_bounds__(kThreads) void k_residual_march(const Tb* __restric
 // of the partial sums differs (tiles of 128 x 4*MY).
 constexpr int PX = 128;
 
+template <int RY = MY>
 __device__ __forceinline__ MarchTile pair_tile(int N, int nb, const int* active) {
-  const int nbx = (N + PX - 1) / PX, nby = (N + MTY - 1) / MTY;
+  constexpr int TY = MW * RY;
+  const int nbx = (N + PX - 1) / PX, nby = (N + TY - 1) / TY;
   const int t = xcd_tile_index(nbx * nby * nb);
   MarchTile m;
   m.k = t / (nbx * nby);
@@ -580,8 +584,8 @@ __device__ __forceinline__ MarchTile pair_tile(int N, int nb, const int* active)
   const int by = m.rem / nbx, bx = m.rem - by * nbx;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   m.x = bx * PX + 2 * lane;  // even column of the lane's pair
-  m.ybeg = by * MTY + w * MY;
-  m.yend = m.ybeg + MY < N ? m.ybeg + MY : N;
+  m.ybeg = by * TY + w * RY;
+  m.yend = m.ybeg + RY < N ? m.ybeg + RY : N;
   m.ok = m.k < nb && !(active && !active[m.k]);
   return m;
 }
@@ -601,7 +605,7 @@ __global__ __launch_bounds__(kThreads) void k_apply_pair(const T* __restrict__ x
                                                          R_t<T> c, int nb, const int* active,
                                                          c64* partials, int* tlog) {
   __shared__ double red[16];
-  const MarchTile m = pair_tile(N, nb, active);
+  const MarchTile m = pair_tile<>(N, nb, active);
   if (tlog && m.rem == 0 && threadIdx.x == 0) tlog[m.k] = active ? active[m.k] : 1;
   if (!m.ok) return;
   const int64_t n = (int64_t)N * N;
@@ -678,7 +682,7 @@ __global__ __launch_bounds__(kThreads) void k_residual_pair(const Tb* __restrict
                                                             const int* active, c64* partials,
                                                             int* tlog) {
   __shared__ double red[16];
-  const MarchTile m = pair_tile(N, nb, active);
+  const MarchTile m = pair_tile<>(N, nb, active);
   if (tlog && m.rem == 0 && threadIdx.x == 0) tlog[m.k] = active ? active[m.k] : 1;
   if (!m.ok) return;
   const int64_t n = (int64_t)N * N;
@@ -747,7 +751,7 @@ __global__ __launch_bounds__(kThreads) void k_xr_pair(T* __restrict__ x, T* __re
                                                       const int* active, c64* partials, int* tlog,
                                                       int x_zero) {
   __shared__ double red[16];
-  const MarchTile m = pair_tile(N, nb, active);
+  const MarchTile m = pair_tile<>(N, nb, active);
   if (tlog && m.rem == 0 && threadIdx.x == 0) tlog[m.k] = active ? active[m.k] : 1;
   if (!m.ok) return;
   const int64_t n = (int64_t)N * N;
@@ -804,6 +808,112 @@ __global__ __launch_bounds__(kThreads) void k_xr_pair(T* __restrict__ x, T* __re
     const int tiles = ((N + PX - 1) / PX) * ((N + MTY - 1) / MTY);
     partials[(int64_t)m.k * tiles + m.rem] = {dre, dim};
   }
+}
+
+// FP64 refinement of the FP32 correction in one pass: y_out = y_in + x32, partials
+// of b^T x32 (the stated-error share) and r = b - A y_out (rounded to FP32) with
+// its |r|^2.  The product needs y_out at the neighbours, formed there from y_in and
+// x32, so y alternates between two planes (y_in == nullptr: zero); dst[k] = `which`
+// records where column k's y is.  HBM-bound: 28 bytes per unknown (20 from zero;
+// 4 more with an FP64 b) where the fold (28) and the residual (16) were separate
+// passes; x32 needs no clearing, its next update writes it without reading.  Per
+// 1024^2 trace 110 -> 75 ms (5.0 TB/s on the finest grid; 95 ms with 8 rows per
+// wave instead of 4, whose 163 registers leave three waves per SIMD).
+constexpr int FY = 4;  // rows per wave
+template <typename Tb, bool HY>
+__global__ __launch_bounds__(kThreads) void k_fold_residual_pair(
+    const Tb* __restrict__ b, const double* __restrict__ yin, const float* __restrict__ x,
+    double* __restrict__ yout, float* __restrict__ r, int N, double d, double c, int nb,
+    const int* active, c64* pbd, c64* prr, int* dst, int which, int* tlog) {
+  __shared__ double red[16];
+  const MarchTile m = pair_tile<FY>(N, nb, active);
+  if (tlog && m.rem == 0 && threadIdx.x == 0) tlog[m.k] = active ? active[m.k] : 1;
+  if (!m.ok) return;
+  if (m.rem == 0 && threadIdx.x == 0) dst[m.k] = which;
+  const int64_t n = (int64_t)N * N, off = (int64_t)m.k * n;
+  const int half = N >> 1;
+  const float* xs = x + off;
+  const double* ys = yin + (HY ? off : 0);
+  const Pair<float>* xc = reinterpret_cast<const Pair<float>*>(xs);
+  const Pair<double>* yc = reinterpret_cast<const Pair<double>*>(ys);
+  const Pair<Tb>* bc = reinterpret_cast<const Pair<Tb>*>(b + off);
+  Pair<double>* yo = reinterpret_cast<Pair<double>*>(yout + off);
+  Pair<float>* rc = reinterpret_cast<Pair<float>*>(r + off);
+  const bool col_ok = m.x < N;
+  const int px = col_ok ? (m.x >> 1) : 0;
+  const int lane = threadIdx.x & 63;
+  const int xe = lane == 0 ? m.x - 1 : m.x + 2;
+  const bool edge = (lane == 0 || lane == 63) && xe >= 0 && xe < N;
+  Pair<double> cy[FY + 2];
+  Pair<float> cx[FY + 2];
+  double ey[FY];
+  float ex[FY];
+  Pair<Tb> bb[FY];
+#pragma unroll
+  for (int j = 0; j < FY + 2; ++j) {
+    const int yy = m.ybeg - 1 + j;
+    const bool ok = col_ok && yy >= 0 && yy < N && yy <= m.yend;
+    const int at = ok ? yy * half + px : 0;
+    const Pair<float> a = xc[at];
+    cx[j] = ok ? a : Pair<float>{0.f, 0.f};
+    cy[j] = Pair<double>{0.0, 0.0};
+    if (HY) {
+      const Pair<double> v = yc[at];
+      if (ok) cy[j] = v;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < FY; ++j) {
+    const int yy = m.ybeg + j;
+    const bool ok = col_ok && yy < m.yend;
+    const int at = yy * N + (edge ? xe : 0);
+    ex[j] = ldz(xs, at, ok && edge);
+    ey[j] = HY ? ldz(ys, at, ok && edge) : 0.0;
+    const Pair<Tb> q = bc[ok ? yy * half + px : 0];
+    bb[j] = ok ? q : Pair<Tb>{(Tb)0, (Tb)0};
+  }
+  auto fold = [](Pair<double> y, Pair<float> v) {
+    return Pair<double>{y.e0 + (double)v.e0, y.e1 + (double)v.e1};
+  };
+  double dbd = 0.0, drr = 0.0;
+  Pair<double> up = fold(cy[0], cx[0]), mid = fold(cy[1], cx[1]);
+#pragma unroll
+  for (int j = 0; j < FY; ++j) {
+    const int yy = m.ybeg + j;
+    const Pair<double> dn = fold(cy[j + 2], cx[j + 2]);
+    const double e = ey[j] + (double)ex[j];
+    const double sl = wave_shr1(mid.e1), sr = wave_shl1(mid.e0);
+    const double l0 = lane == 0 ? e : sl, r1 = lane == 63 ? e : sr;
+    const double v0 = (double)bb[j].e0 - (d * mid.e0 - c * (up.e0 + dn.e0 + l0 + mid.e1));
+    const double v1 = (double)bb[j].e1 - (d * mid.e1 - c * (up.e1 + dn.e1 + mid.e0 + r1));
+    if (col_ok && yy < m.yend) {
+      yo[yy * half + px] = mid;
+      rc[yy * half + px] = Pair<float>{(float)v0, (float)v1};
+      dbd += (double)bb[j].e0 * (double)cx[j + 1].e0;
+      dbd += (double)bb[j].e1 * (double)cx[j + 1].e1;
+      drr += v0 * v0;
+      drr += v1 * v1;
+    }
+    up = mid;
+    mid = dn;
+  }
+  block_sum2<kThreads>(dbd, drr, red);
+  if (threadIdx.x == 0) {
+    const int tiles = ((N + PX - 1) / PX) * ((N + MW * FY - 1) / (MW * FY));
+    pbd[(int64_t)m.k * tiles + m.rem] = {dbd, 0.0};
+    prr[(int64_t)m.k * tiles + m.rem] = {drr, 0.0};
+  }
+}
+
+// y[k] = alt[k] for the columns whose solution lies in the second plane (dst[k])
+__global__ void k_collect(double* __restrict__ y, const double* __restrict__ alt, const int* dst,
+                          int64_t n) {
+  const int k = blockIdx.y;
+  if (!dst[k]) return;
+  const int64_t off = (int64_t)k * n;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    y[off + i] = alt[off + i];
 }
 
 // rc = R (b - A x): one thread per coarse column, RR coarse rows (2*RR fine
@@ -1001,6 +1111,34 @@ void poisson_residual(const Tb* b, const Tx* x, Tr* r, int N, double d, double c
                 b, x, r, N, (R_t<Tx>)d, (R_t<Tx>)c, nb, active, partials, timing_log());
 }
 
+int poisson_fold_tiles(int N) {
+  return ((N + PX - 1) / PX) * ((N + MW * FY - 1) / (MW * FY));
+}
+template <typename Tb>
+void poisson_fold_residual(const Tb* b, const double* yin, const float* x, double* yout, float* r,
+                           int N, double d, double c, int nb, const int* active, c64* pbd,
+                           c64* prr, int* dst, int which, hipStream_t s) {
+  if (!pair_march(N)) throw Error(MLMC_EINVAL, "the lockstep CG needs an even side >= 64");
+  if (yin)
+    MLMC_LAUNCH((k_fold_residual_pair<Tb, true>), dim3(poisson_fold_tiles(N) * nb), dim3(kThreads), 0, s,
+                b, yin, x, yout, r, N, d, c, nb, active, pbd, prr, dst, which, timing_log());
+  else
+    MLMC_LAUNCH((k_fold_residual_pair<Tb, false>), dim3(poisson_fold_tiles(N) * nb), dim3(kThreads), 0, s,
+                b, yout, x, yout, r, N, d, c, nb, active, pbd, prr, dst, which, timing_log());
+}
+template void poisson_fold_residual<float>(const float*, const double*, const float*, double*,
+                                           float*, int, double, double, int, const int*, c64*,
+                                           c64*, int*, int, hipStream_t);
+template void poisson_fold_residual<double>(const double*, const double*, const float*, double*,
+                                            float*, int, double, double, int, const int*, c64*,
+                                            c64*, int*, int, hipStream_t);
+
+void poisson_collect(double* y, const double* alt, const int* dst, int64_t n, int nb,
+                     hipStream_t s) {
+  const int64_t blocks = std::min<int64_t>((n + 1023) / 1024, 256);
+  hipLaunchKernelGGL(k_collect, dim3((unsigned)blocks, nb), dim3(256), 0, s, y, alt, dst, n);
+}
+
 template <typename T, int SR, int NSW>
 static void rbgs_march_launch(const T* xin, const T* b, T* xout, const T* ec, double omega, int N,
                               double d, double c, int nb, const int* active, bool reverse,
@@ -1152,8 +1290,5 @@ template void poisson_residual<double, double, float>(const double*, const doubl
 template void poisson_residual<float, float, float>(const float*, const float*, float*, int,
                                                     double, double, int, const int*, c64*,
                                                     hipStream_t);
-template void poisson_residual<float, double, float>(const float*, const double*, float*, int,
-                                                     double, double, int, const int*, c64*,
-                                                     hipStream_t);
 
 }  // namespace mlmc

@@ -72,13 +72,52 @@ __global__ __launch_bounds__(kThreads) void k_finish(const c64* partials, int nb
 // in the same order, then the scalar rule of k_cg_alpha / k_cg_beta
 __global__ __launch_bounds__(kThreads) void k_finish_alpha(const c64* partials, int nblk,
                                                            c64* pq, const c64* rz,
-                                                           const int* active, c64* alpha) {
+                                                           const int* active, c64* alpha,
+                                                           c64* lastcorr) {
   __shared__ double lds[16];
   const int k = blockIdx.x;
   const c64 v = body::finish(partials, nblk, k, lds);
   if (threadIdx.x == 0) {
     pq[k] = v;
     body::alpha_rule(v, rz, active, k, alpha);
+    if (lastcorr && (!active || active[k])) lastcorr[k] = {alpha[k].re * rz[k].re, 0.0};
+  }
+}
+
+// k_finish followed by the convergence test of the same column (mark_rule)
+__global__ __launch_bounds__(kThreads) void k_finish_mark(const c64* partials, int nblk, c64* rr,
+                                                          const c64* ref, double tol2,
+                                                          int* active) {
+  __shared__ double lds[16];
+  const int k = blockIdx.x;
+  if (!active[k]) return;
+  const c64 v = body::finish(partials, nblk, k, lds);
+  if (threadIdx.x == 0) {
+    rr[k] = v;
+    body::mark_rule(rr, ref, tol2, active, k);
+  }
+}
+
+// a refinement's scalars of one column in one launch: the sums of b^T x32 (pbd;
+// nullptr: bd holds them) and |r|^2, the stated error, the restart test, the new
+// reference residual and the convergence test
+__global__ __launch_bounds__(kThreads) void k_refine_finish(
+    const c64* pbd, const c64* prr, int nblk, c64* bd, c64* rr_upd, c64* rr_new,
+    const c64* rr_rec, c64* rz, c64* err, const c64* bb, double tol2, double factor, int* active) {
+  __shared__ double lds[16];
+  const int k = blockIdx.x;
+  if (!active[k]) return;
+  if (pbd) {
+    const c64 v = body::finish(pbd, nblk, k, lds);
+    if (threadIdx.x == 0) bd[k] = v;
+  }
+  const c64 w = body::finish(prr, nblk, k, lds);
+  if (threadIdx.x == 0) {
+    rr_new[k] = w;
+    body::ir_err_rule(bd, rr_upd, rr_new, err, k);
+    body::restart_rule(rr_new, rr_rec, rz, factor, k);
+    rr_upd[k] = w;
+    body::mark_rule(rr_new, bb, tol2, active, k);
   }
 }
 
@@ -142,16 +181,6 @@ __global__ void k_ir_err(const c64* bd, const c64* rr_old, const c64* rr_new,
   body::ir_err_rule(bd, rr_old, rr_new, err, k);
 }
 
-// after a refinement: where the new FP64 residual exceeds the FP32 recursion's
-// own residual by more than `factor` (in squared norm), the kept direction no
-// longer fits the new residual; zeroing rz makes the next beta 0 (a restart)
-__global__ void k_cg_restart(const c64* rr_new, const c64* rr_rec, c64* rz, const int* active,
-                             double factor, int nb) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nb || !active[k]) return;
-  body::restart_rule(rr_new, rr_rec, rz, factor, k);
-}
-
 __global__ void k_set_count(int* c, int v) { *c = v; }
 
 __global__ void k_refine_due(const c64* rr, const c64* rr_upd, const c64* bb, double delta2,
@@ -175,12 +204,6 @@ __global__ void k_set_ones(int* a, int nb) {
 __global__ void k_select(c64* dst, const c64* src, const int* active, int nb) {
   int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k < nb && active[k]) dst[k] = src[k];
-}
-
-__global__ void k_lastcorr(const c64* alpha, const c64* rz, const int* active, c64* lc,
-                           int nb) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < nb && (!active || active[k])) lc[k] = {alpha[k].re * rz[k].re, 0.0};
 }
 
 template <typename T>
@@ -705,9 +728,9 @@ void finish_sums(const c64* partials, int nblk, int nb, c64* out, hipStream_t s)
 }
 
 void finish_alpha(const c64* partials, int nblk, int nb, c64* pq, const c64* rz,
-                  const int* active, c64* alpha, hipStream_t s) {
+                  const int* active, c64* alpha, hipStream_t s, c64* lastcorr) {
   hipLaunchKernelGGL(k_finish_alpha, dim3(nb), dim3(kThreads), 0, s, partials, nblk, pq, rz,
-                     active, alpha);
+                     active, alpha, lastcorr);
 }
 void finish_beta(const c64* partials, int nblk, int nb, c64* rz_new, c64* rz, const int* active,
                  c64* beta, hipStream_t s) {
@@ -732,11 +755,6 @@ void count_active(const int* active, int nb, int* count, hipStream_t s) {
   hipLaunchKernelGGL(k_count, dim3(1), dim3(256), 0, s, active, nb, count);
 }
 
-void cg_restart_on_drift(const c64* rr_new, const c64* rr_rec, c64* rz, const int* active,
-                         double factor, int nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_restart, dim3((nb + 255) / 256), dim3(256), 0, s, rr_new, rr_rec, rz,
-                     active, factor, nb);
-}
 void ir_stated_error(const c64* bd, const c64* rr_old, const c64* rr_new, const int* active,
                      c64* err, int nb, hipStream_t s) {
   hipLaunchKernelGGL(k_ir_err, dim3((nb + 255) / 256), dim3(256), 0, s, bd, rr_old, rr_new,
@@ -756,10 +774,17 @@ void set_all_active(int* active, int nb, hipStream_t s) {
 void select_active(c64* dst, const c64* src, const int* active, int nb, hipStream_t s) {
   hipLaunchKernelGGL(k_select, dim3((nb + 255) / 256), dim3(256), 0, s, dst, src, active, nb);
 }
-void cg_lastcorr(const c64* alpha, const c64* rz, const int* active, c64* lastcorr, int nb,
-                 hipStream_t s) {
-  hipLaunchKernelGGL(k_lastcorr, dim3((nb + 255) / 256), dim3(256), 0, s, alpha, rz, active,
-                     lastcorr, nb);
+void finish_mark(const c64* partials, int nblk, int nb, c64* rr, const c64* ref, double tol2,
+                 int* active, hipStream_t s) {
+  hipLaunchKernelGGL(k_finish_mark, dim3(nb), dim3(kThreads), 0, s, partials, nblk, rr, ref, tol2,
+                     active);
+}
+void refine_finish(const c64* pbd, const c64* prr, int nblk, int nb, c64* bd, c64* rr_upd,
+                   c64* rr_new, const c64* rr_rec, c64* rz, c64* err, const c64* bb, double tol2,
+                   double factor, int* active, int* count, hipStream_t s) {
+  hipLaunchKernelGGL(k_refine_finish, dim3(nb), dim3(kThreads), 0, s, pbd, prr, nblk, bd, rr_upd,
+                     rr_new, rr_rec, rz, err, bb, tol2, factor, active);
+  count_active(active, nb, count, s);
 }
 
 template <typename T>
@@ -778,12 +803,6 @@ void ir_fold(double* y, float* d, const double* b, int64_t n, int nb, const int*
              c64* partials, hipStream_t s, bool y_zero) {
   if (n <= 0 || nb <= 0) return;
   MLMC_LAUNCH(k_ir_fold<double>, dim3(reduce_blocks(n), nb), dim3(kThreads), 0, s, y, d, b, n,
-              active, partials, timing_log(), y_zero ? 1 : 0);
-}
-void ir_fold(double* y, float* d, const float* b, int64_t n, int nb, const int* active,
-             c64* partials, hipStream_t s, bool y_zero) {
-  if (n <= 0 || nb <= 0) return;
-  MLMC_LAUNCH(k_ir_fold<float>, dim3(reduce_blocks(n), nb), dim3(kThreads), 0, s, y, d, b, n,
               active, partials, timing_log(), y_zero ? 1 : 0);
 }
 void rhs_fp32(const double* b, float* r, float* b32, int64_t n, int nb, int* inexact,
