@@ -18,6 +18,8 @@ SOURCES = [
     "kernels_varcoef.hip",
     "kernels_nn.hip",
     "kernels_csr.hip",
+    "kernels_rows.hip",
+    "kernels_small_csr.hip",
     "kernels_defl.hip",
     "kernels_group.hip",
     "context.cpp",

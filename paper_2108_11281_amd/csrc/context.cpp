@@ -631,9 +631,12 @@ int Context::op_tiles(int l) const {
 template <typename T>
 void Context::op_apply(int l, const T* x, T* y, int nb, const int* act, c64* partials) {
   const Level& L = lv_[l - 1];
-  if (csr_)
-    csr_residual<T, T, T>(nullptr, x, y, csr_mat<T>(l), nb, csr_cols(L, nb), act, partials, s_);
-  else if (varcoef_)
+  if (csr_) {
+    if constexpr (sizeof(T) == 8)
+      csr_residual(nullptr, x, y, L.A64, nb, act, partials, s_);
+    else
+      throw Error(MLMC_ESTATE, "CSR building blocks are FP64");
+  } else if (varcoef_)
     varcoef_residual<T, T, T>(nullptr, x, y, vc_faces<T>(l), vc_diag<T>(l), L.side, nb, L.cols,
                               act, partials, s_);
   else
@@ -644,9 +647,12 @@ template <typename Tb, typename Tx, typename Tr>
 void Context::op_residual(int l, const Tb* b, const Tx* x, Tr* r, int nb, const int* act,
                           c64* partials) {
   const Level& L = lv_[l - 1];
-  if (csr_)
-    csr_residual<Tb, Tx, Tr>(b, x, r, csr_mat<Tx>(l), nb, csr_cols(L, nb), act, partials, s_);
-  else if (varcoef_)
+  if (csr_) {
+    if constexpr (sizeof(Tb) == 8 && sizeof(Tx) == 8 && sizeof(Tr) == 8)
+      csr_residual(b, x, r, L.A64, nb, act, partials, s_);
+    else
+      throw Error(MLMC_ESTATE, "CSR building blocks are FP64");
+  } else if (varcoef_)
     varcoef_residual<Tb, Tx, Tr>(b, x, r, vc_faces<Tx>(l), vc_diag<Tx>(l), L.side, nb, L.cols,
                                  act, partials, s_);
   else
@@ -658,8 +664,7 @@ void Context::op_update_apply(int l, const T* p_old, const T* z, const c64* beta
                               T* q, int nb, const int* act) {
   const Level& L = lv_[l - 1];
   if (csr_)
-    csr_update_apply<T>(p_old, z, beta, p_new, q, csr_mat<T>(l), nb, csr_cols(L, nb), act,
-                        partials_, s_);
+    rows_update_apply<T>(p_old, z, beta, p_new, q, csr_mat<T>(l), nb, act, partials_, s_);
   else if (varcoef_)
     varcoef_update_apply<T>(p_old, z, beta, p_new, q, vc_faces<T>(l), vc_diag<T>(l), L.side, nb,
                             L.cols, act, partials_, s_);
@@ -673,22 +678,42 @@ template <typename T>
 void Context::op_xr(int l, T* x, T* r, const T* p, const T* q, const c64* alpha, int nb,
                     const int* act, bool x_zero) {
   const Level& L = lv_[l - 1];
-  if (csr_ || varcoef_)
+  if (csr_)
+    rows_xr<T>(x, r, p, q, alpha, (int)L.n, nb, act, partials_, x_zero, s_);
+  else if (varcoef_)
     cg_update_xr<T>(x, r, p, q, alpha, L.n, nb, act, partials_, s_, x_zero);
   else
     poisson_xr<T>(x, r, p, alpha, L.side, L.d, L.c, nb, act, partials_, s_, x_zero);
 }
 
+// the Krylov methods' dots and residuals (CSR: interleaved blocks)
+template <typename T>
+void Context::kry_dot(int l, const T* x, const T* y, int nb, const int* act, c64* partials) {
+  const int64_t n = lv_[l - 1].n;
+  if (csr_)
+    rows_dot<T>(x, y, (int)n, nb, act, partials, s_);
+  else
+    vec_dot_partials<T>(x, y, n, nb, act, partials, s_);
+}
+template <typename T, typename Tr>
+void Context::kry_residual(int l, const T* b, const T* x, Tr* r, int nb, const int* act,
+                           c64* partials) {
+  if (csr_)
+    rows_residual<T, Tr>(b, x, r, csr_mat<T>(l), nb, act, partials, s_);
+  else
+    op_residual<T, T, Tr>(l, b, x, r, nb, act, partials);
+}
+
 template <typename T>
 void Context::op_res_restrict(int l, const T* b, const T* x, T* rc, int nb, const int* act) {
   const Level& L = lv_[l - 1];
-  if (csr_ && general_) {
+  if (csr_) {  // interleaved blocks, as the V-cycle
     T* r = work<T>().vt[l - 1];
-    csr_residual<T, T, T>(b, x, r, csr_mat<T>(l), nb, csr_cols(L, nb), act, nullptr, s_);
-    csr_spmm<T>(r, rc, csr_R<T>(l), 1.0, 0.0, nb, csr_cols(L, nb), act, s_);
-  } else if (csr_) {
-    csr_restrict<T>(b, x, rc, work<T>().vt[l - 1], csr_mat<T>(l), csr_agg<T>(l), nb,
-                    csr_cols(L, nb), act, s_);
+    rows_residual<T, T>(b, x, r, csr_mat<T>(l), nb, act, nullptr, s_);
+    if (general_)
+      rows_spmm<T>(r, rc, csr_R<T>(l), 1.0, 0.0, nb, act, s_);
+    else
+      rows_agg_sum<T>(r, rc, csr_agg<T>(l), nb, act, s_);
   }
   else if (varcoef_)
     varcoef_restrict<T>(b, x, rc, vc_faces<T>(l), vc_diag<T>(l), L.side, true, nb, L.cols, act,
@@ -701,11 +726,16 @@ template <typename T>
 void Context::op_prolong(int l, const T* ec, T* x, int nb, const int* act, double beta) {
   const Level& L = lv_[l - 1];
   const double w = beta == 0.0 ? 1.0 : omega_;
-  if (csr_ && general_)
-    csr_spmm<T>(ec, x, csr_P<T>(l), w, beta, nb, csr_cols(L, nb), act, s_);
-  else if (csr_)
-    csr_prolong<T>(ec, x, csr_agg<T>(l), (int)L.n, w, beta, nb, act, s_);
-  else if (varcoef_)
+  if (csr_) {
+    if constexpr (sizeof(T) == 8) {
+      if (general_)
+        csr_spmm(ec, x, L.P64, w, beta, nb, act, s_);
+      else
+        csr_prolong(ec, x, L.G64, (int)L.n, w, beta, nb, act, s_);
+    } else {
+      throw Error(MLMC_ESTATE, "CSR building blocks are FP64");
+    }
+  } else if (varcoef_)
     varcoef_prolong<T>(ec, x, L.side, w, beta, nb, act, s_);
   else
     agg2d_prolong<T>(ec, x, L.side, w, beta, nb, act, s_);
@@ -714,12 +744,16 @@ void Context::op_prolong(int l, const T* ec, T* x, int nb, const int* act, doubl
 template <typename T>
 void Context::op_restrict(int l, const T* x, T* xc, int nb, const int* act) {
   const Level& L = lv_[l - 1];
-  if (csr_ && general_)
-    csr_spmm<T>(x, xc, csr_R<T>(l), 1.0, 0.0, nb, csr_cols(L, nb), act, s_);
-  else if (csr_)
-    csr_restrict<T>(nullptr, x, xc, nullptr, csr_mat<T>(l), csr_agg<T>(l), nb, csr_cols(L, nb),
-                    act, s_);
-  else if (varcoef_)
+  if (csr_) {
+    if constexpr (sizeof(T) == 8) {
+      if (general_)
+        csr_spmm(x, xc, L.R64, 1.0, 0.0, nb, act, s_);
+      else
+        csr_restrict(x, xc, L.G64, (int)L.n, nb, act, s_);
+    } else {
+      throw Error(MLMC_ESTATE, "CSR building blocks are FP64");
+    }
+  } else if (varcoef_)
     varcoef_restrict<T>(nullptr, x, xc, nullptr, nullptr, L.side, false, nb, L.cols, act, s_);
   else
     agg2d_restrict<T>(x, xc, L.side, nb, act, s_);
@@ -742,9 +776,12 @@ void Context::second_coarse_cycle(int l, const T* bc, T* ec, int nb, const int* 
   Work<T>& w = work<T>();
   T* r2 = w.vr2[l];
   T* e2 = w.ve2[l];
-  op_residual<T, T, T>(l + 1, bc, ec, r2, nb, act, nullptr);
+  kry_residual<T, T>(l + 1, bc, ec, r2, nb, act, nullptr);
   vcycle<T>(l + 1, r2, e2, nb, act, nullptr);
-  vec_add_to<T>(ec, e2, lv_[l].n, nb, act, s_);
+  if (csr_)  // interleaved: no column mask (inactive columns are not read again)
+    vec_add_to<T>(ec, e2, lv_[l].n * nb, 1, nullptr, s_);
+  else
+    vec_add_to<T>(ec, e2, lv_[l].n, nb, act, s_);
 }
 
 // ---------------------------------------------------------------------------
@@ -959,7 +996,7 @@ template <typename T>
 int Context::vcycle_partials(int l, bool* fused) const {
   const int64_t n = lv_[l - 1].n;
   *fused = false;
-  if (varcoef_ || csr_ || l == Ls_ || opt_.nu_post == 0) return reduce_blocks(n);
+  if (varcoef_ || csr_ || l == Ls_ || opt_.nu_post == 0) return dot_blocks(l);
   enum { kNull, kTmp, kX };
   const int per = sweeps_per_pass(l);
   int u = kNull;
@@ -1075,20 +1112,15 @@ int Context::pcg(int l, const T* b, T* x, int nb, int* act, double tol, c64* las
   Work<T>& w = work<T>();
   const Level& L = lv_[l - 1];
   const int64_t n = L.n;
-  const int nblk = reduce_blocks(n);
-  const int ntiles = op_tiles(l);
+  const int nblk = dot_blocks(l);
+  const int ntiles = kry_tiles(l);
   c64 *rr0 = scal_[kRr0], *rz = scal_[kRz], *tmp = scal_[kTmp], *alpha = scal_[kAlpha],
       *beta = scal_[kBeta];
-  vec_zero<T>(x, n, nb, act, s_);
-  if (l == Ls_) {  // direct solve on the coarsest level
-    dense_apply<T>(w.ainvT, b, x, (int)n, nb, act, s_, w.ld);
-    if (lastcorr) vec_zero<c64>(lastcorr, 1, nb, nullptr, s_);
-    return 0;
-  }
+  vec_zero<T>(x, n * nb, 1, nullptr, s_);
   const double en = (double)sizeof(T) * (double)n;
   const bool stencil = !varcoef_ && !csr_;  // A p is not stored
-  vec_copy<T>(b, w.r, n, nb, act, s_);
-  vec_dot_partials<T>(b, b, n, nb, act, partials_, s_);
+  vec_copy<T>(b, w.r, n * nb, 1, nullptr, s_);
+  kry_dot<T>(l, b, b, nb, act, partials_);
   finish_sums(partials_, nblk, nb, rr0, s_);
   bool fused = false;
   const int nvp = vcycle_partials<T>(l, &fused);
@@ -1140,8 +1172,8 @@ void Context::pcg_refined(int l, const double* b, double* y, int nb, double tol,
   Work<float>& w = w32_;
   const Level& L = lv_[l - 1];
   const int64_t n = L.n;
-  const int nblk = reduce_blocks(n);
-  const int ntiles = op_tiles(l);
+  const int nblk = dot_blocks(l);
+  const int ntiles = kry_tiles(l);
   int* act = act_outer_;
   c64 *bb = scal_[kBb], *bd = scal_[kBd], *rr_upd = scal_[kRres], *rr_new = scal_[kRres2];
   c64 *rz = scal_[kRz], *tmp = scal_[kTmp], *alpha = scal_[kAlpha], *beta = scal_[kBeta];
@@ -1169,7 +1201,7 @@ void Context::pcg_refined(int l, const double* b, double* y, int nb, double tol,
     finish_sums(partials_, nblk, nb, bb, s_);
     MLMC_HIP(hipMemcpyAsync(count_host_ + 4, count_dev_ + 4, sizeof(int), hipMemcpyDeviceToHost,
                             s_));
-  } else {
+  } else if (!csr_) {  // CSR: solve() wrote r with the interleaved copy of b
     vec_convert<float, double>(b, r, n, nb, nullptr, s_);
   }
   vec_copy<c64>(bb, rr_upd, 1, nb, nullptr, s_);
@@ -1236,10 +1268,15 @@ void Context::pcg_refined(int l, const double* b, double* y, int nb, double tol,
       // y, x32 out: 32 bytes per unknown, 8 fewer on the first fold, which does
       // not read y)
       timed<double>(l, kTimIrFold, (folds ? 32.0 : 24.0) * (double)n, act, nb,
-                    [&] { ir_fold(y, x32, b, n, nb, act, partials_, s_, folds == 0); });
+                    [&] {
+                      if (csr_)
+                        rows_fold(y, x32, b, (int)n, nb, act, partials_, folds == 0, s_);
+                      else
+                        ir_fold(y, x32, b, n, nb, act, partials_, s_, folds == 0);
+                    });
       finish_sums(partials_, nblk, nb, bd, s_);
       timed<double>(l, kTimIrResidual, 20.0 * (double)n, act, nb,
-                    [&] { op_residual<double, double, float>(l, b, y, r, nb, act, partials_); });
+                    [&] { kry_residual<double, float>(l, b, y, r, nb, act, partials_); });
     }
     ++folds;
     // the kept direction stays only while the recursion's residual (tmp, from
@@ -1392,8 +1429,18 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
   } else if (opt_.precision == MLMC_FP64 || fp64_batch(nb)) {
     MLMC_HIP(hipMemcpyAsync(act_inner_, act_outer_, sizeof(int) * nb,
                             hipMemcpyDeviceToDevice, s_));
-    pcg<double>(l, b, y, nb, act_inner_, tol, err);
+    if (csr_) {
+      rows_in<double>(b, rowsB_, nullptr, n, nb, s_);
+      pcg<double>(l, rowsB_, rowsY_, nb, act_inner_, tol, err);
+      rows_out<double>(rowsY_, y, n, nb, s_);
+    } else {
+      pcg<double>(l, b, y, nb, act_inner_, tol, err);
+    }
     counters[1] += 1;
+  } else if (csr_) {
+    rows_in<float>(b, rowsB_, w32_.r, n, nb, s_);
+    pcg_refined(l, rowsB_, rowsY_, nb, tol, err);
+    rows_out<double>(rowsY_, y, n, nb, s_);
   } else {
     pcg_refined(l, b, y, nb, tol, err);
   }
@@ -1702,8 +1749,13 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
       xb = dalloc_n<T>(m);
       if (rc) rct = dalloc_n<T>(mc);
     }
-    to_t(bt, b, m);
-    if (!zero_start) to_t(xa, x, m);
+    // CSR: interleaved working copies, as the solver's
+    auto in_t = [&](T* dst, const double* src) {
+      if (csr_) rows_in<T>(src, nullptr, dst, n, nrhs, s_);
+      else to_t(dst, src, m);
+    };
+    in_t(bt, b);
+    if (!zero_start) in_t(xa, x);
     else if (sweeps == 0) vec_zero<T>(xa, m, 1, nullptr, s_);
     const Level& L = lv_[level - 1];
     bool restricted = false;
@@ -1714,11 +1766,10 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
       cop_smooth_n<C>(level, reinterpret_cast<const C*>(bt), reinterpret_cast<C*>(xa), nrhs,
                       nullptr, sweeps, zero_start, reverse);
     } else if (csr_) {
-      if (zero_start) vec_zero<T>(xa, n, nrhs, nullptr, s_);  // as the V-cycle starts
+      if (zero_start) vec_zero<T>(xa, m, 1, nullptr, s_);  // as the V-cycle starts
       for (int i = 0; i < sweeps; ++i)
-        csr_gs_sweep<T>(bt, xa, csr_sweep<T>(level), (int)n, nrhs, csr_cols(L, nrhs),
-                        csr_tail >= 0 ? csr_tail : this->csr_tail(L, nrhs), nullptr, reverse,
-                        s_);
+        rows_gs_sweep<T>(bt, xa, csr_sweep<T>(level), nrhs,
+                         csr_tail >= 0 ? csr_tail : this->csr_tail(L, nrhs), nullptr, reverse, s_);
     } else if (varcoef_) {
       for (int i = 0; i < sweeps; ++i) {
         const bool z = zero_start && i == 0;
@@ -1765,8 +1816,13 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
         op_res_restrict<T>(level, bt, xa, rct, nrhs, nullptr);
       }
     }
-    from_t(xa, x, m);
-    if (rct) from_t(rct, rc, mc);
+    if (csr_) {
+      rows_out<T>(xa, x, n, nrhs, s_);
+      if (rct) rows_out<T>(rct, rc, lv_[level].n, nrhs, s_);
+    } else {
+      from_t(xa, x, m);
+      if (rct) from_t(rct, rc, mc);
+    }
     MLMC_HIP(hipGetLastError());
     if (ws) return;  // the caller's workspace: no stream synchronisation needed
     MLMC_HIP(hipStreamSynchronize(s_));

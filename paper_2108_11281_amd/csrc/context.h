@@ -47,10 +47,9 @@ struct Level {
   double *kf64 = nullptr, *dg64 = nullptr, *kl64 = nullptr;
   float *dg32 = nullptr, *kl32 = nullptr;
   int cols = 4;  // right-hand sides per thread of the stencil kernels (autotuned)
-  int cols_narrow = 4;  // CSR kernels: the same for launches of at most 16 columns
-  // CSR sweep: largest class (in slices) of the trailing classes that share
+  // CSR sweep: largest class (in rows) of the trailing classes that share
   // launches, full and narrow batches (autotuned; 0: a launch per class)
-  int tail_slices = 0, tail_slices_narrow = 0;
+  int tail_rows = 0, tail_rows_narrow = 0;
   int bsr_form[2] = {0, 0};  // block-stencil kernel form, complex64 / complex128 (autotuned)
   int mcols = 0;  // right-hand sides per wave of the fused 3D sweep (0: in-place sweeps)
   // POISSON2D: rows per segment of the fused sweep, FP32 and FP64 (autotuned)
@@ -129,7 +128,7 @@ class Context {
   // ws: nullptr (working copies allocated for the call) or a device workspace
   // of ws_bytes that holds them
   // csr_tail (CSR levels): -1 the level's tuned sweep schedule, 0 a launch per
-  // colour class, > 0 the trailing classes of at most that many slices share
+  // colour class, > 0 the trailing classes of at most that many rows share
   // launches
   void smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool zero_start,
                    const double* b, double* x, double* rc, void* ws = nullptr,
@@ -221,12 +220,10 @@ class Context {
   template <typename T> int bsr_form(const Level& L, int nb) const {
     return nb >= 32 ? L.bsr_form[sizeof(T) == sizeof(c64) ? 1 : 0] : 0;
   }
-  // right-hand sides per thread of the CSR kernels on level L for nb columns
-  // (narrow batches, such as the pilot and the first samples of a level, have
-  // their own tuned value)
-  int csr_cols(const Level& L, int nb) const { return nb <= 16 ? L.cols_narrow : L.cols; }
+  // CSR sweep schedule for nb columns (narrow batches, such as the pilot and the
+  // first samples of a level, have their own tuned value)
   int csr_tail(const Level& L, int nb) const {
-    return nb <= 16 ? L.tail_slices_narrow : L.tail_slices;
+    return nb <= 16 ? L.tail_rows_narrow : L.tail_rows;
   }
   // red-black sweeps fused into one pass of the Poisson smoother on level l
   int sweeps_per_pass(int l) const { return lv_[l - 1].side >= 64 ? 2 : 1; }
@@ -299,8 +296,18 @@ class Context {
   template <typename T> void op_xr(int l, T* x, T* r, const T* p, const T* q, const c64* alpha,
                                    int nb, const int* act, bool x_zero);
   int op_xr_partials(int l) const {
-    return varcoef_ || csr_ ? reduce_blocks(lv_[l - 1].n) : op_tiles(l);
+    return varcoef_ || csr_ ? dot_blocks(l) : kry_tiles(l);
   }
+  // the solver's vectors on level l (CSR: interleaved blocks): partial sums of its
+  // dots, of its residual and direction kernels, and those operations
+  int dot_blocks(int l) const {
+    return csr_ ? rows_blocks((int)lv_[l - 1].n) : reduce_blocks(lv_[l - 1].n);
+  }
+  int kry_tiles(int l) const { return csr_ ? dot_blocks(l) : op_tiles(l); }
+  template <typename T> void kry_dot(int l, const T* x, const T* y, int nb, const int* act,
+                                     c64* partials);
+  template <typename T, typename Tr>
+  void kry_residual(int l, const T* b, const T* x, Tr* r, int nb, const int* act, c64* partials);
   template <typename T> void vcycle_vc(int l, const T* b, T* x, int nb, const int* act,
                                        c64* rz_partials, bool top = false);
   template <typename T> Work<T>& work();
@@ -413,6 +420,23 @@ class Context {
   // (finest-level probes restricted level by level through gA_/gB_)
   bool general_ = false;
   double *gA_ = nullptr, *gB_ = nullptr;
+  // CSR: a solve's right-hand sides and solutions as interleaved blocks, on which
+  // the Krylov and V-cycle kernels of these operators work
+  double *rowsB_ = nullptr, *rowsY_ = nullptr;
+  // CSR: the levels from small_csr_level to L_s - 1 whose V-cycle one workgroup
+  // per vector runs (in the precision of the mode), device descriptors
+  template <typename T> struct SmallCsr {
+    SmallCsrLevel<T>* lev = nullptr;  // one per level from small_csr_level_[1]
+    SmallCsrCoarse<T> coarse;
+  };
+  SmallCsr<float> sc32_;
+  SmallCsr<double> sc64_;
+  std::vector<int> small_np_;          // positions of each of these levels
+  // first such level for narrow batches (at most 16 columns) and for wide ones
+  int small_csr_level_[2] = {1 << 30, 1 << 30};
+  int small_csr_level(int nb) const { return small_csr_level_[nb <= 16 ? 0 : 1]; }
+  template <typename T> SmallCsr<T>& small_csr_of();
+  template <typename T> void build_small_csr();
   // learned smoother state: FP32 master weights, Adam moments, gradient, BF16
   // fragments, BF16 link features; nn_use_ is true while a solve runs with it
   bool nn_ready_ = false, nn_use_ = false;
@@ -477,7 +501,7 @@ inline bool smooth_flags_valid(int flags) {
 }
 inline int smooth_csr_tail(int flags) {
   if (flags & MLMC_SMOOTH_CLASS_LAUNCHES) return 0;
-  return (flags & MLMC_SMOOTH_SHARED_TAIL) ? kTailWaves : -1;
+  return (flags & MLMC_SMOOTH_SHARED_TAIL) ? 1024 : -1;  // rows of a shared class
 }
 
 // splitmix64 finaliser (sampling of timed launches)

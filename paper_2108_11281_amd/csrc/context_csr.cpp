@@ -337,41 +337,41 @@ void Context::csr_upload(Level& L, bool last) {
   const int* dsptr = up(sptr);
   const int* dsci = up(sci);
   L.A64 = {n, n, rp, ci, up(L.h_v), dsptr, dsci, up(sv)};
-  L.A32 = {n, n, rp, ci, up(to_f32(L.h_v)), dsptr, dsci, up(to_f32(sv))};
-  // the off-diagonal part by colour class (ascending rows within a class), each
-  // class padded to whole slices, and the inverted diagonal per position
+  L.A32 = {n, n, rp, ci, up(to_f32(L.h_v))};
+  // the off-diagonal part by colour class (ascending rows within a class) and the
+  // inverted diagonal per position
   const int ncol = n ? *std::max_element(L.h_colour.begin(), L.h_colour.end()) + 1 : 0;
   std::vector<int> cnt(ncol, 0);
   for (int i = 0; i < n; ++i) ++cnt[L.h_colour[i]];
-  std::vector<int> soff(ncol + 1, 0);
-  for (int c = 0; c < ncol; ++c) soff[c + 1] = soff[c] + (cnt[c] + 63) / 64;
-  std::vector<int> srow(64 * (size_t)soff[ncol], -1);
-  {
-    std::vector<int> fill(ncol);
-    for (int c = 0; c < ncol; ++c) fill[c] = 64 * soff[c];
-    for (int i = 0; i < n; ++i) srow[fill[L.h_colour[i]]++] = i;
-  }
-  std::vector<double> sdi(srow.size(), 0.0);
-  for (size_t k = 0; k < srow.size(); ++k)
-    if (srow[k] >= 0) {
-      const int i = srow[k];
-      for (int64_t q = L.h_rp[i]; q < L.h_rp[i + 1]; ++q)
-        if (L.h_ci[q] == i) sdi[k] = 1.0 / L.h_v[q];
+  std::vector<int> off(ncol + 1, 0);
+  for (int c = 0; c < ncol; ++c) off[c + 1] = off[c] + cnt[c];
+  std::vector<int> order(n), fill(off.begin(), off.end() - (ncol ? 1 : 0));
+  for (int i = 0; i < n; ++i) order[fill[L.h_colour[i]]++] = i;
+  std::vector<int> srow(4 * (size_t)n), gci;  // (row, first entry, end, 0) per position
+  std::vector<double> sdi(n, 0.0), gv;
+  gci.reserve(L.h_ci.size());
+  gv.reserve(L.h_ci.size());
+  for (int k = 0; k < n; ++k) {
+    const int i = order[k];
+    srow[4 * (size_t)k] = i;
+    srow[4 * (size_t)k + 1] = (int)gci.size();
+    for (int64_t q = L.h_rp[i]; q < L.h_rp[i + 1]; ++q) {
+      if (L.h_ci[q] == i) {
+        sdi[k] = 1.0 / L.h_v[q];
+      } else {
+        gci.push_back(L.h_ci[q]);
+        gv.push_back(L.h_v[q]);
+      }
     }
-  std::vector<int> gptr, gci;
-  std::vector<double> gv;
-  sell(srow, true, gptr, gci, gv);
-  const int* dsrow = up(srow);
-  const int* dgptr = up(gptr);
-  const int* dgci = up(gci);
-  L.S64.srow = L.S32.srow = dsrow;
-  L.S64.sptr = L.S32.sptr = dgptr;
-  L.S64.sci = L.S32.sci = dgci;
-  L.S64.sv = up(gv);
-  L.S64.sdi = up(sdi);
-  L.S32.sv = up(to_f32(gv));
-  L.S32.sdi = up(to_f32(sdi));
-  L.S64.soff = L.S32.soff = soff;
+    srow[4 * (size_t)k + 2] = (int)gci.size();
+  }
+  L.S64.rows = L.S32.rows = reinterpret_cast<const int4*>(up(srow));
+  L.S64.ci = L.S32.ci = up(gci);
+  L.S64.v = up(gv);
+  L.S64.di = up(sdi);
+  L.S32.v = up(to_f32(gv));
+  L.S32.di = up(to_f32(sdi));
+  L.S64.off = L.S32.off = off;
   if (last) return;
   if (general_) {
     // given prolongation P (n x pcols) and R = P^T, SELL-64 copies of both
@@ -389,8 +389,11 @@ void Context::csr_upload(Level& L, bool last) {
       sell_build(M.rp, M.ci, M.v, rows, false, false, sp, sc, sw);
       const int* dsp = up(sp);
       const int* dsc = up(sc);
-      m64 = {M.n, M.cols, nullptr, nullptr, nullptr, dsp, dsc, up(sw)};
-      m32 = {M.n, M.cols, nullptr, nullptr, nullptr, dsp, dsc, up(to_f32(sw))};
+      std::vector<int> mrp(M.rp.begin(), M.rp.end());
+      const int* drp = up(mrp);
+      const int* dci = up(M.ci);
+      m64 = {M.n, M.cols, drp, dci, up(M.v), dsp, dsc, up(sw)};
+      m32 = {M.n, M.cols, drp, dci, up(to_f32(M.v))};
     };
     put(Ph, L.P32, L.P64);
     put(Rh, L.R32, L.R64);
@@ -479,11 +482,17 @@ void Context::build_csr(const mlmc_operator& A, const int32_t* const* aggs, cons
   for (int l = 0; l < Ls_; ++l) csr_upload(lv_[l], l + 1 == Ls_);
   MLMC_HIP(hipStreamSynchronize(s_));
   finish_real_build();
+  rowsB_ = dalloc_n<double>(lv_[0].n * nb_);
+  rowsY_ = dalloc_n<double>(lv_[0].n * nb_);
   if (general_) {
     gA_ = dalloc_n<double>(lv_[1].n * nb_);
     gB_ = dalloc_n<double>(lv_[1].n * nb_);
     csr_general_coarse_trace();
   }
+  if (opt_.precision == MLMC_FP32_IR64)
+    build_small_csr<float>();
+  else
+    build_small_csr<double>();
   tune_csr();
 }
 
@@ -550,29 +559,194 @@ void Context::samples_batch_general(int level, uint64_t seed, uint64_t first, in
   finish_samples(level, nbatch, okc1.data(), okc2.data(), first, out, err_out);
 }
 
-// Autotuner of the CSR kernels: per smoothed level, time one Gauss-Seidel
-// sweep with 1, 2, 4 and 8 right-hand sides per thread (the results are
-// identical; only the reuse of the row's indices and values and the
-// parallelism differ), once over all nb columns and once over a narrow batch
-// of 16, and keep the fastest of each for every CSR kernel of that level; then,
-// with that choice, the sweep's schedule of its trailing small colour classes
-// (a launch per class, or the trailing classes of at most 4, 16 or 64 slices
-// in shared launches: fewer launches, fewer compute units per class; the
+template <> Context::SmallCsr<float>& Context::small_csr_of<float>() { return sc32_; }
+template <> Context::SmallCsr<double>& Context::small_csr_of<double>() { return sc64_; }
+
+// The small levels of the hierarchy, one vector per workgroup: the run of levels
+// above the coarsest one whose iterate fits into LDS with 16-bit positions and that
+// gain from it.  The workgroup's sweep costs about 0.2 us per 1000 entries whatever
+// the batch (one compute unit's gathers and loads), the launches it replaces 3.5-5
+// us per colour class for narrow batches and two to three times that for full ones:
+// so 10,000 entries per class for batches of at most 16 vectors, 40,000 for wider.
+// Measured (FP32, geometric graphs, 16 classes, 2 + 2 sweeps, narrow): 4,700 rows 20
+// us for the way down against about 110 us of launches, 27,600 rows 190 us against
+// about 150.
+template <typename T>
+void Context::build_small_csr() {
+  const size_t entry = sizeof(T) + 2;
+  auto layout = [&](const Level& L, std::vector<int>& cls, std::vector<int>& row,
+                    std::vector<int>& pos) {
+    const std::vector<int>& off = L.S64.off;
+    const int ncls = (int)off.size() - 1;
+    cls.assign(ncls + 1, 0);
+    for (int c = 0; c < ncls; ++c) cls[c + 1] = cls[c] + (off[c + 1] - off[c] + 63) / 64;
+    row.assign(64 * (size_t)cls[ncls], -1);
+    pos.assign(L.n, 0);
+    // longest rows of a class first, so that the rows of a slice are alike
+    std::vector<int> fill(ncls), by_len(L.n);
+    for (int c = 0; c < ncls; ++c) fill[c] = 64 * cls[c];
+    std::iota(by_len.begin(), by_len.end(), 0);
+    std::stable_sort(by_len.begin(), by_len.end(), [&](int i, int j) {
+      return L.h_rp[i + 1] - L.h_rp[i] > L.h_rp[j + 1] - L.h_rp[j];
+    });
+    for (int i : by_len) {
+      pos[i] = fill[L.h_colour[i]]++;
+      row[pos[i]] = i;
+    }
+  };
+  const int nc = (int)lv_[Ls_ - 1].n;
+  int first = Ls_, narrow = Ls_;
+  while (first > 1) {
+    const Level& L = lv_[first - 2];
+    const int ncls = (int)L.S64.off.size() - 1;
+    if (L.n > 60000) break;
+    std::vector<int> cls, row, pos;
+    layout(L, cls, row, pos);
+    const double nnz = (double)(L.h_rp[L.n] - L.n);
+    if (row.size() * sizeof(T) > (size_t)kSmallCsrLds || row.size() > 65535) break;
+    if (nnz > 40e3 * ncls) break;
+    --first;
+    if (nnz <= 10e3 * ncls && narrow == first + 1) narrow = first;
+  }
+  if (first >= Ls_ || nc > 65535) return;
+  small_csr_level_[0] = narrow < Ls_ ? narrow : 1 << 30;
+  small_csr_level_[1] = first;
+  auto up = [&](const auto& h) {
+    using V = typename std::decay<decltype(h)>::type::value_type;
+    V* d = dalloc_n<V>(std::max<int64_t>((int64_t)h.size(), 1));
+    if (!h.empty()) {
+      MLMC_HIP(hipMemcpyAsync(d, h.data(), sizeof(V) * h.size(), hipMemcpyHostToDevice, s_));
+      MLMC_HIP(hipStreamSynchronize(s_));
+    }
+    return d;
+  };
+  auto to_t = [](const std::vector<double>& a) { return std::vector<T>(a.begin(), a.end()); };
+  // SELL-64 rows of (rp, ci, v) in the order `rows` (-1: empty) with columns mapped
+  // by `map` (empty: kept)
+  auto sell = [&](const std::vector<int64_t>& rp, const std::vector<int>& ci,
+                  const std::vector<double>& v, const std::vector<int>& rows, bool skip_diag,
+                  const std::vector<int>& map) {
+    std::vector<int> sptr, sci;
+    std::vector<double> sv;
+    sell_build(rp, ci, v, rows, skip_diag, false, sptr, sci, sv);
+    std::vector<unsigned short> c16(sci.size(), 0);
+    for (size_t e = 0; e < sci.size(); ++e)
+      c16[e] = (unsigned short)(map.empty() || sv[e] == 0.0 ? (sv[e] == 0.0 ? 0 : sci[e])
+                                                            : map[sci[e]]);
+    SellView<T> view;
+    view.ptr = up(sptr);
+    view.ci = up(c16);
+    view.v = up(to_t(sv));
+    return view;
+  };
+  std::vector<SmallCsrLevel<T>> desc(Ls_ - first);
+  std::vector<int> cls, row, pos, ncls_, nrow, npos;
+  layout(lv_[first - 1], cls, row, pos);
+  for (int l = first; l < Ls_; ++l) {
+    const Level& L = lv_[l - 1];
+    SmallCsrLevel<T>& d = desc[l - first];
+    const bool last = l + 1 == Ls_;
+    std::vector<int> next_rows;  // the next level's rows in its order
+    if (last) {
+      npos.clear();
+      next_rows.resize(nc);
+      std::iota(next_rows.begin(), next_rows.end(), 0);
+    } else {
+      layout(lv_[l], ncls_, nrow, npos);
+      next_rows = nrow;
+    }
+    d.np = (int)row.size();
+    d.ncls = (int)cls.size() - 1;
+    small_np_.push_back(d.np);
+    d.cls = up(cls);
+    d.row = up(row);
+    d.off = sell(L.h_rp, L.h_ci, L.h_v, row, true, pos);
+    std::vector<double> di(row.size(), 0.0), dd(row.size(), 0.0);
+    for (size_t k = 0; k < row.size(); ++k)
+      if (row[k] >= 0)
+        for (int64_t q = L.h_rp[row[k]]; q < L.h_rp[row[k] + 1]; ++q)
+          if (L.h_ci[q] == row[k]) {
+            dd[k] = L.h_v[q];
+            di[k] = 1.0 / L.h_v[q];
+          }
+    d.di = up(to_t(di));
+    d.dd = up(to_t(dd));
+    if (general_) {
+      HostCsr Ph;
+      Ph.n = (int)L.n;
+      Ph.cols = L.pcols;
+      Ph.rp = L.hp_rp;
+      Ph.ci = L.hp_ci;
+      Ph.v = L.hp_v;
+      const HostCsr Rh = transpose(Ph);
+      d.P = sell(Ph.rp, Ph.ci, Ph.v, row, false, npos);
+      d.R = sell(Rh.rp, Rh.ci, Rh.v, next_rows, false, pos);
+    } else {
+      // members (ascending natural order) per next-level position, and the scales
+      std::vector<int> size(lv_[l].n, 0), start(lv_[l].n + 1, 0), member(L.n);
+      for (int i = 0; i < (int)L.n; ++i) ++size[L.h_agg[i]];
+      for (int J = 0; J < (int)lv_[l].n; ++J) start[J + 1] = start[J] + size[J];
+      {
+        std::vector<int> fill(start.begin(), start.end() - 1);
+        for (int i = 0; i < (int)L.n; ++i) member[fill[L.h_agg[i]]++] = i;
+      }
+      std::vector<int> mptr(next_rows.size() + 1, 0), mem, agg(row.size(), 0);
+      std::vector<double> cs(next_rows.size(), 0.0), fs(row.size(), 0.0);
+      for (size_t q = 0; q < next_rows.size(); ++q) {
+        const int J = next_rows[q];
+        if (J >= 0) {
+          for (int m = start[J]; m < start[J + 1]; ++m) mem.push_back(pos[member[m]]);
+          cs[q] = 1.0 / std::sqrt((double)size[J]);
+        }
+        mptr[q + 1] = (int)mem.size();
+      }
+      for (size_t k = 0; k < row.size(); ++k)
+        if (row[k] >= 0) {
+          const int J = L.h_agg[row[k]];
+          agg[k] = last ? J : npos[J];
+          fs[k] = 1.0 / std::sqrt((double)size[J]);
+        }
+      d.mptr = up(mptr);
+      d.mem = up(mem);
+      d.agg = up(agg);
+      d.cs = up(to_t(cs));
+      d.fs = up(to_t(fs));
+    }
+    d.b = dalloc_n<T>((int64_t)d.np * nb_);
+    d.x = dalloc_n<T>((int64_t)d.np * nb_);
+    d.r = dalloc_n<T>((int64_t)d.np * nb_);
+    cls = ncls_;
+    row = nrow;
+    pos = npos;
+  }
+  SmallCsr<T>& S = small_csr_of<T>();
+  Work<T>& w = work<T>();
+  S.lev = up(desc);
+  S.coarse.n = nc;
+  S.coarse.ld = w.ld;
+  S.coarse.inv = w.ainvT;
+  S.coarse.b = dalloc_n<T>((int64_t)nc * nb_);
+  S.coarse.x = dalloc_n<T>((int64_t)nc * nb_);
+  small_csr_setup();
+}
+
+// Autotuner of the CSR sweep: per smoothed level, once over all nb columns and
+// once over a narrow batch of 16, the schedule of its trailing small colour
+// classes (a launch per class, or the trailing classes of at most 256, 1024 or
+// 4096 rows in shared launches: fewer launches, fewer compute units per class; the
 // results are identical).  Each candidate is timed as the best of five sweeps
 // after a warm-up.  Runs once at setup on the library's own work vectors.
 void Context::tune_csr() {
   const bool fp32 = opt_.precision == MLMC_FP32_IR64;
   hipEvent_t a = event(), b = event();
-  auto time_sweep = [&](const Level& L, int ncols, int cols, int tail) {
+  auto time_sweep = [&](const Level& L, int ncols, int tail) {
     float ms = 1e30f;  // best of 5 after a warm-up run (robust to noise)
     for (int rep = 0; rep < 6; ++rep) {
       MLMC_HIP(hipEventRecord(a, s_));
       if (fp32)
-        csr_gs_sweep<float>(w32_.r, w32_.x, L.S32, (int)L.n, ncols, cols, tail, nullptr, false,
-                            s_);
+        rows_gs_sweep<float>(w32_.r, w32_.x, L.S32, ncols, tail, nullptr, false, s_);
       else
-        csr_gs_sweep<double>(w64_.r, w64_.x, L.S64, (int)L.n, ncols, cols, tail, nullptr, false,
-                             s_);
+        rows_gs_sweep<double>(w64_.r, w64_.x, L.S64, ncols, tail, nullptr, false, s_);
       MLMC_HIP(hipEventRecord(b, s_));
       MLMC_HIP(hipEventSynchronize(b));
       float t = 0.f;
@@ -581,43 +755,34 @@ void Context::tune_csr() {
     }
     return ms;
   };
-  for (int l = 1; l < Ls_; ++l) {
+  for (int l = 1; l < Ls_ && l < small_csr_level_[0]; ++l) {
     Level& L = lv_[l - 1];
-    const std::vector<int>& soff = L.S32.soff;
+    const std::vector<int>& off = L.S32.off;
     for (int narrow = 0; narrow < 2; ++narrow) {
       const int ncols = narrow ? std::min(nb_, 16) : nb_;
-      float best = 1e30f;
-      int best_cols = 4;
-      for (int cols : {1, 2, 4, 8}) {
-        const float ms = time_sweep(L, ncols, cols, 0);
-        if (ms < best) {
-          best = ms;
-          best_cols = cols;
-        }
-      }
-      (narrow ? L.cols_narrow : L.cols) = best_cols;
       // shared launches only where they are at least 5% faster than a launch
       // per class, so that the choice does not follow timing noise
-      const float t_classes = best;
-      int best_tail = 0, last_start = csr_tail_start(soff, 0);
-      for (int tail : {4, 16, 64}) {
-        const int start = csr_tail_start(soff, tail);
+      const float t_classes = time_sweep(L, ncols, 0);
+      float best = t_classes;
+      int best_tail = 0, last_start = csr_tail_start(off, 0);
+      for (int tail : {256, 1024, 4096}) {
+        const int start = csr_tail_start(off, tail);
         if (start == last_start) continue;  // the same schedule as a smaller bound
         last_start = start;
-        const float ms = time_sweep(L, ncols, best_cols, tail);
+        const float ms = time_sweep(L, ncols, tail);
         if (ms < best && ms < 0.95f * t_classes) {
           best = ms;
           best_tail = tail;
         }
       }
-      (narrow ? L.tail_slices_narrow : L.tail_slices) = best_tail;
+      (narrow ? L.tail_rows_narrow : L.tail_rows) = best_tail;
     }
   }
   ev_pool_.push_back(a);
   ev_pool_.push_back(b);
 }
 
-// V-cycle of a CSR level: in-place multicolour Gauss-Seidel sweeps (classes in
+// V-cycle of a CSR level on interleaved blocks: in-place multicolour Gauss-Seidel sweeps (classes in
 // ascending order before the coarse correction, descending after it, so the
 // preconditioner is symmetric), residual + restriction, prolongation +
 // omega-scaled correction.
@@ -629,8 +794,23 @@ void Context::vcycle_csr(int l, const T* b, T* x, int nb, const int* act, c64* r
   const Level& L = lv_[l - 1];
   const int64_t n = L.n;
   const double en = (double)sizeof(T) * (double)n;
-  if (l == Ls_) {
-    dense_apply<T>(w.ainvT, b, x, (int)n, nb, act, s_, w.ld);
+  const SmallCsr<T>& sc = small_csr_of<T>();
+  if (l < Ls_ && l >= small_csr_level(nb) && sc.lev) {
+    const int at = l - small_csr_level_[1], nl = Ls_ - l;
+    const int np = *std::max_element(small_np_.begin() + at, small_np_.end());
+    const bool all = sc.coarse.n <= kSmallCsrDense;
+    auto part = [&](int mode) {
+      small_csr<T>(sc.lev + at, nl, np, sc.coarse, b, x, nb, opt_.nu_pre, opt_.nu_post, omega_,
+                   mode, act, s_);
+    };
+    timed<T>(l, kTimGs, 2.0 * en, act, nb, [&] { part(all ? kSmallCsrAll : kSmallCsrDown); });
+    if (!all) {
+      dense_apply<T>(sc.coarse.inv, sc.coarse.b, sc.coarse.x, sc.coarse.n, nb, act, s_,
+                     sc.coarse.ld);
+      timed<T>(l, kTimGs, 2.0 * en, act, nb, [&] { part(kSmallCsrUp); });
+    }
+  } else if (l == Ls_) {
+    rows_dense<T>(w.ainvT, b, x, (int)n, w.ld, nb, act, s_);
   } else {
     const CsrMat<T>& A = csr_mat<T>(l);
     const CsrSweep<T>& S = csr_sweep<T>(l);
@@ -642,46 +822,49 @@ void Context::vcycle_csr(int l, const T* b, T* x, int nb, const int* act, c64* r
     const double res_mat = (double)nnz * (4.0 + sizeof(T)) + 4.0 * (double)n;
     const double enc = (double)sizeof(T) * (double)lv_[l].n;
     const int pre = opt_.nu_pre, post = opt_.nu_post;
-    const int cols = csr_cols(L, nb), tail = csr_tail(L, nb);
-    if (pre > 0) vec_zero<T>(x, n, nb, act, s_);
+    const int tail = csr_tail(L, nb);
+    if (pre > 0) vec_zero<T>(x, n * nb, 1, nullptr, s_);
     for (int i = 0; i < pre; ++i)
       timed<T>(l, kTimGs, 3.0 * en + sweep_mat / nb, act, nb,
-               [&] { csr_gs_sweep<T>(b, x, S, (int)n, nb, cols, tail, act, false, s_); });
+               [&] { rows_gs_sweep<T>(b, x, S, nb, tail, act, false, s_); });
     T* bc = w.vb[l];
     T* ec = w.vx[l];
     if (general_) {  // given P and R = P^T
       const CsrMat<T>& Pm = csr_P<T>(l);
       const CsrMat<T>& Rm = csr_R<T>(l);
       if (pre == 0) {
-        csr_spmm<T>(b, bc, Rm, 1.0, 0.0, nb, cols, act, s_);
+        rows_spmm<T>(b, bc, Rm, 1.0, 0.0, nb, act, s_);
       } else {
         timed<T>(l, kTimResRestrict, 2.0 * en + enc + res_mat / nb, act, nb, [&] {
-          csr_residual<T, T, T>(b, x, w.vt[l - 1], A, nb, cols, act, nullptr, s_);
-          csr_spmm<T>(w.vt[l - 1], bc, Rm, 1.0, 0.0, nb, cols, act, s_);
+          rows_residual<T, T>(b, x, w.vt[l - 1], A, nb, act, nullptr, s_);
+          rows_spmm<T>(w.vt[l - 1], bc, Rm, 1.0, 0.0, nb, act, s_);
         });
       }
       vcycle_csr<T>(l + 1, bc, ec, nb, act, nullptr);
       second_coarse_cycle<T>(l, bc, ec, nb, act, top);
       timed<T>(l, kTimProlong, (pre == 0 ? 1.0 : 2.0) * en + enc, act, nb, [&] {
-        csr_spmm<T>(ec, x, Pm, omega_, pre == 0 ? 0.0 : 1.0, nb, cols, act, s_);
+        rows_spmm<T>(ec, x, Pm, omega_, pre == 0 ? 0.0 : 1.0, nb, act, s_);
       });
     } else {
       if (pre == 0)
-        csr_restrict<T>(nullptr, b, bc, nullptr, A, G, nb, cols, act, s_);
+        rows_agg_sum<T>(b, bc, G, nb, act, s_);
       else  // the residual passes through the level's scratch vector
         timed<T>(l, kTimResRestrict, 2.0 * en + enc + res_mat / nb, act, nb,
-                 [&] { csr_restrict<T>(b, x, bc, w.vt[l - 1], A, G, nb, cols, act, s_); });
+                 [&] {
+                   rows_residual<T, T>(b, x, w.vt[l - 1], A, nb, act, nullptr, s_);
+                   rows_agg_sum<T>(w.vt[l - 1], bc, G, nb, act, s_);
+                 });
       vcycle_csr<T>(l + 1, bc, ec, nb, act, nullptr);
       second_coarse_cycle<T>(l, bc, ec, nb, act, top);
       timed<T>(l, kTimProlong, (pre == 0 ? 1.0 : 2.0) * en + enc, act, nb, [&] {
-        csr_prolong<T>(ec, x, G, (int)n, omega_, pre == 0 ? 0.0 : 1.0, nb, act, s_);
+        rows_prolong<T>(ec, x, G, (int)n, omega_, pre == 0 ? 0.0 : 1.0, nb, act, s_);
       });
     }
     for (int i = 0; i < post; ++i)
       timed<T>(l, kTimGs, 3.0 * en + sweep_mat / nb, act, nb,
-               [&] { csr_gs_sweep<T>(b, x, S, (int)n, nb, cols, tail, act, true, s_); });
+               [&] { rows_gs_sweep<T>(b, x, S, nb, tail, act, true, s_); });
   }
-  if (rz_partials) vec_dot_partials<T>(b, x, n, nb, act, rz_partials, s_);
+  if (rz_partials) rows_dot<T>(b, x, (int)n, nb, act, rz_partials, s_);
 }
 
 template void Context::vcycle_csr<float>(int, const float*, float*, int, const int*, c64*, bool);

@@ -465,19 +465,19 @@ struct CsrMat {
   const int* rp = nullptr;    // n + 1 row offsets
   const int* ci = nullptr;    // column of each entry
   const T* v = nullptr;       // value of each entry
-  const int* sptr = nullptr;  // SELL-64 slice offsets (ceil(n/64) + 1)
+  const int* sptr = nullptr;  // SELL-64 slice offsets (ceil(n/64) + 1), FP64 only
   const int* sci = nullptr;
   const T* sv = nullptr;
 };
-// the off-diagonal part with rows grouped by colour class, in SELL-64 slices
-// that never straddle two classes: class c owns slices soff[c]..soff[c+1]-1
-// (host offsets); position k = 64 s + l holds row srow[k] (-1: padding) with
-// sdi[k] = 1 / a_ii
+// the off-diagonal part with rows grouped by colour class (ascending within a
+// class): class c owns positions off[c]..off[c+1]-1 (host offsets); position k is
+// the row rows[k].x with entries rows[k].y .. rows[k].z - 1 and di[k] = 1 / a_ii
 template <typename T>
 struct CsrSweep {
-  const int *srow = nullptr, *sptr = nullptr, *sci = nullptr;
-  const T *sv = nullptr, *sdi = nullptr;
-  std::vector<int> soff;
+  const int4* rows = nullptr;
+  const int* ci = nullptr;
+  const T *v = nullptr, *di = nullptr;
+  std::vector<int> off;
 };
 // aggregation to the next level: agg[i] = aggregate of unknown i; the members
 // of J are arows[aptr[J]..aptr[J+1]-1] (ascending); fs[i] = cs[agg[i]] = 1/sqrt|J|
@@ -487,53 +487,130 @@ struct CsrAgg {
   const int *agg = nullptr, *aptr = nullptr, *arows = nullptr;
   const T *fs = nullptr, *cs = nullptr;
 };
-int csr_blocks(int n);  // partial sums per column of csr_residual / csr_update_apply
+// FP64 building blocks on RHS-major blocks (from the SELL-64 copies)
+int csr_blocks(int n);  // partial sums per column of csr_residual
 // r = b - A x (r = A x when b is null); partials as the stencil residuals
-template <typename Tb, typename T, typename Tr>
-void csr_residual(const Tb* b, const T* x, Tr* r, const CsrMat<T>& A, int nb, int cols,
+void csr_residual(const double* b, const double* x, double* r, const CsrMat<double>& A, int nb,
                   const int* active, c64* partials, hipStream_t s);
-// p_new = z + beta p_old, q = A p_new, partials of p_new^T q
-template <typename T>
-void csr_update_apply(const T* p_old, const T* z, const c64* beta, T* p_new, T* q,
-                      const CsrMat<T>& A, int nb, int cols, const int* active, c64* partials,
-                      hipStream_t s);
+// xc = R x, R = P^T
+void csr_restrict(const double* x, double* xc, const CsrAgg<double>& G, int n, int nb,
+                  const int* active, hipStream_t s);
+// x = beta x + omega P ec
+void csr_prolong(const double* ec, double* x, const CsrAgg<double>& G, int n, double omega,
+                 double beta, int nb, const int* active, hipStream_t s);
+// y = beta y + w M x for a rectangular M (M.n x M.ncol; y has M.n, x M.ncol
+// entries per column; beta = 0: y is not read): the general prolongation
+// (M = P) and restriction (M = R = P^T) between CSR levels
+void csr_spmm(const double* x, double* y, const CsrMat<double>& M, double w, double beta, int nb,
+              const int* active, hipStream_t s);
+// left half of the n x 2n augmented matrix [A | .] (rows of width 2n)
+void csr_dense(const CsrMat<double>& A, double* aug, hipStream_t s);
+
+// ----- the solver's kernels on interleaved blocks of W vectors ----------------
+// (element i of vector c at [i W + c]; from the plain CSR copies)
+int rows_per_block(int n);
+int rows_blocks(int n);  // partial sums per column of the reductions below
+// RHS-major FP64 block -> interleaved FP64 (dst, nullable) and To (dst2, nullable)
+template <typename To>
+void rows_in(const double* src, double* dst, To* dst2, int64_t n, int W, hipStream_t s);
+// interleaved block -> RHS-major FP64 block
+template <typename Ts>
+void rows_out(const Ts* src, double* dst, int64_t n, int W, hipStream_t s);
 // One Gauss-Seidel sweep in place over the colour classes (reverse: last class
 // first).  Each class is one launch, except the trailing run of classes of at
-// most tail_slices slices each (csr_tail_start; tail_slices 0: none), which
-// shares launches of up to kMaxTailClasses classes: one workgroup of
-// kTailWaves waves per column group, a barrier between classes.  The rows of a
-// class are independent, so both schedules give the same result.
+// most tail_rows rows each (csr_tail_start; 0: none), which shares launches of up
+// to kMaxTailClasses classes: one workgroup of kTailWaves waves per column group,
+// a barrier between classes.  The rows of a class are independent, so both
+// schedules give the same result.
 constexpr int kTailWaves = 16;
 constexpr int kMaxTailClasses = 64;
 struct CsrTail {
   int count, reverse;
-  int soff[kMaxTailClasses + 1];
+  int off[kMaxTailClasses + 1];
 };
-inline int csr_tail_start(const std::vector<int>& soff, int tail_slices) {
-  int c = (int)soff.size() - 1;
-  if (tail_slices <= 0) return c;
-  while (c > 0 && soff[c] - soff[c - 1] <= tail_slices) --c;
+inline int csr_tail_start(const std::vector<int>& off, int tail_rows) {
+  int c = (int)off.size() - 1;
+  if (tail_rows <= 0) return c;
+  while (c > 0 && off[c] - off[c - 1] <= tail_rows) --c;
   return c;
 }
 template <typename T>
-void csr_gs_sweep(const T* b, T* x, const CsrSweep<T>& S, int n, int nb, int cols,
-                  int tail_slices, const int* active, bool reverse, hipStream_t s);
-// xc = R (b - A x) (b non-null; the residual goes through rtmp, n x nb) or
-// xc = R x (b null), R = P^T
+void rows_gs_sweep(const T* b, T* x, const CsrSweep<T>& S, int W, int tail_rows, const int* active,
+                   bool reverse, hipStream_t s);
+// r = b - A x ; partials (nullable) of |r|^2
+template <typename T, typename Tr>
+void rows_residual(const T* b, const T* x, Tr* r, const CsrMat<T>& A, int W, const int* active,
+                   c64* partials, hipStream_t s);
+// p_new = z + beta p_old, q = A p_new, partials of p_new^T q
 template <typename T>
-void csr_restrict(const T* b, const T* x, T* xc, T* rtmp, const CsrMat<T>& A,
-                  const CsrAgg<T>& G, int nb, int cols, const int* active, hipStream_t s);
-// x = beta x + omega P ec
+void rows_update_apply(const T* p_old, const T* z, const c64* beta, T* p_new, T* q,
+                       const CsrMat<T>& A, int W, const int* active, c64* partials, hipStream_t s);
+// x += alpha p ; r -= alpha q ; partials of |r|^2 (x_zero: x taken as zero)
 template <typename T>
-void csr_prolong(const T* ec, T* x, const CsrAgg<T>& G, int n, double omega, double beta, int nb,
-                 const int* active, hipStream_t s);
-// left half of the n x 2n augmented matrix [A | .] (rows of width 2n)
-void csr_dense(const CsrMat<double>& A, double* aug, hipStream_t s);
-// y = beta y + w M x for a rectangular M (M.n x M.ncol; y has M.n, x M.ncol
-// entries per column; beta = 0: y is not read): the general prolongation
-// (M = P) and restriction (M = R = P^T) between CSR levels
+void rows_xr(T* x, T* r, const T* p, const T* q, const c64* alpha, int n, int W, const int* active,
+             c64* partials, bool x_zero, hipStream_t s);
+// partials of x^T y
 template <typename T>
-void csr_spmm(const T* x, T* y, const CsrMat<T>& M, double w, double beta, int nb, int cols,
-              const int* active, hipStream_t s);
+void rows_dot(const T* x, const T* y, int n, int W, const int* active, c64* partials,
+              hipStream_t s);
+// y += d, partials of b^T d, d = 0 (y_zero: y taken as zero)
+void rows_fold(double* y, float* d, const double* b, int n, int W, const int* active,
+               c64* partials, bool y_zero, hipStream_t s);
+// y = beta y + w M x (M rectangular; beta = 0: y is not read)
+template <typename T>
+void rows_spmm(const T* x, T* y, const CsrMat<T>& M, double w, double beta, int W,
+               const int* active, hipStream_t s);
+// rc = R r ; x = beta x + omega P ec, aggregation
+template <typename T>
+void rows_agg_sum(const T* r, T* rc, const CsrAgg<T>& A, int W, const int* active, hipStream_t s);
+template <typename T>
+void rows_prolong(const T* ec, T* x, const CsrAgg<T>& A, int n, double omega, double beta, int W,
+                  const int* active, hipStream_t s);
+// Z = A^-1 B from the packed transposed inverse (dense_pack4)
+template <typename T>
+void rows_dense(const T* Pk, const T* B, T* Z, int n, int ld, int W, const int* active,
+                hipStream_t s);
+
+// ----- small levels of a matrix-given hierarchy, one vector per workgroup -----
+constexpr int kSmallCsrLds = 160 * 1024;  // a compute unit's LDS: the iterate fits
+constexpr int kSmallCsrDense = 256;       // largest coarsest level solved in the kernel
+// SELL-64 rows (slice s: ptr[s] .. ptr[s + 1] - 1, entry-major), 16-bit columns
+template <typename T>
+struct SellView {
+  const int* ptr = nullptr;
+  const unsigned short* ci = nullptr;
+  const T* v = nullptr;
+};
+// a smoothed level; unknowns numbered by position in the sweep's order, classes
+// padded to whole slices (np positions in all)
+template <typename T>
+struct SmallCsrLevel {
+  int np = 0, ncls = 0;
+  const int* cls = nullptr;          // first slice of each class (ncls + 1)
+  const int* row = nullptr;          // natural index of a position (-1: padding)
+  SellView<T> off;                   // off-diagonal part
+  const T *di = nullptr, *dd = nullptr;  // 1 / a_ii and a_ii (padding: 0)
+  // transfers to the next level (its positions; natural order on the coarsest):
+  // aggregation (members of J in mem[mptr[J]..], scales) or, with mptr null, R and P
+  const int *mptr = nullptr, *mem = nullptr, *agg = nullptr;
+  const T *cs = nullptr, *fs = nullptr;
+  SellView<T> R, P;
+  T *b = nullptr, *x = nullptr, *r = nullptr;  // blocks [vector][position]
+};
+template <typename T>
+struct SmallCsrCoarse {
+  int n = 0, ld = 0;
+  const T* inv = nullptr;            // packed transposed inverse (dense_pack4)
+  T *b = nullptr, *x = nullptr;      // blocks [vector][unknown]
+};
+enum { kSmallCsrAll = 0, kSmallCsrDown = 1, kSmallCsrUp = 2 };
+void small_csr_setup();
+// one V-cycle x = M b of the nl levels lev (device array), b and x interleaved
+// blocks of W vectors of the first one: all of it (coarsest solve included, n <=
+// kSmallCsrDense), or the parts before and after the coarsest solve
+template <typename T>
+void small_csr(const SmallCsrLevel<T>* lev, int nl, int np_max, const SmallCsrCoarse<T>& cs,
+               const T* b, T* x, int W, int pre, int post, double omega, int mode,
+               const int* active, hipStream_t s);
 
 }  // namespace mlmc
