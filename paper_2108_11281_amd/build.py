@@ -14,6 +14,7 @@ SOURCES = [
     "kernels_poisson.hip",
     "kernels_small.hip",
     "kernels_wilson.hip",
+    "kernels_bsr8.hip",
     "kernels_krylov.hip",
     "kernels_varcoef.hip",
     "kernels_nn.hip",

@@ -1405,7 +1405,7 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
                                 reinterpret_cast<const c64*>(y), reinterpret_cast<c64*>(r64_),
                                 nb, nullptr, partials_);
     finish_sums(partials_, lv_[l - 1].wilson ? wilson_residual_blocks(lv_[l - 1].side)
-                                             : bsr_residual_blocks(lv_[l - 1].side),
+                                             : bsr_residual_blocks(lv_[l - 1].side, lv_[l - 1].dof),
                 nb, rres, s_);
     vec_dot_partials<c64>(reinterpret_cast<const c64*>(b), reinterpret_cast<const c64*>(b), n,
                           nb, nullptr, partials_, s_);

@@ -245,6 +245,7 @@ void Context::tune_bsr() {
   };
   for (int l = 2; l < Ls_; ++l) {
     Level& L = lv_[l - 1];
+    if (L.dof == 8) continue;  // one form, on the matrix cores
     if (opt_.precision == MLMC_FP32_IR64)
       L.bsr_form[0] = time_form(c32(), L, l, 1) < time_form(c32(), L, l, 0) ? 1 : 0;
     else
@@ -477,7 +478,7 @@ void Context::solve_complex(int l, const c64* b, c64* y, int nb, c64* err) {
   const Level& L = lv_[l - 1];
   const int64_t n = L.n;
   const int nblk = reduce_blocks(n);
-  const int rblk = L.wilson ? wilson_residual_blocks(L.side) : bsr_residual_blocks(L.side);
+  const int rblk = L.wilson ? wilson_residual_blocks(L.side) : bsr_residual_blocks(L.side, L.dof);
   c64 *bb = scal_[kBb], *bd = scal_[kBd], *rr_old = scal_[kRres], *rr_new = scal_[kRres2];
   const double tol = opt_.solve_tol;
   vec_dot_partials<c64>(b, b, n, nb, nullptr, partials_, s_);

@@ -382,7 +382,7 @@ void nn_round_inputs(const float* src, void* dst, int64_t count, hipStream_t s);
 
 // ----- complex lattice operators (Wilson 2-spin, block stencils, transfers) ---
 int wilson_residual_blocks(int N);
-int bsr_residual_blocks(int Nc);
+int bsr_residual_blocks(int Nc, int dof);
 // r = b - D x ; b == nullptr: r = D x (partials then of conj(x)^T r)
 template <typename Tb, typename T, typename Tr>
 void wilson_residual(const Tb* b, const T* x, Tr* r, const T* U, int N, double diag, int nb,
@@ -406,6 +406,18 @@ void bsr_residual(const Tb* b, const T* x, Tr* r, const T* B, int Nc, int dof, i
 template <typename T>
 void bsr_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int dof, int nb,
               const int* active, bool zero_init, bool reverse, int form, hipStream_t s);
+// the same with eight unknowns per (coarse) site, on the matrix cores; the
+// restriction needs rows of blk dofF fine unknowns that are a multiple of eight
+int bsr8_residual_blocks(int Nc);
+template <typename T>
+void bsr8_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int nb, const int* active,
+               bool zero_init, bool reverse, hipStream_t s);
+template <typename T, typename Tr>
+void bsr8_residual(const T* b, const T* x, Tr* r, const T* B, int Nc, int nb, const int* active,
+                   c64* partials, hipStream_t s);
+template <typename T>
+void agg8_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int nb,
+                   const int* active, hipStream_t s);
 template <typename T>
 void agg_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int dofC, int nb,
                   const int* active, hipStream_t s);
