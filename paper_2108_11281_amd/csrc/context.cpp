@@ -119,6 +119,7 @@ Context::~Context() {
   }
   if (count_host_) (void)hipHostFree(count_host_);
   if (host_c64_) (void)hipHostFree(host_c64_);
+  if (nn_host_) (void)hipHostFree(nn_host_);
 }
 
 void* Context::dalloc(size_t bytes) {

@@ -442,6 +442,14 @@ class Context {
   bool nn_ready_ = false, nn_use_ = false;
   float *nn_w_ = nullptr, *nn_m_ = nullptr, *nn_v_ = nullptr, *nn_g_ = nullptr;
   void *nn_frag_ = nullptr, *nn_links_ = nullptr;
+  float* nn_host_ = nullptr;  // pinned: gradient and loss
+  // work buffers of nn_loss_grad, kept for steps of up to kNnKeepCrops crops
+  static constexpr int kNnKeepCrops = 1024;
+  void* nn_ws_in_ = nullptr;
+  float* nn_ws_g_ = nullptr;
+  double* nn_ws_l_ = nullptr;
+  int nn_ws_crops_ = 0;
+  void nn_free_ws();
   double* theta_dev_ = nullptr;
   double* nn_loss_ = nullptr;
   int m_ = 16;                    // FGMRES restart length
