@@ -445,7 +445,6 @@ class Context {
   float* nn_host_ = nullptr;  // pinned: gradient and loss
   // work buffers of nn_loss_grad, kept for steps of up to kNnKeepCrops crops
   static constexpr int kNnKeepCrops = 1024;
-  void* nn_ws_in_ = nullptr;
   float* nn_ws_g_ = nullptr;
   double* nn_ws_l_ = nullptr;
   int nn_ws_crops_ = 0;

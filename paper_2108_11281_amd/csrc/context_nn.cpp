@@ -101,22 +101,18 @@ void Context::nn_loss_grad(int ncrops, const float* in, const float* tgt, double
   MLMC_REQUIRE(nn_ready_, MLMC_ESTATE, "no network weights set or trained");
   MLMC_REQUIRE(ncrops >= 1 && ncrops <= 65536, MLMC_EINVAL, "ncrops must be in [1, 65536]");
   const int nw = nn_num_weights();
-  const int64_t nin = (int64_t)ncrops * nn_crop_in_elems();
   // the work buffers of a training loop's steps are kept, up to kNnKeepCrops crops
-  // (24 KiB each), and grow to the largest step: an allocation and its release
+  // (16 KiB each), and grow to the largest step: an allocation and its release
   // synchronise the stream, which took about 40 of the 125 us of a step of 256 crops
   const bool keep = ncrops <= kNnKeepCrops;
   if (!keep || ncrops > nn_ws_crops_) {
     nn_free_ws();
-    nn_ws_in_ = dalloc((size_t)nin * 2);
     nn_ws_g_ = dalloc_n<float>((int64_t)ncrops * nw);
     nn_ws_l_ = dalloc_n<double>(ncrops);
     nn_ws_crops_ = ncrops;
   }
   double* l = reinterpret_cast<double*>(nn_g_ + nw);
-  nn_round_inputs(in, nn_ws_in_, nin, s_);
-  nn_train_step(nn_ws_in_, tgt, nullptr, ncrops, nn_frag_, nn_w_, nn_ws_g_, nn_ws_l_, nn_g_, l,
-                s_);
+  nn_train_step(in, true, tgt, nullptr, ncrops, nn_frag_, nn_w_, nn_ws_g_, nn_ws_l_, nn_g_, l, s_);
   MLMC_HIP(hipMemcpyAsync(nn_host_, nn_g_, sizeof(float) * (nw + 2), hipMemcpyDeviceToHost, s_));
   MLMC_HIP(hipStreamSynchronize(s_));
   MLMC_HIP(hipGetLastError());
@@ -127,8 +123,6 @@ void Context::nn_loss_grad(int ncrops, const float* in, const float* tgt, double
 
 void Context::nn_free_ws() {
   nn_ws_crops_ = 0;
-  dfree(nn_ws_in_);
-  nn_ws_in_ = nullptr;
   dfree(nn_ws_g_);
   nn_ws_g_ = nullptr;
   dfree(nn_ws_l_);
@@ -190,8 +184,7 @@ void Context::nn_adam_step(const float* grad, double lr, int t) {
   }
   std::memcpy(nn_host_, grad, sizeof(float) * nw);
   MLMC_HIP(hipMemcpyAsync(nn_g_, nn_host_, sizeof(float) * nw, hipMemcpyHostToDevice, s_));
-  nn_adam(nn_w_, nn_m_, nn_v_, nn_g_, lr, 0.9, 0.999, 1e-8, t, s_);
-  nn_pack(nn_w_, nn_frag_, s_);
+  nn_adam(nn_w_, nn_m_, nn_v_, nn_g_, nn_frag_, lr, 0.9, 0.999, 1e-8, t, s_);
   MLMC_HIP(hipStreamSynchronize(s_));
   MLMC_HIP(hipGetLastError());
 }
@@ -297,15 +290,14 @@ void Context::nn_train(const float* w_init, const mlmc_train_options& o,
   double* lpart = dalloc_n<double>(o.batch);
   double* losses = dalloc_n<double>(o.steps);
   int64_t pos = 0;
+  nn_pack(nn_w_, nn_frag_, s_);
   for (int t = 1; t <= o.steps; ++t) {
-    nn_pack(nn_w_, nn_frag_, s_);
-    nn_train_step(in, tgt, order_dev + pos, o.batch, nn_frag_, nn_w_, gpart, lpart, nn_g_,
+    nn_train_step(in, false, tgt, order_dev + pos, o.batch, nn_frag_, nn_w_, gpart, lpart, nn_g_,
                   losses + (t - 1), s_);
-    nn_adam(nn_w_, nn_m_, nn_v_, nn_g_, o.lr, 0.9, 0.999, 1e-8, t, s_);
+    nn_adam(nn_w_, nn_m_, nn_v_, nn_g_, nn_frag_, o.lr, 0.9, 0.999, 1e-8, t, s_);
     pos += o.batch;
     if (pos >= ncrops) pos -= ncrops;
   }
-  nn_pack(nn_w_, nn_frag_, s_);
   std::vector<double> hl((size_t)o.steps);
   MLMC_HIP(hipMemcpyAsync(hl.data(), losses, sizeof(double) * o.steps, hipMemcpyDeviceToHost, s_));
   MLMC_HIP(hipStreamSynchronize(s_));

@@ -367,18 +367,17 @@ void nn_pack(const float* w, void* frag, hipStream_t s);
 void nn_apply(const c32* r, c32* x, const c64* rr, double inv_n, const void* links,
               const void* frag, int N, int nb, const int* active, hipStream_t s);
 // forward + backward of ncrops crops (crop order[i], or i when order is null):
-// per-crop gradients, then grad = their fixed-order sum and *loss = the mean
+// (inputs BF16, or FP32 that are rounded) per-crop gradients, then grad = their fixed-order sum and *loss = the mean
 // squared error
-void nn_train_step(const void* in, const float* tgt, const int* order, int ncrops,
+void nn_train_step(const void* in, bool in_fp32, const float* tgt, const int* order, int ncrops,
                    const void* frag, const float* w, float* gpart, double* lpart, float* grad,
                    double* loss, hipStream_t s);
-// Adam step t (from 1) on the FP32 master weights
-void nn_adam(float* w, float* m, float* v, const float* g, double lr, double b1, double b2,
-             double eps, int t, hipStream_t s);
+// Adam step t (from 1) on the FP32 master weights, and their fragments as nn_pack's
+void nn_adam(float* w, float* m, float* v, const float* g, void* frag, double lr, double b1,
+             double b2, double eps, int t, hipStream_t s);
 // training crops from FP64 residual / error fields (origin: column, y0, x0 per crop)
 void nn_crops(const c64* r, const c64* e, const c64* rr, double inv_n, const void* links,
               const int* origin, int ncrops, int N, void* in, float* tgt, hipStream_t s);
-void nn_round_inputs(const float* src, void* dst, int64_t count, hipStream_t s);
 
 // ----- complex lattice operators (Wilson 2-spin, block stencils, transfers) ---
 int wilson_residual_blocks(int N);

@@ -44,6 +44,13 @@ __device__ __forceinline__ bf8 bf8_zero() {
   return z;
 }
 
+// this lane's weight fragments of a forward layer
+template <int NCH>
+__device__ __forceinline__ void load_frags(const bf8* __restrict__ frag, int lane, bf8 (&b)[NCH]) {
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) b[c] = frag[c * 64 + lane];
+}
+
 // One forward convolution layer of a workgroup (NW waves): out region Ho x Wo
 // from the input region (Ho+2) x (Wo+2) in LDS ([site][CIN] BF16, or with PIN
 // two planes [CIN/8][site][8] of in_plane sites).  Output either BF16
@@ -54,11 +61,8 @@ __device__ __forceinline__ bf8 bf8_zero() {
 template <int NW, int CIN, int COUT, int NCH, bool RELU, bool F32OUT, bool PIN = false,
           bool POUT = false>
 __device__ void conv_fwd(const __bf16* __restrict__ in, int Wi, void* out, int Wo, int Ho,
-                         const bf8* __restrict__ frag, int wave, int lane, int in_plane = 0,
+                         const bf8 (&b)[NCH], int wave, int lane, int in_plane = 0,
                          int out_plane = 0) {
-  bf8 b[NCH];
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) b[c] = frag[c * 64 + lane];
   const int nsites = Wo * Ho;
   const int mtiles = (nsites + 15) / 16;
   const int g = lane >> 4, r16 = lane & 15;
@@ -145,16 +149,22 @@ __global__ __launch_bounds__(256) void k_nn_apply(const c32* __restrict__ r, c32
     d[7] = links[site * 4 + 3];
   }
   __syncthreads();
+  bf8 f1[kCh1];
+  load_frags(frag + kFragL1 * 64, lane, f1);
   conv_fwd<4, kC0, kC1, kCh1, true, false, false, true>(sm.x0, kT0, sm.h1, kT1, kT1,
-                                                     frag + kFragL1 * 64, wave, lane, 0,
+                                                     f1, wave, lane, 0,
                                                      kT1 * kT1);
   __syncthreads();
+  bf8 f2[kCh2];
+  load_frags(frag + kFragL2 * 64, lane, f2);
   conv_fwd<4, kC1, kC2, kCh2, true, false, true, true>(sm.h1, kT1, sm.h2, kT2, kT2,
-                                                    frag + kFragL2 * 64, wave, lane, kT1 * kT1,
+                                                    f2, wave, lane, kT1 * kT1,
                                                     kT2 * kT2);
   __syncthreads();
+  bf8 f3[kCh3];
+  load_frags(frag + kFragL3 * 64, lane, f3);
   conv_fwd<4, kC2, kC3, kCh3, false, true, true, false>(sm.h2, kT2, sm.o, kTo, kTo,
-                                                     frag + kFragL3 * 64, wave, lane, kT2 * kT2);
+                                                     f3, wave, lane, kT2 * kT2);
   __syncthreads();
   {
     const int ly = tid / kTo, lx = tid - ly * kTo;
@@ -182,10 +192,9 @@ __global__ void k_nn_links(const double* __restrict__ theta, __bf16* __restrict_
   }
 }
 
-// forward B fragments from the FP32 master weights W[co][ci][tap]
-__global__ void k_nn_pack(const float* __restrict__ w, bf8* __restrict__ frag) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= kFrags * 64) return;
+// forward B fragment of lane t % 64, chunk t / 64, from the FP32 master weights
+// W[co][ci][tap]
+__device__ __forceinline__ void pack_fragment(const float* w, bf8* __restrict__ frag, int t) {
   const int chunk = t / 64, lane = t % 64;
   int layer, c, cin, cout, off;
   if (chunk < kFragL2) {
@@ -206,6 +215,11 @@ __global__ void k_nn_pack(const float* __restrict__ w, bf8* __restrict__ frag) {
     v[j] = (__bf16)val;
   }
   frag[t] = v;
+}
+
+__global__ void k_nn_pack(const float* __restrict__ w, bf8* __restrict__ frag) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < kFrags * 64) pack_fragment(w, frag, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -289,16 +303,12 @@ __device__ void conv_wgrad(const __bf16* __restrict__ dy, const __bf16* __restri
 // over the WI x WI input region; dY [site][DYS] on the (WI-2) x (WI-2) output
 // region (DYS = padded channel count, 8 or 16), W FP32 master weights of the
 // layer; result BF16 [site][16].  Tiles first, first + stride, ...
-template <int CIN, int COUT, int DYS, int WI>
-__device__ void conv_dgrad(const __bf16* __restrict__ dy, const __bf16* __restrict__ X,
-                           const float* __restrict__ W, __bf16* __restrict__ dx, int first,
-                           int stride, int lane) {
-  constexpr int K = 9 * DYS;
-  constexpr int NCH = (K + 31) / 32;
-  constexpr int Wo = WI - 2;
+constexpr int dgrad_chunks(int dys) { return (9 * dys + 31) / 32; }
+template <int CIN, int COUT, int DYS, int NCH>
+__device__ __forceinline__ void dgrad_frags(const float* __restrict__ W, int lane, bf8 (&b)[NCH]) {
+  static_assert(NCH == dgrad_chunks(DYS), "whole rows of weights");
   const int g = lane >> 4, r16 = lane & 15;
   // B fragments: k = tap * DYS + co, column ci = r16
-  bf8 b[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
 #pragma unroll
@@ -309,6 +319,14 @@ __device__ void conv_dgrad(const __bf16* __restrict__ dy, const __bf16* __restri
                                                    : (__bf16)0.0f;
     }
   }
+}
+
+template <int CIN, int DYS, int WI, int NCH>
+__device__ void conv_dgrad(const __bf16* __restrict__ dy, const __bf16* __restrict__ X,
+                           const bf8 (&b)[NCH], __bf16* __restrict__ dx, int first, int stride,
+                           int lane) {
+  constexpr int Wo = WI - 2;
+  const int g = lane >> 4, r16 = lane & 15;
   constexpr int nsites = WI * WI, mtiles = (nsites + 15) / 16;
   for (int m = first; m < mtiles; m += stride) {
     const int q = 16 * m + r16;
@@ -339,13 +357,16 @@ __device__ void conv_dgrad(const __bf16* __restrict__ dy, const __bf16* __restri
 }
 
 // 256 crops on an MI355X: 42 us with four waves per crop and two-byte gathers, 25 us with
-// sixteen waves, 21 us with transposing reads; bound by the chain of six layers.
+// sixteen waves, 21 us with transposing reads (FP32 inputs rounded on the way, a pass of
+// 4 us before); bound by the chain of six layers.
 // Sixteen waves per crop: a step of 256 crops puts one workgroup on each CU, and the
 // chain of barriers and LDS gathers needs the waves to hide it.  Of each backward layer
 // nine waves form the weight gradient (one tap each) while the other seven form the data
 // gradient.
 constexpr int kTrainThreads = 1024, kTrainWaves = kTrainThreads / 64;
-__global__ __launch_bounds__(kTrainThreads) void k_nn_train(const __bf16* __restrict__ in,
+static_assert(kT0 * kT0 <= kTrainThreads, "one thread per input site");
+template <typename Tin>
+__global__ __launch_bounds__(kTrainThreads) void k_nn_train(const Tin* __restrict__ in,
                                                             const float* __restrict__ tgt,
                                                             const int* __restrict__ order,
                                                             const bf8* __restrict__ frag,
@@ -358,26 +379,37 @@ __global__ __launch_bounds__(kTrainThreads) void k_nn_train(const __bf16* __rest
   const int crop = order ? order[item] : item;       // crop in the data set
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the three layers' weights and the targets are on their way before the first layer
+  bf8 f1[kCh1], f2[kCh2], f3[kCh3];
+  load_frags(frag + kFragL1 * 64, lane, f1);
+  load_frags(frag + kFragL2 * 64, lane, f2);
+  load_frags(frag + kFragL3 * 64, lane, f3);
+  float t[kC3] = {0.f, 0.f, 0.f, 0.f};
+  if (tid < kTo * kTo) {
+#pragma unroll
+    for (int c = 0; c < kC3; ++c) t[c] = tgt[((int64_t)crop * kTo * kTo + tid) * kC3 + c];
+  }
   {
-    const bf8* src = reinterpret_cast<const bf8*>(in + (int64_t)crop * kT0 * kT0 * kC0);
+    // FP32 inputs are rounded here
+    typedef Tin in8 __attribute__((ext_vector_type(8), aligned(sizeof(Tin) == 4 ? 4 : 16)));
+    const in8* src = reinterpret_cast<const in8*>(in + (int64_t)crop * kT0 * kT0 * kC0);
     bf8* dst = reinterpret_cast<bf8*>(sm.x0);
-    for (int i = tid; i < kT0 * kT0; i += kTrainThreads) dst[i] = src[i];
+    if (tid < kT0 * kT0) dst[tid] = __builtin_convertvector(src[tid], bf8);
     if (tid < 4) sm.zero[tid] = (__bf16)0.0f;
   }
   __syncthreads();
   conv_fwd<kTrainWaves, kC0, kC1, kCh1, true, false>(sm.x0, kT0, sm.h1, kT1, kT1,
-                                                     frag + kFragL1 * 64, wave, lane);
+                                                     f1, wave, lane);
   __syncthreads();
   conv_fwd<kTrainWaves, kC1, kC2, kCh2, true, false>(sm.h1, kT1, sm.h2, kT2, kT2,
-                                                     frag + kFragL2 * 64, wave, lane);
+                                                     f2, wave, lane);
   __syncthreads();
   conv_fwd<kTrainWaves, kC2, kC3, kCh3, false, true>(sm.h2, kT2, sm.o, kTo, kTo,
-                                                     frag + kFragL3 * 64, wave, lane);
+                                                     f3, wave, lane);
   __syncthreads();
   // loss and dL/d out (one site per thread)
   double l2 = 0.0;
   if (tid < kTo * kTo) {
-    const float* t = tgt + ((int64_t)crop * kTo * kTo + tid) * kC3;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       float d = 0.f;
@@ -388,21 +420,26 @@ __global__ __launch_bounds__(kTrainThreads) void k_nn_train(const __bf16* __rest
       sm.dout[tid * 8 + c] = (__bf16)(dscale * d);
     }
   }
+  constexpr int NG = wgrad_items(16), ND = kTrainWaves - NG;
+  bf8 d3[dgrad_chunks(8)], d2[dgrad_chunks(16)];
+  if (wave >= NG) {
+    dgrad_frags<kC2, kC3, 8>(w + kOffW3, lane, d3);
+    dgrad_frags<kC1, kC2, 16>(w + kOffW2, lane, d2);
+  }
   double dummy = 0.0;
   block_sum2<kTrainThreads>(l2, dummy, sm.red);
   if (tid == 0) lpart[item] = l2;
   __syncthreads();
   float* gw = gpart + (int64_t)item * kNumW;
-  constexpr int NG = wgrad_items(16), ND = kTrainWaves - NG;
   if (wave < NG)
     conv_wgrad<kC2, kC3, 8, kTo>(sm.dout, sm.h2, sm.zero, gw + kOffW3, wave, lane);
   else
-    conv_dgrad<kC2, kC3, 8, kT2>(sm.dout, sm.h2, w + kOffW3, sm.dz2, wave - NG, ND, lane);
+    conv_dgrad<kC2, 8, kT2>(sm.dout, sm.h2, d3, sm.dz2, wave - NG, ND, lane);
   __syncthreads();
   if (wave < NG)
     conv_wgrad<kC1, kC2, 16, kT2>(sm.dz2, sm.h1, sm.zero, gw + kOffW2, wave, lane);
   else
-    conv_dgrad<kC1, kC2, 16, kT1>(sm.dz2, sm.h1, w + kOffW2, sm.dz1, wave - NG, ND, lane);
+    conv_dgrad<kC1, 16, kT1>(sm.dz2, sm.h1, d2, sm.dz1, wave - NG, ND, lane);
   __syncthreads();
   if (wave < wgrad_items(kC0))
     conv_wgrad<kC0, kC1, 16, kT1>(sm.dz1, sm.x0, sm.zero, gw + kOffW1, wave, lane);
@@ -452,17 +489,29 @@ __global__ __launch_bounds__(64) void k_nn_reduce(const float* __restrict__ gpar
   grad[i] = s;
 }
 
-__global__ void k_nn_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                          const float* __restrict__ g, float lr, float b1, float b2, float eps,
-                          float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= kNumW) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+// one Adam step; the block then packs the forward fragments of the new weights
+__global__ __launch_bounds__(1024) void k_nn_adam(float* __restrict__ w, float* __restrict__ m,
+                                                  float* __restrict__ v,
+                                                  const float* __restrict__ g,
+                                                  bf8* __restrict__ frag, float lr, float b1,
+                                                  float b2, float eps, float c1, float c2) {
+  __shared__ float ws[kNumW];
+#pragma unroll
+  for (int u = 0; u < (kNumW + 1023) / 1024; ++u) {
+    const int i = 1024 * u + threadIdx.x;
+    if (i < kNumW) {
+      const float gi = g[i];
+      const float mi = b1 * m[i] + (1.f - b1) * gi;
+      const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+      m[i] = mi;
+      v[i] = vi;
+      const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+      w[i] = wi;
+      ws[i] = wi;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kFrags * 64) pack_fragment(ws, frag, threadIdx.x);
 }
 
 // training crops: input [crop][22*22][8] BF16 from the residual r (scaled by the
@@ -501,14 +550,6 @@ __global__ void k_nn_crops(const c64* __restrict__ r, const c64* __restrict__ e,
   }
 }
 
-// FP32 crops (tests) -> BF16 inputs
-__global__ void k_nn_round_inputs(const float* __restrict__ src, __bf16* __restrict__ dst,
-                                  int64_t count) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = (__bf16)src[i];
-}
-
 }  // namespace
 
 int nn_num_weights() { return kNumW; }
@@ -535,32 +576,34 @@ void nn_apply(const c32* r, c32* x, const c64* rr, double inv_n, const void* lin
               active, timing_log());
 }
 
-void nn_train_step(const void* in, const float* tgt, const int* order, int ncrops,
+void nn_train_step(const void* in, bool in_fp32, const float* tgt, const int* order, int ncrops,
                    const void* frag, const float* w, float* gpart, double* lpart, float* grad,
                    double* loss, hipStream_t s) {
   const double count = (double)ncrops * kTo * kTo * kC3;
-  MLMC_LAUNCH(k_nn_train, dim3(ncrops), dim3(kTrainThreads), 0, s, static_cast<const __bf16*>(in), tgt,
-              order, static_cast<const bf8*>(frag), w, gpart, lpart, (float)(2.0 / count));
+  const bf8* f = static_cast<const bf8*>(frag);
+  if (in_fp32)
+    MLMC_LAUNCH(k_nn_train<float>, dim3(ncrops), dim3(kTrainThreads), 0, s,
+                static_cast<const float*>(in), tgt, order, f, w, gpart, lpart,
+                (float)(2.0 / count));
+  else
+    MLMC_LAUNCH(k_nn_train<__bf16>, dim3(ncrops), dim3(kTrainThreads), 0, s,
+                static_cast<const __bf16*>(in), tgt, order, f, w, gpart, lpart,
+                (float)(2.0 / count));
   hipLaunchKernelGGL(k_nn_reduce, dim3((kNumW + 63) / 64 + 1), dim3(64), 0, s, gpart, lpart,
                      ncrops, grad, loss, 1.0 / count);
 }
 
-void nn_adam(float* w, float* m, float* v, const float* g, double lr, double b1, double b2,
-             double eps, int t, hipStream_t s) {
+void nn_adam(float* w, float* m, float* v, const float* g, void* frag, double lr, double b1,
+             double b2, double eps, int t, hipStream_t s) {
   const double c1 = 1.0 - std::pow(b1, t), c2 = 1.0 - std::pow(b2, t);
-  hipLaunchKernelGGL(k_nn_adam, dim3((kNumW + 255) / 256), dim3(256), 0, s, w, m, v, g, (float)lr,
-                     (float)b1, (float)b2, (float)eps, (float)c1, (float)c2);
+  hipLaunchKernelGGL(k_nn_adam, dim3(1), dim3(1024), 0, s, w, m, v, g, static_cast<bf8*>(frag),
+                     (float)lr, (float)b1, (float)b2, (float)eps, (float)c1, (float)c2);
 }
 
 void nn_crops(const c64* r, const c64* e, const c64* rr, double inv_n, const void* links,
               const int* origin, int ncrops, int N, void* in, float* tgt, hipStream_t s) {
   hipLaunchKernelGGL(k_nn_crops, dim3(ncrops), dim3(256), 0, s, r, e, rr, inv_n,
                      static_cast<const __bf16*>(links), origin, N, static_cast<__bf16*>(in), tgt);
-}
-
-void nn_round_inputs(const float* src, void* dst, int64_t count, hipStream_t s) {
-  hipLaunchKernelGGL(k_nn_round_inputs, dim3(256), dim3(256), 0, s, src,
-                     static_cast<__bf16*>(dst), count);
 }
 
 }  // namespace mlmc
