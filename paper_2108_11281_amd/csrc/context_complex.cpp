@@ -419,9 +419,7 @@ void Context::fgmres_cycle(int l, const T* r, T* d, int nb, int* act, double tol
   const int nblk = reduce_blocks(n);
   c64 *beta2 = scal_[kRr0], *wn2 = scal_[kTmp];
   MLMC_HIP(hipMemcpyAsync(gstart_, act, sizeof(int) * nb, hipMemcpyDeviceToDevice, s_));
-  vec_dot_partials<T>(r, r, n, nb, act, partials_, s_);
-  finish_sums(partials_, nblk, nb, beta2, s_);
-  vec_scale_inv_norm<T>(f.V, r, beta2, n, nb, act, s_);
+  krylov_normalise<T>(f.V, r, n, nb, act, beta2, partials_, s_);
   givens_init(gH_, gcs_, gsn_, gg_, gdims_, beta2, act, m_, nb, s_);
   // with opts.graphs (and no kernel timing) every iteration replays a HIP graph
   // captured once per (precision, level, batch width, iteration, smoother):
@@ -442,13 +440,7 @@ void Context::fgmres_cycle(int l, const T* r, T* d, int nb, int* act, double tol
       T* w = f.V + (j + 1) * vs;
       cvcycle<T>(l, vj, zj, nb, act, true);
       cop_residual<T, T, T>(l, (const T*)nullptr, zj, w, nb, act, nullptr);
-      int mb = 0;
-      krylov_mdot<T>(f.V, vs, j + 1, w, n, nb, act, partials_, &mb, s_);
-      finish_sums(partials_, mb, nb * (j + 1), ghcol_, s_);
-      krylov_maxpy<T>(f.V, vs, j + 1, ghcol_, w, n, nb, act, s_);
-      vec_dot_partials<T>(w, w, n, nb, act, partials_, s_);
-      finish_sums(partials_, nblk, nb, wn2, s_);
-      vec_scale_inv_norm<T>(w, w, wn2, n, nb, act, s_);
+      krylov_orthonormalise<T>(f.V, vs, j + 1, w, n, nb, act, ghcol_, wn2, partials_, s_);
       givens_step(gH_, gcs_, gsn_, gg_, gdims_, ghcol_, wn2, beta2, tol, j, m_, act, nb,
                   count_map_ + 5 + (j & 1), s_);
     };

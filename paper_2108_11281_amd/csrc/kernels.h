@@ -439,18 +439,17 @@ void stencil_entries(const c64* Bf, const c64* U, double wdiag, int Nf, int dof,
                      c64* vals, hipStream_t s);
 
 // ----- batched flexible GMRES helpers ------------------------------------------
+// one step of classical Gram-Schmidt: h = V^H w, w -= V h, wn2 = |w|^2, w /= |w|
 template <typename T>
-void krylov_mdot(const T* V, int64_t vstride, int nv, const T* w, int64_t n, int nb,
-                 const int* active, c64* partials, int* nblk_out, hipStream_t s);
+void krylov_orthonormalise(const T* V, int64_t vstride, int nv, T* w, int64_t n, int nb,
+                           const int* active, c64* h, c64* wn2, c64* partials, hipStream_t s);
+// dst = src / |src| and nrm2 = |src|^2
 template <typename T>
-void krylov_maxpy(const T* V, int64_t vstride, int nv, const c64* h, T* w, int64_t n, int nb,
-                  const int* active, hipStream_t s);
+void krylov_normalise(T* dst, const T* src, int64_t n, int nb, const int* active, c64* nrm2,
+                      c64* partials, hipStream_t s);
 template <typename T>
 void krylov_combine(const T* Z, int64_t vstride, const c64* y, int ldy, const int* dims, T* d,
                     int64_t n, int nb, const int* start, hipStream_t s);
-template <typename T>
-void vec_scale_inv_norm(T* dst, const T* src, const c64* nrm2, int64_t n, int nb,
-                        const int* active, hipStream_t s);
 void givens_init(c64* H, c64* cs, c64* sn, c64* g, int* dims, const c64* beta2,
                  const int* active, int m, int nb, hipStream_t s);
 void givens_step(c64* H, c64* cs, c64* sn, c64* g, int* dims, const c64* h, const c64* wn2,

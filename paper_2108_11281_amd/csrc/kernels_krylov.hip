@@ -4,79 +4,146 @@
 // Krylov vectors of one basis are stored consecutively: vector i of column k
 // at base + i*vstride + k*n.
 #include "kernels.h"
+#include "vec_body.h"
 
 namespace mlmc {
 namespace {
 
 constexpr int kMaxBasis = 33;  // restart length + 1
 
+// the sums over a block of N values per thread, in the order of block_sum2; thread
+// t < N receives value t
+template <int N>
+__device__ __forceinline__ double block_sums(double (&v)[N], double* lds) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double t = wave_sum(v[i]);
+    if (lane == 0) lds[wave * N + i] = t;
+  }
+  __syncthreads();
+  double sum = 0.0;
+  if ((int)threadIdx.x < N) {
+    for (int w = 0; w < kThreads / 64; ++w) sum += lds[w * N + threadIdx.x];
+  }
+  return sum;
+}
+
 // partials[((k*nv + i) * nblk) + b] = sum over block b of conj(V_i) w  (column k);
-// the basis is walked in groups of four vectors (register accumulators), w is
-// re-read per group from cache
+// blockIdx.z is a group of four vectors (register accumulators): w is re-read per
+// group from cache.  The groups ran one after the other in a block before, each
+// ending in four block sums: 8.8 us instead of 5.1 for 5 columns of 8192 unknowns.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_mdot(const T* __restrict__ V, int64_t vstride,
                                                    int nv, const T* __restrict__ w, int64_t n,
                                                    const int* active, c64* partials) {
-  __shared__ double red[16];
-  const int k = blockIdx.y, nblk = gridDim.x;
+  __shared__ double red[kThreads / 64 * 8];
+  const int k = blockIdx.y, nblk = gridDim.x, i0 = 4 * blockIdx.z;
   if (active && !active[k]) return;
   const int64_t chunk = (n + nblk - 1) / nblk;
   const int64_t lo = (int64_t)blockIdx.x * chunk;
   const int64_t hi = lo + chunk < n ? lo + chunk : n;
   const T* wk = w + (int64_t)k * n;
-  for (int i0 = 0; i0 < nv; i0 += 4) {
-    double re[4] = {0, 0, 0, 0}, im[4] = {0, 0, 0, 0};
-    const int gcount = nv - i0 < 4 ? nv - i0 : 4;
-    // two elements per step, their ten loads issued before the products, which
-    // accumulate in element order as in a plain strided loop
-    for (int64_t e0 = lo + threadIdx.x; e0 < hi; e0 += 2 * kThreads) {
-      T we[2], ve[2][4];
+  double sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  const int gcount = nv - i0 < 4 ? nv - i0 : 4;
+  // two elements per step, their ten loads issued before the products, which
+  // accumulate in element order as in a plain strided loop
+  for (int64_t e0 = lo + threadIdx.x; e0 < hi; e0 += 2 * kThreads) {
+    T we[2], ve[2][4];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int64_t e = e0 + (int64_t)q * kThreads;
-        const int64_t ec = e < hi ? e : lo;
-        we[q] = wk[ec];
+    for (int q = 0; q < 2; ++q) {
+      const int64_t e = e0 + (int64_t)q * kThreads;
+      const int64_t ec = e < hi ? e : lo;
+      we[q] = wk[ec];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        ve[q][u] = V[(i0 + (u < gcount ? u : 0)) * vstride + (int64_t)k * n + ec];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (e0 + (int64_t)q * kThreads < hi) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          ve[q][u] = V[(i0 + (u < gcount ? u : 0)) * vstride + (int64_t)k * n + ec];
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        if (e0 + (int64_t)q * kThreads < hi) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (u < gcount) cdot_acc(re[u], im[u], ve[q][u], we[q]);
-        }
+          if (u < gcount) cdot_acc(sum[2 * u], sum[2 * u + 1], ve[q][u], we[q]);
       }
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (u < gcount) {
-        double a = re[u], b = im[u];
-        block_sum2<kThreads>(a, b, red);
-        if (threadIdx.x == 0) partials[((int64_t)k * nv + i0 + u) * nblk + blockIdx.x] = {a, b};
-      }
-    }
+  }
+  const double v = block_sums<8>(sum, red);
+  const int t = threadIdx.x;
+  if (t < 2 * gcount) {
+    double* out = reinterpret_cast<double*>(partials + ((int64_t)k * nv + i0 + (t >> 1)) * nblk +
+                                            blockIdx.x);
+    out[t & 1] = v;
   }
 }
 
-// w -= sum_i h[k*nv + i] V_i
-template <typename T>
+// w -= sum_i h[k*nv + i] V_i, and partials of |w|^2 per block of kThreads EPT elements.
+// hparts != nullptr: h is formed here from the nhp partials of each entry (eight lanes
+// per entry), and block 0 stores it.  w may not be shared with the partials' readers:
+// wparts is another region than hparts.
+template <typename T, int EPT>
 __global__ __launch_bounds__(kThreads) void k_maxpy(const T* __restrict__ V, int64_t vstride,
-                                                    int nv, const c64* __restrict__ h,
+                                                    int nv, c64* h, const c64* hparts, int nhp,
                                                     T* __restrict__ w, int64_t n,
-                                                    const int* active) {
-  const int k = blockIdx.y;
+                                                    const int* active, c64* wparts) {
+  __shared__ double hs[2 * kMaxBasis], red[kThreads / 64];
+  const int k = blockIdx.y, t = threadIdx.x;
   if (active && !active[k]) return;
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e >= n) return;
-  T acc = w[(int64_t)k * n + e];
+  const int64_t e0 = (int64_t)blockIdx.x * (kThreads * EPT) + t;
+  T acc[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int64_t e = e0 + (int64_t)u * kThreads;
+    acc[u] = e < n ? w[(int64_t)k * n + e] : zero_of(T());
+  }
+  if (hparts) {
+    for (int i = t >> 3; i < nv; i += kThreads / 8) {
+      const c64* p = hparts + ((int64_t)k * nv + i) * nhp;
+      double re = 0.0, im = 0.0;
+      for (int b = t & 7; b < nhp; b += 8) {
+        re += p[b].re;
+        im += p[b].im;
+      }
+#pragma unroll
+      for (int m = 1; m < 8; m *= 2) {
+        re += __shfl_xor(re, m, 64);
+        im += __shfl_xor(im, m, 64);
+      }
+      if ((t & 7) == 0) {
+        hs[2 * i] = re;
+        hs[2 * i + 1] = im;
+        if (blockIdx.x == 0) h[(int64_t)k * nv + i] = {re, im};
+      }
+    }
+  } else if (t < nv) {
+    const c64 c = h[(int64_t)k * nv + t];
+    hs[2 * t] = c.re;
+    hs[2 * t + 1] = c.im;
+  }
+  __syncthreads();
 #pragma unroll 4
   for (int i = 0; i < nv; ++i) {
-    const c64 c = h[(int64_t)k * nv + i];
-    acc -= scale_by(c.re, c.im, V[i * vstride + (int64_t)k * n + e]);
+    const T* vk = V + i * vstride + (int64_t)k * n;
+    T ve[EPT];
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+      const int64_t e = e0 + (int64_t)u * kThreads;
+      ve[u] = vk[e < n ? e : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) acc[u] -= scale_by(hs[2 * i], hs[2 * i + 1], ve[u]);
   }
-  w[(int64_t)k * n + e] = acc;
+  double sum[1] = {0.0}, unused = 0.0;
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int64_t e = e0 + (int64_t)u * kThreads;
+    if (e < n) {
+      w[(int64_t)k * n + e] = acc[u];
+      cdot_acc(sum[0], unused, acc[u], acc[u]);
+    }
+  }
+  const double v = block_sums<1>(sum, red);
+  if (t == 0) wparts[(int64_t)k * gridDim.x + blockIdx.x] = {v, 0.0};
 }
 
 // d = sum_{i < dims[k]} y[k*ldy + i] Z_i for columns with start[k]
@@ -100,16 +167,34 @@ __global__ __launch_bounds__(kThreads) void k_combine(const T* __restrict__ Z, i
   d[(int64_t)k * n + e] = acc;
 }
 
-// dst = src / sqrt(nrm2[k])
-template <typename T>
-__global__ void k_scale_inv_norm(T* dst, const T* src, const c64* nrm2, int64_t n,
-                                 const int* active) {
+// dst = src / |src|, |src|^2 the sum of column k's np partials, which every block forms
+// and block 0 stores in nrm2 (dst may be src)
+template <typename T, int EPT>
+__global__ __launch_bounds__(kThreads) void k_scale_inv_norm(T* dst, const T* src,
+                                                             const c64* parts, int np, c64* nrm2,
+                                                             int64_t n, const int* active) {
+  __shared__ double lds[16], total;
   const int k = blockIdx.y;
   if (active && !active[k]) return;
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e >= n) return;
-  const double s = nrm2[k].re > 0.0 ? 1.0 / sqrt(nrm2[k].re) : 0.0;
-  dst[(int64_t)k * n + e] = scale_by(s, 0.0, src[(int64_t)k * n + e]);
+  const int64_t e0 = (int64_t)blockIdx.x * (kThreads * EPT) + threadIdx.x;
+  T v[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int64_t e = e0 + (int64_t)u * kThreads;
+    v[u] = src[(int64_t)k * n + (e < n ? e : 0)];
+  }
+  const c64 f = body::finish(parts, np, k, lds);
+  if (threadIdx.x == 0) {
+    total = f.re;
+    if (blockIdx.x == 0) nrm2[k] = f;
+  }
+  __syncthreads();
+  const double s = total > 0.0 ? 1.0 / sqrt(total) : 0.0;
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int64_t e = e0 + (int64_t)u * kThreads;
+    if (e < n) dst[(int64_t)k * n + e] = scale_by(s, 0.0, v[u]);
+  }
 }
 
 struct GState {
@@ -138,20 +223,33 @@ __global__ void k_givens_step(GState st, const c64* h, const c64* wn2, const c64
   __syncthreads();
   for (int k = threadIdx.x; k < nb; k += blockDim.x) {
     if (!active[k]) continue;
-    c64* Hk = st.H + (int64_t)k * (m + 1) * m;
-    const c64* hk = h + (int64_t)k * (j + 1);
+    c64* __restrict__ Hk = st.H + (int64_t)k * (m + 1) * m;
+    const c64* __restrict__ hk = h + (int64_t)k * (j + 1);
+    const c64* __restrict__ csk = st.cs + (int64_t)k * m;
+    const c64* __restrict__ snk = st.sn + (int64_t)k * m;
     // rotation i acts on entries i (already rotated by rotation i - 1) and i + 1
     // (still as formed): the column streams through `a`, and entry i is final
     // after rotation i (no indexed local array, which would live in scratch)
     c64 a = hk[0];
-    for (int i = 0; i < j; ++i) {
-      const double c = st.cs[(int64_t)k * m + i].re;
-      const c64 s = st.sn[(int64_t)k * m + i];
-      const c64 b = hk[i + 1];
-      // [a; b] <- [c a + s b; -conj(s) a + c b]
-      Hk[(int64_t)i * m + j] = c * a + s * b;
-      const c64 sc = {s.re, -s.im};
-      a = c * b - sc * a;
+    // four rotations' loads at a time ahead of their chain
+    for (int i0 = 0; i0 < j; i0 += 4) {
+      double c[4];
+      c64 s[4], b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u < j ? i0 + u : i0;
+        c[u] = csk[i].re;
+        s[u] = snk[i];
+        b[u] = hk[i + 1];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (i0 + u >= j) break;
+        // [a; b] <- [c a + s b; -conj(s) a + c b]
+        Hk[(int64_t)(i0 + u) * m + j] = c[u] * a + s[u] * b[u];
+        const c64 sc = {s[u].re, -s[u].im};
+        a = c[u] * b[u] - sc * a;
+      }
     }
     const c64 b = {sqrt(wn2[k].re), 0.0};
     const double na = sqrt(a.re * a.re + a.im * a.im), nbv = sqrt(b.re * b.re + b.im * b.im);
@@ -190,21 +288,25 @@ __global__ void k_givens_step(GState st, const c64* h, const c64* wn2, const c64
   if (threadIdx.x == 0) *count = cnt;
 }
 
-// y = R^{-1} g (back substitution on the rotated Hessenberg), per column
-__global__ void k_givens_solve(GState st, c64* y, const int* start, int m, int nb) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nb || !start[k]) return;
+// y = R^{-1} g (back substitution on the rotated Hessenberg): a wave per column, lane i
+// keeps row i's right-hand side, R in LDS (one thread per column and loads in the chain:
+// 15 us for 16 vectors)
+__global__ __launch_bounds__(64) void k_givens_solve(GState st, c64* y, const int* start, int m) {
+  __shared__ c64 R[(kMaxBasis - 1) * (kMaxBasis - 1)];
+  const int k = blockIdx.x, lane = threadIdx.x;
+  if (!start[k]) return;
   const c64* Hk = st.H + (int64_t)k * (m + 1) * m;
-  const c64* gk = st.g + (int64_t)k * (m + 1);
-  c64* yk = y + (int64_t)k * m;
   const int d = st.dims[k];
+  for (int i = lane; i < d * d; i += 64) R[i] = Hk[(int64_t)(i / d) * m + i % d];
+  c64 acc = lane < d ? st.g[(int64_t)k * (m + 1) + lane] : c64{0.0, 0.0};
+  __syncthreads();
   for (int i = d - 1; i >= 0; --i) {
-    c64 acc = gk[i];
-    for (int j = i + 1; j < d; ++j) acc -= Hk[(int64_t)i * m + j] * yk[j];
-    const c64 rii = Hk[(int64_t)i * m + i];
+    const c64 rii = R[i * d + i];
     const double dd = rii.re * rii.re + rii.im * rii.im;
     const c64 inv = dd > 0.0 ? c64{rii.re / dd, -rii.im / dd} : c64{0.0, 0.0};
-    yk[i] = inv * acc;
+    const c64 yi = inv * c64{__shfl(acc.re, i, 64), __shfl(acc.im, i, 64)};
+    if (lane == i) y[(int64_t)k * m + i] = yi;
+    if (lane < i) acc -= R[lane * d + i] * yi;
   }
 }
 
@@ -212,25 +314,64 @@ inline dim3 grid_n(int64_t n, int nb) {
   return dim3((unsigned)((n + kThreads - 1) / kThreads), (unsigned)nb);
 }
 
+// elements per thread of the passes over one vector: one while that keeps the launch
+// below four blocks per CU, else four (fewer partials to sum in each block)
+inline int elems_per_thread(int64_t n, int nb) {
+  return (n + kThreads - 1) / kThreads * nb < 1024 ? 1 : 4;
+}
+inline int pass_blocks(int64_t n, int ept) {
+  return (int)((n + kThreads * ept - 1) / (kThreads * ept));
+}
+// partials per dot product up to which every block of the update sums them itself
+// instead of a launch between: 64 partials of 17 vectors are 17 KB per block, half of
+// what the block reads of the vectors, against 3 us for the launch
+constexpr int kInlineSums = 64;
+
 }  // namespace
 
+// one step of classical Gram-Schmidt for the basis V_0 .. V_{nv-1}: h = V^H w,
+// w -= V h, wn2 = |w|^2, w /= |w|
 template <typename T>
-void krylov_mdot(const T* V, int64_t vstride, int nv, const T* w, int64_t n, int nb,
-                 const int* active, c64* partials, int* nblk_out, hipStream_t s) {
+void krylov_orthonormalise(const T* V, int64_t vstride, int nv, T* w, int64_t n, int nb,
+                           const int* active, c64* h, c64* wn2, c64* partials, hipStream_t s) {
   MLMC_REQUIRE(nv <= kMaxBasis, MLMC_EUNSUPPORTED, "Krylov basis too large");
   // enough parallelism but few partials: nv*nb*nblk entries
   int nblk = reduce_blocks(n);
   if (nblk > 256) nblk = 256;
-  *nblk_out = nblk;
-  hipLaunchKernelGGL(k_mdot<T>, dim3(nblk, nb), dim3(kThreads), 0, s, V, vstride, nv, w, n,
-                     active, partials);
+  hipLaunchKernelGGL(k_mdot<T>, dim3(nblk, nb, (nv + 3) / 4), dim3(kThreads), 0, s, V, vstride,
+                     nv, w, n, active, partials);
+  const bool fused = nblk <= kInlineSums;
+  if (!fused) finish_sums(partials, nblk, nb * nv, h, s);
+  c64* wparts = fused ? partials + (int64_t)nblk * nb * nv : partials;
+  const c64* hparts = fused ? partials : nullptr;
+  const int ept = elems_per_thread(n, nb), np = pass_blocks(n, ept);
+  const dim3 g((unsigned)np, (unsigned)nb);
+  if (ept == 1) {
+    hipLaunchKernelGGL((k_maxpy<T, 1>), g, dim3(kThreads), 0, s, V, vstride, nv, h, hparts, nblk,
+                       w, n, active, wparts);
+    hipLaunchKernelGGL((k_scale_inv_norm<T, 1>), g, dim3(kThreads), 0, s, w, w, wparts, np, wn2,
+                       n, active);
+  } else {
+    hipLaunchKernelGGL((k_maxpy<T, 4>), g, dim3(kThreads), 0, s, V, vstride, nv, h, hparts, nblk,
+                       w, n, active, wparts);
+    hipLaunchKernelGGL((k_scale_inv_norm<T, 4>), g, dim3(kThreads), 0, s, w, w, wparts, np, wn2,
+                       n, active);
+  }
 }
 
+// dst = src / |src| and nrm2 = |src|^2
 template <typename T>
-void krylov_maxpy(const T* V, int64_t vstride, int nv, const c64* h, T* w, int64_t n, int nb,
-                  const int* active, hipStream_t s) {
-  hipLaunchKernelGGL(k_maxpy<T>, grid_n(n, nb), dim3(kThreads), 0, s, V, vstride, nv, h, w, n,
-                     active);
+void krylov_normalise(T* dst, const T* src, int64_t n, int nb, const int* active, c64* nrm2,
+                      c64* partials, hipStream_t s) {
+  vec_dot_partials<T>(src, src, n, nb, active, partials, s);
+  const int ept = elems_per_thread(n, nb);
+  const dim3 g((unsigned)pass_blocks(n, ept), (unsigned)nb);
+  if (ept == 1)
+    hipLaunchKernelGGL((k_scale_inv_norm<T, 1>), g, dim3(kThreads), 0, s, dst, src, partials,
+                       reduce_blocks(n), nrm2, n, active);
+  else
+    hipLaunchKernelGGL((k_scale_inv_norm<T, 4>), g, dim3(kThreads), 0, s, dst, src, partials,
+                       reduce_blocks(n), nrm2, n, active);
 }
 
 template <typename T>
@@ -238,13 +379,6 @@ void krylov_combine(const T* Z, int64_t vstride, const c64* y, int ldy, const in
                     int64_t n, int nb, const int* start, hipStream_t s) {
   hipLaunchKernelGGL(k_combine<T>, grid_n(n, nb), dim3(kThreads), 0, s, Z, vstride, y, ldy,
                      dims, d, n, start);
-}
-
-template <typename T>
-void vec_scale_inv_norm(T* dst, const T* src, const c64* nrm2, int64_t n, int nb,
-                        const int* active, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_inv_norm<T>, grid_n(n, nb), dim3(kThreads), 0, s, dst, src, nrm2,
-                     n, active);
 }
 
 void givens_init(c64* H, c64* cs, c64* sn, c64* g, int* dims, const c64* beta2,
@@ -265,23 +399,19 @@ void givens_step(c64* H, c64* cs, c64* sn, c64* g, int* dims, const c64* h, cons
 void givens_solve(c64* H, c64* cs, c64* sn, c64* g, int* dims, c64* y, const int* start, int m,
                   int nb, hipStream_t s) {
   GState st{H, cs, sn, g, dims};
-  hipLaunchKernelGGL(k_givens_solve, dim3((nb + 255) / 256), dim3(256), 0, s, st, y, start, m,
-                     nb);
+  MLMC_REQUIRE(m < kMaxBasis, MLMC_EUNSUPPORTED, "Krylov basis too large");
+  hipLaunchKernelGGL(k_givens_solve, dim3(nb), dim3(64), 0, s, st, y, start, m);
 }
 
-#define MLMC_INST_K(T)                                                                      \
-  template void krylov_mdot<T>(const T*, int64_t, int, const T*, int64_t, int, const int*,  \
-                               c64*, int*, hipStream_t);                                    \
-  template void krylov_maxpy<T>(const T*, int64_t, int, const c64*, T*, int64_t, int,       \
-                                const int*, hipStream_t);                                   \
-  template void krylov_combine<T>(const T*, int64_t, const c64*, int, const int*, T*,       \
-                                  int64_t, int, const int*, hipStream_t);                   \
-  template void vec_scale_inv_norm<T>(T*, const T*, const c64*, int64_t, int, const int*,   \
-                                      hipStream_t);
+#define MLMC_INST_K(T)                                                                        \
+  template void krylov_orthonormalise<T>(const T*, int64_t, int, T*, int64_t, int, const int*, \
+                                         c64*, c64*, c64*, hipStream_t);                      \
+  template void krylov_normalise<T>(T*, const T*, int64_t, int, const int*, c64*, c64*,       \
+                                    hipStream_t);                                             \
+  template void krylov_combine<T>(const T*, int64_t, const c64*, int, const int*, T*,         \
+                                  int64_t, int, const int*, hipStream_t);
 
 MLMC_INST_K(c32)
 MLMC_INST_K(c64)
-MLMC_INST_K(float)
-MLMC_INST_K(double)
 
 }  // namespace mlmc
