@@ -245,7 +245,7 @@ void Context::tune_bsr() {
   };
   for (int l = 2; l < Ls_; ++l) {
     Level& L = lv_[l - 1];
-    if (L.dof == 8) continue;  // one form, on the matrix cores
+    if (bsr8_ok(L.dof)) continue;  // one form, on the matrix cores
     if (opt_.precision == MLMC_FP32_IR64)
       L.bsr_form[0] = time_form(c32(), L, l, 1) < time_form(c32(), L, l, 0) ? 1 : 0;
     else
@@ -395,13 +395,34 @@ void Context::cvcycle(int l, const T* b, T* x, int nb, const int* act, bool top)
   const int pre = opt_.nu_pre, post = opt_.nu_post;
   if (pre == 0) vec_zero<T>(x, n, nb, act, s_);
   cop_smooth_n<T>(l, b, x, nb, act, pre, true, false);
-  T* res = w.vt[l - 1];
-  cop_residual<T, T, T>(l, b, x, res, nb, act, nullptr);
-  cop_restrict<T>(l, res, w.vb[l], nb, act);
+  // block levels whose coarse sites have as many unknowns: the residual of one colour is
+  // restricted as it is formed, and the correction is added where the first half sweep
+  // reads it
+  const Level& L = lv_[l - 1];
+  const bool fused = !L.wilson && bsr8_ok(L.dof) && lv_[l].dof == L.dof;
+  if (fused && pre > 0) {
+    bsr8_residual_restrict<T>(b, x, w.vb[l], blocks<T>(l), qmat<T>(l), L.side, L.dof, L.blk, nb,
+                              act, false, s_);
+  } else {
+    T* res = w.vt[l - 1];
+    cop_residual<T, T, T>(l, b, x, res, nb, act, nullptr);
+    cop_restrict<T>(l, res, w.vb[l], nb, act);
+  }
   cvcycle<T>(l + 1, w.vb[l], w.vx[l], nb, act);
   csecond_coarse_cycle<T>(l, w.vb[l], w.vx[l], nb, act, top);
-  cop_prolong<T>(l, w.vx[l], x, nb, act, omega_, 1.0);
-  cop_smooth_n<T>(l, b, x, nb, act, post, false, true);
+  if (fused && post > 0) {
+    const double es = (double)sizeof(T) * L.dof * (double)L.side * L.side;
+    const double bytes =
+        es * (3.0 + 1.0 / (L.blk * L.blk)) + 7.0 * L.dof * es / (double)nb;
+    timed<T>(l, kTimGs, bytes, act, nb, [&] {
+      bsr8_prolong_rbgs<T>(w.vx[l], qmat<T>(l), L.blk, omega_, b, x, blocks<T>(l), dinv<T>(l),
+                           L.side, L.dof, nb, act, true, s_);
+    });
+    cop_smooth_n<T>(l, b, x, nb, act, post - 1, false, true);
+  } else {
+    cop_prolong<T>(l, w.vx[l], x, nb, act, omega_, 1.0);
+    cop_smooth_n<T>(l, b, x, nb, act, post, false, true);
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -405,17 +405,27 @@ void bsr_residual(const Tb* b, const T* x, Tr* r, const T* B, int Nc, int dof, i
 template <typename T>
 void bsr_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int dof, int nb,
               const int* active, bool zero_init, bool reverse, int form, hipStream_t s);
-// the same with eight unknowns per (coarse) site, on the matrix cores; the
+// the same with four or eight unknowns per (coarse) site, on the matrix cores; the
 // restriction needs rows of blk dofF fine unknowns that are a multiple of eight
+inline bool bsr8_ok(int dof) { return dof == 4 || dof == 8; }
 int bsr8_residual_blocks(int Nc);
 template <typename T>
-void bsr8_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int nb, const int* active,
-               bool zero_init, bool reverse, hipStream_t s);
-template <typename T, typename Tr>
-void bsr8_residual(const T* b, const T* x, Tr* r, const T* B, int Nc, int nb, const int* active,
-                   c64* partials, hipStream_t s);
+void bsr8_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int dof, int nb,
+               const int* active, bool zero_init, bool reverse, hipStream_t s);
+// a sweep of x + omega P xc (Q: the aggregates' bases, dof columns), the sum not stored
 template <typename T>
-void agg8_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int nb,
+void bsr8_prolong_rbgs(const T* xc, const T* Q, int blk, double omega, const T* b, T* x,
+                       const T* B, const T* Dinv, int Nc, int dof, int nb, const int* active,
+                       bool reverse, hipStream_t s);
+template <typename T, typename Tr>
+void bsr8_residual(const T* b, const T* x, Tr* r, const T* B, int Nc, int dof, int nb,
+                   const int* active, c64* partials, hipStream_t s);
+// xc = P^H (b - A x) of an x that a sweep (reverse as there) has just left
+template <typename T>
+void bsr8_residual_restrict(const T* b, const T* x, T* xc, const T* B, const T* Q, int Nc, int dof,
+                            int blk, int nb, const int* active, bool reverse, hipStream_t s);
+template <typename T>
+void agg8_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int dofC, int nb,
                    const int* active, hipStream_t s);
 template <typename T>
 void agg_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int dofC, int nb,

@@ -858,7 +858,7 @@ inline dim3 grid_waves(int64_t items, int nb) {
 
 int wilson_residual_blocks(int N) { return (N * N + kThreads - 1) / kThreads; }
 int bsr_residual_blocks(int Nc, int dof) {
-  return dof == 8 ? bsr8_residual_blocks(Nc) : (Nc * Nc + kThreads - 1) / kThreads;
+  return bsr8_ok(dof) ? bsr8_residual_blocks(Nc) : (Nc * Nc + kThreads - 1) / kThreads;
 }
 
 template <typename Tb, typename T, typename Tr>
@@ -914,9 +914,9 @@ void wilson_rbgs_fused(const T* b, const T* xin, T* xout, const T* U, int N, dou
 template <typename Tb, typename T, typename Tr>
 void bsr_residual(const Tb* b, const T* x, Tr* r, const T* B, int Nc, int dof, int nb,
                   const int* active, c64* partials, int form, hipStream_t s) {
-  if (dof == 8) {
+  if (bsr8_ok(dof)) {
     static_assert(std::is_same<Tb, T>::value, "b and x have one type");
-    bsr8_residual<T, Tr>(b, x, r, B, Nc, nb, active, partials, s);
+    bsr8_residual<T, Tr>(b, x, r, B, Nc, dof, nb, active, partials, s);
     return;
   }
   // partial sums (the outer residual) come from the thread-per-site form
@@ -941,8 +941,8 @@ template <typename T>
 void bsr_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int dof, int nb,
               const int* active, bool zero_init, bool reverse, int form, hipStream_t s) {
   if (Nc & 1) throw Error(MLMC_EINVAL, "red-black block sweep needs an even lattice side");
-  if (dof == 8) {
-    bsr8_rbgs<T>(b, x, B, Dinv, Nc, nb, active, zero_init, reverse, s);
+  if (bsr8_ok(dof)) {
+    bsr8_rbgs<T>(b, x, B, Dinv, Nc, dof, nb, active, zero_init, reverse, s);
     return;
   }
   const int first = reverse ? 1 : 0;
@@ -967,8 +967,8 @@ template <typename T>
 void agg_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int dofC, int nb,
                   const int* active, hipStream_t s) {
   const int Nc = Nf / blk;
-  if (dofC == 8 && blk * dofF % 8 == 0) {
-    agg8_restrict<T>(x, xc, q, Nf, dofF, blk, nb, active, s);
+  if (bsr8_ok(dofC) && blk * dofF % 8 == 0) {
+    agg8_restrict<T>(x, xc, q, Nf, dofF, blk, dofC, nb, active, s);
     return;
   }
   const dim3 g((unsigned)(Nc * Nc), (unsigned)((nb + 63) / 64));

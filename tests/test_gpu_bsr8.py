@@ -1,5 +1,5 @@
-"""Levels with eight complex unknowns per site (matrix-core block kernels): operator,
-sweeps, restriction and reported residuals at the edges of the column groups, on
+"""Levels with four or eight complex unknowns per site (matrix-core block kernels):
+operator, sweeps, restriction, whole V-cycle steps and reported residuals at the edges of the column groups, on
 hierarchies whose restrictions take the matrix cores or (rows of four fine unknowns) not, against sparse matrices formed from the exported prolongations."""
 import ctypes
 
@@ -14,32 +14,34 @@ from workloads import gauge_field
 pytestmark = pytest.mark.gpu
 
 WIDTHS = [1, 7, 8, 9, 16, 17, 33]
-CASES = {  # kind, side, block: 8-dof levels of sides 8 and 2; 12, 6 (and 3); 6; 4
-    "wilson_4": ("wilson2d", 32, 4, 3),
-    "wilson_2": ("wilson2d", 24, 2, 4),
-    "gauge_8": ("gauge2d", 48, 8, 2),
-    "gauge_4": ("gauge2d", 16, 4, 3),
+CASES = {  # kind, side, block, levels, n_vec: block levels of sides 8, 2; 12, 6, 3; 6; 4; ..
+    "wilson_4": ("wilson2d", 32, 4, 3, 8),
+    "wilson_2": ("wilson2d", 24, 2, 4, 8),
+    "wilson_3": ("wilson2d", 36, 3, 3, 4),
+    "gauge_8": ("gauge2d", 48, 8, 2, 8),
+    "gauge_4": ("gauge2d", 32, 4, 3, 4),
+    "gauge_2": ("gauge2d", 16, 2, 3, 4),
 }
 
 
-def _problem(name, precision, **kw):
+def _problem(name, precision, pre=1, post=2, **kw):
     import paper_2108_11281_amd as m
-    kind, N, blk, L = CASES[name]
+    kind, N, blk, L, nv = CASES[name]
     th = gauge_field(N, sigma=0.3, seed=4)
     A = operators.wilson2d(N, th, 0.2) if kind == "wilson2d" else operators.gauge_laplacian(N, th, 0.1)
     est = m.TraceEstimator(kind, N, L, L, mass=0.2 if kind == "wilson2d" else 0.1, field=th,
-                           block=blk, n_vec=8, setup_sweeps=4, setup_seed=1, nb=max(WIDTHS),
-                           precision=precision, nu_pre=1, nu_post=2, **kw)
+                           block=blk, n_vec=nv, setup_sweeps=4, setup_seed=1, nb=max(WIDTHS),
+                           precision=precision, nu_pre=pre, nu_post=post, **kw)
     As, Ps, side, dof = [sp.csr_matrix(A)], [], N, 2 if kind == "wilson2d" else 1
     for l in range(L - 1):
-        q = est.export_prolongation(l + 1, 8)
+        q = est.export_prolongation(l + 1, nv)
         y, x = np.divmod(np.arange(side * side), side)
         agg = np.repeat((y // blk) * (side // blk) + x // blk, dof)
-        rows = np.repeat(np.arange(len(agg)), 8)
-        P = sp.csr_matrix((q.ravel(), (rows, (agg[:, None] * 8 + np.arange(8)).ravel())))
+        rows = np.repeat(np.arange(len(agg)), nv)
+        P = sp.csr_matrix((q.ravel(), (rows, (agg[:, None] * nv + np.arange(nv)).ravel())))
         As.append((P.conj().T @ As[-1] @ P).tocsr())
         Ps.append(P)
-        side, dof = side // blk, 8
+        side, dof = side // blk, nv
     return est, As, Ps
 
 
@@ -53,7 +55,7 @@ def test_kernels_at_every_width(name, precision):
     require_gpu()
     est, A, P = _problem(name, precision)
     rng = np.random.default_rng(7)
-    L = len(A)
+    L, nv = len(A), CASES[name][4]
     # FP64: sums of at most 128 products; FP32 sweeps: a few FP32 roundings per update
     tol = 1e-12
     for w in WIDTHS:
@@ -68,7 +70,7 @@ def test_kernels_at_every_width(name, precision):
             assert np.max(np.abs(Y - ref)) <= tol * np.max(np.abs(ref)), (w, l)
             if l < L - 1:
                 B = _random(rng, w, A[l].shape[0])
-                colour = np.repeat(hierarchy.site_coloring(int(np.sqrt(A[l].shape[0] // 8))), 8)
+                colour = np.repeat(hierarchy.site_coloring(int(np.sqrt(A[l].shape[0] // nv))), nv)
                 for reverse, zero in [(False, False), (True, False), (False, True)]:
                     Y = from_dev(est.smooth(l + 1, to_dev(B), None if zero else to_dev(X), 1,
                                             reverse, zero_start=zero), complex_=True)
@@ -99,4 +101,42 @@ def test_solve_of_an_8_dof_level(name, precision):
         # rounding of r: 1e-16 of A y against residuals above 1e-9
         assert np.all((ref > 1e-9) & (ref < 1e-1)), ref
         assert np.all(np.abs(rel - ref) <= 1e-6 * ref), w
+    est.close()
+
+
+def _vcycle(A, P, nv, l, b, pre, post, omega):
+    if l == len(A) - 1:
+        return np.linalg.solve(A[l].toarray(), b)
+    colour = np.repeat(hierarchy.site_coloring(int(np.sqrt(A[l].shape[0] // nv))), nv)
+    X = np.zeros_like(b)
+    for k in range(b.shape[1]):
+        X[:, k] = hierarchy.rbgs_sweeps(A[l], b[:, k], X[:, k], colour, pre, False)
+    X = X + omega * (P[l] @ _vcycle(A, P, nv, l + 1, P[l].conj().T @ (b - A[l] @ X), pre, post,
+                                    omega))
+    for k in range(b.shape[1]):
+        X[:, k] = hierarchy.rbgs_sweeps(A[l], b[:, k], X[:, k], colour, post, True)
+    return X
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir64"])
+@pytest.mark.parametrize("name,pre,post", [("wilson_4", 1, 1), ("wilson_4", 2, 0),
+                                           ("wilson_2", 1, 2), ("wilson_2", 0, 1),
+                                           ("gauge_4", 1, 1), ("gauge_2", 2, 2)])
+def test_one_step_is_the_vcycle(name, pre, post, precision):
+    require_gpu()
+    omega = 1.0 if pre == post else 1.2
+    est, A, P = _problem(name, precision, pre=pre, post=post, omega=omega, krylov_restart=1,
+                         solve_tol=0.9999)
+    rng = np.random.default_rng(11)
+    b = _random(rng, max(WIDTHS), A[1].shape[0]).T
+    z = _vcycle(A[1:], P[1:], CASES[name][4], 0, b, pre, post, omega)
+    # one minimal-residual step along M b
+    w = A[1] @ z
+    ref = (z * ((w.conj() * b).sum(0) / (w.conj() * w).sum(0))).T
+    for width in WIDTHS:
+        Y, _ = est.solve(2, to_dev(b.T[:width]))
+        err = np.max(np.abs(from_dev(Y, complex_=True) - ref[:width]), axis=1)
+        # FP64: rounding through the dense inverse; FP32: of some hundred operations
+        tol = 1e-10 if precision == "fp64" else 1e-4
+        assert np.all(err <= tol * np.max(np.abs(ref[:width]), axis=1)), (width, err)
     est.close()
