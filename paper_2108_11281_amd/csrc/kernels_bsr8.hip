@@ -193,7 +193,9 @@ struct Cols {
       col[q] = k < nb ? k : 0;
       any = any || on[q];
     }
-    live = __any(any);
+    // narrow batches don't wait for the flags before their loads: inactive columns are
+    // only not stored
+    live = CG == 1 || __any(any);
   }
 };
 
