@@ -100,8 +100,7 @@ struct Work {
   // the MFMA tile kernel's layout (dense_pack4), complex ones plain row-major
   T* ainvT = nullptr;
   int ld = 0;               // its leading dimension (n rounded up to 16, zero padded)
-  // complex operators: its real representation (2n x 2n, transposed) for the
-  // real MFMA product on interleaved vectors, in the tile kernel's layout
+  // complex operators: the inverse in the order of dense_complex_pack (n a multiple of 8)
   typename Traits<T>::real* ainvR = nullptr;
 };
 

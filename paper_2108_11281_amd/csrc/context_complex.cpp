@@ -192,21 +192,13 @@ void Context::build_wilson(const double* theta) {
     wc32_.ainvT = dalloc_n<c32>((int64_t)ns * ns);
     vec_convert<c32, c64>(wc64_.ainvT, wc32_.ainvT, (int64_t)ns * ns, 1, nullptr, s_);
   }
-  // the coarsest solve as a real MFMA product with the 2n x 2n real
-  // representation (interleaved complex vectors are real vectors of length 2n)
-  // (in the MFMA tile kernel's layout)
-  if (dense_mfma_layout<double>(2 * ns)) {
-    double* plain = dalloc_n<double>(4 * (int64_t)ns * ns);
-    dense_complex_to_real<c64, double>(wc64_.ainvT, plain, ns, s_);
-    wc64_.ainvR = dalloc_n<double>(4 * (int64_t)ns * ns);
-    dense_pack4<double>(plain, wc64_.ainvR, 2 * ns, s_);
-    dfree(plain);
+  // the coarsest solve on the matrix cores
+  if (ns % 8 == 0) {
+    wc64_.ainvR = dalloc_n<double>(dense_complex_elems(ns));
+    dense_complex_pack<c64>(wc64_.ainvT, wc64_.ainvR, ns, s_);
     if (opt_.precision == MLMC_FP32_IR64) {
-      float* plain32 = dalloc_n<float>(4 * (int64_t)ns * ns);
-      dense_complex_to_real<c32, float>(wc32_.ainvT, plain32, ns, s_);
-      wc32_.ainvR = dalloc_n<float>(4 * (int64_t)ns * ns);
-      dense_pack4<float>(plain32, wc32_.ainvR, 2 * ns, s_);
-      dfree(plain32);
+      wc32_.ainvR = dalloc_n<float>(dense_complex_elems(ns));
+      dense_complex_pack<c32>(wc32_.ainvT, wc32_.ainvR, ns, s_);
     }
   }
   if (L_ == Ls_) {
@@ -346,12 +338,10 @@ void Context::cop_prolong(int l, const T* ec, T* x, int nb, const int* act, doub
 // coarsest solve x = A_{L_s}^{-1} b of the complex hierarchy
 template <typename T>
 void Context::coarse_apply(const T* b, T* x, int nb, const int* act) {
-  using R = typename Traits<T>::real;
   Work<T>& w = work<T>();
   const int n = (int)lv_[Ls_ - 1].n;
   if (w.ainvR)
-    dense_apply<R>(w.ainvR, reinterpret_cast<const R*>(b), reinterpret_cast<R*>(x), 2 * n, nb,
-                   act, s_);
+    dense_complex_apply<T>(w.ainvR, b, x, n, nb, act, s_);
   else
     dense_apply<T>(w.ainvT, b, x, n, nb, act, s_);
 }

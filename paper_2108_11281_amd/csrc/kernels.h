@@ -189,10 +189,14 @@ constexpr bool dense_mfma_layout(int ld) {
 // consecutive rows j a lane reads for one column i are contiguous
 template <typename T>
 void dense_pack4(const T* At, T* out, int ld, hipStream_t s);
-// Mt (2n x 2n, real) = transposed real representation of the complex matrix
-// whose transpose is At, for dense_apply<R> on interleaved (re, im) vectors
-template <typename T, typename R>
-void dense_complex_to_real(const T* At, R* Mt, int n, hipStream_t s);
+// the same for a complex matrix (n a multiple of 8) in an order of its own
+// (dense_complex_elems reals), from the transposed matrix
+int64_t dense_complex_elems(int n);
+template <typename T>
+void dense_complex_pack(const T* At, typename Traits<T>::real* M, int n, hipStream_t s);
+template <typename T>
+void dense_complex_apply(const typename Traits<T>::real* M, const T* b, T* z, int n, int nb,
+                         const int* active, hipStream_t s);
 // out[j][i] = in[i][j] (n x n)
 template <typename T>
 void dense_transpose(const T* in, T* out, int n, hipStream_t s);

@@ -566,6 +566,114 @@ __global__ __launch_bounds__(kThreads) void k_agg8_restrict(const T* __restrict_
   }
 }
 
+// ---- dense complex products ------------------------------------------------------
+// z = M b per column for the coarsest inverse M (n a multiple of 8): a block per RT
+// tiles of 8 rows and 8 CG columns, its sixteen waves share the reduction index in ranges
+// of chunks of 16; the partial tiles are summed in wave order.  M comes in the order the
+// products need it (pack_dense): 16 bytes per lane and chunk in f32, 32 in f64.
+// The real representation this replaces has each entry twice: n = 2048, up to 16
+// complex64 columns 12.2 us (64 MB, at the memory's rate), 64 columns 91; now 8.2 (8 columns), 12.3 (16) and
+// 60 (64).
+constexpr int kDenseWaves = 16, kDenseBlock = kDenseWaves * 64;
+
+// the reduction index of lane group g, step s of chunk c
+template <typename R>
+__device__ __forceinline__ int dense_k(int c, int g, int s) {
+  return sizeof(R) == 4 ? 16 * c + 8 * (s >> 1) + 2 * g + (s & 1) : 16 * c + 4 * s + g;
+}
+
+template <typename T, int RT, int CG>
+__global__ __launch_bounds__(kDenseBlock) void k_dense_complex(const R_t<T>* __restrict__ M,
+                                                               const T* __restrict__ b,
+                                                               T* __restrict__ z, int n, int nb,
+                                                               const int* active) {
+  using R = R_t<T>;
+  using Acc = typename body::Mfma<R>::acc_t;
+  using V4 = R __attribute__((ext_vector_type(4)));
+  constexpr int NE = 2, W = sizeof(R) == 4 ? 2 : 1, NI = 4 / W;
+  __shared__ R part[kDenseWaves][NE][64];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const Place<R, 8> pl;
+  const Cols<CG> cols(blockIdx.y, pl.kc, nb, active);
+  if (!cols.live) return;  // the whole block
+  const int tiles = n >> 3, chunks = (n + 15) >> 4;
+  const int t0 = blockIdx.x * RT;
+  const R* br = reinterpret_cast<const R*>(b);
+  const int c0 = wave * chunks / kDenseWaves, c1 = (wave + 1) * chunks / kDenseWaves;
+  Acc acc[RT][CG];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int q = 0; q < CG; ++q) acc[t][q] = Acc{0, 0, 0, 0};
+  auto run = [&](auto un, int c) {
+    constexpr int U = decltype(un)::value;
+    V4 a[U][RT];
+    R v[U * CG * 4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int tile = t0 + t < tiles ? t0 + t : t0;
+        a[u][t] = *reinterpret_cast<const V4*>(M + (((int64_t)tile * chunks + c + u) * 64 + lane) * 4);
+      }
+    load_items<R, U * CG * NI, W, false>(
+        [&](int i) {
+          // beyond n (the last chunk of an odd multiple of 8) M is zero
+          const int k = dense_k<R>(c + i / (CG * NI), pl.g, W * (i % NI));
+          return br + (cols.col[i / NI % CG] * n + (k < n ? k : 0)) * 2;
+        },
+        pl.part, v);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int q = 0; q < CG; ++q)
+#pragma unroll
+          for (int t = 0; t < RT; ++t)
+            acc[t][q] = body::Mfma<R>::step(a[u][t][s], v[(u * CG + q) * 4 + s], acc[t][q]);
+  };
+  constexpr int U = RT * CG <= 2 ? 4 : RT * sizeof(R) < 16 ? 2 : 1;
+  int c = c0;
+  for (; c + U <= c1; c += U) run(std::integral_constant<int, U>(), c);
+  for (; c < c1; ++c) run(std::integral_constant<int, 1>(), c);
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int q = 0; q < CG; ++q) {
+      R h[NE];
+      combine<R, NE, false>(acc[t][q], pl.part, h);
+      if (t + q > 0) __syncthreads();
+#pragma unroll
+      for (int e = 0; e < NE; ++e) part[wave][e][lane] = h[e];
+      __syncthreads();
+      if (wave == (t * CG + q) % kDenseWaves) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          h[e] = part[0][e][lane];
+#pragma unroll
+          for (int w = 1; w < kDenseWaves; ++w) h[e] += part[w][e][lane];
+        }
+        store_unknowns<R, 8, R>(reinterpret_cast<R*>(z) + (cols.col[q] * n + 8 * (t0 + t)) * 2, pl,
+                                h, cols.on[q] && t0 + t < tiles);
+      }
+    }
+}
+
+// M from the transposed matrix At[j][i]
+template <typename T>
+__global__ void k_pack_dense(const T* __restrict__ At, R_t<T>* __restrict__ M, int n, int chunks) {
+  using R = R_t<T>;
+  const Place<R, 8> pl;
+  const int c = blockIdx.x, i = 8 * blockIdx.y + pl.ai;
+  for (int s = 0; s < 4; ++s) {
+    const int k = dense_k<R>(c, pl.g, s);
+    R v = 0;
+    if (k < n) v = pl.ap ? At[(int64_t)k * n + i].im : At[(int64_t)k * n + i].re;
+    M[(((int64_t)blockIdx.y * chunks + c) * 64 + threadIdx.x) * 4 + s] = v;
+  }
+}
+
 // right-hand sides per wave: 8 for batches up to 8 (the second group would be empty),
 // 16 beyond: the blocks, twice the size of a column's site vector times eight, are then
 // read half as often
@@ -594,7 +702,7 @@ int sites_per_wave(int Nc) {
   return spw;
 }
 
-constexpr int kOneLaunchWaves = 8192;  // eight per SIMD
+constexpr int kOneLaunchWaves = 2048;  // two per SIMD
 
 }  // namespace
 
@@ -611,9 +719,9 @@ void bsr8_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int dof, int
   with_form(dof, nb, [&](auto d, auto cg, int groups) {
     constexpr int CG = decltype(cg)::value, DOF = decltype(d)::value;
     // One launch from zero while its waves (a site and column group each) are all resident:
-    // 4.2 us instead of 2.3 + 3.4 on 16^2 sites and 5 complex128 columns.  Beyond, the
-    // neighbours' second reading of D^-1 and b costs more than a launch: 21 us on average
-    // over the levels of 64^2 and 16^2 sites with up to 64 columns, against 14 for two.
+    // 4.3 us instead of 2.3 + 3.4 on 16^2 sites and 5 complex128 columns.  Beyond, the
+    // neighbours' second reading of D^-1 and b costs more than a launch: 64^2 sites, 13
+    // complex64 columns 9.5 us against 3 + 4.6, 64 columns 53 against 35.
     if (zero_init && Nc * Nc * groups <= kOneLaunchWaves) {
       MLMC_LAUNCH((k_bsr8_gs<T, DOF, CG, kFromZero>), dim3((unsigned)((Nc * Nc + 3) / 4 * groups)),
                   dim3(kThreads), 0, s, b, x, B, Dinv, none, none, (R_t<T>)0, 1, Nc, first, 0, nb,
@@ -680,6 +788,38 @@ void agg8_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int
   });
 }
 
+int64_t dense_complex_elems(int n) { return (int64_t)(n / 8) * ((n + 15) / 16) * 256; }
+
+template <typename T>
+void dense_complex_pack(const T* At, typename Traits<T>::real* M, int n, hipStream_t s) {
+  const int chunks = (n + 15) / 16;
+  hipLaunchKernelGGL(k_pack_dense<T>, dim3(chunks, n / 8), dim3(64), 0, s, At, M, n, chunks);
+}
+
+template <typename T>
+void dense_complex_apply(const typename Traits<T>::real* M, const T* b, T* z, int n, int nb,
+                         const int* active, hipStream_t s) {
+  const unsigned tiles = (unsigned)(n / 8);
+  auto go = [&](auto rt, auto cg) {
+    constexpr int RT = decltype(rt)::value, CG = decltype(cg)::value;
+    hipLaunchKernelGGL((k_dense_complex<T, RT, CG>), dim3((tiles + RT - 1) / RT, (nb + 8 * CG - 1) / (8 * CG)),
+                       dim3(kDenseBlock), 0, s, M, b, z, n, nb, active);
+  };
+  std::integral_constant<int, 1> one;
+  std::integral_constant<int, 2> two;
+  std::integral_constant<int, 4> four;
+  // as many columns as there are per reading of M, up to 32; beyond, two row tiles per
+  // block halve the readings of the columns instead
+  if (nb <= 8)
+    go(one, one);
+  else if (nb <= 16)
+    go(one, two);
+  else if (nb <= 32 || sizeof(T) == sizeof(c64))  // two tiles spill in f64
+    go(one, four);
+  else if constexpr (sizeof(T) == sizeof(c32))
+    go(two, four);
+}
+
 #define BSR8_INST(T)                                                                            \
   template void bsr8_rbgs<T>(const T*, T*, const T*, const T*, int, int, int, const int*, bool,  \
                              bool, hipStream_t);                                                \
@@ -690,7 +830,10 @@ void agg8_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int
   template void bsr8_residual_restrict<T>(const T*, const T*, T*, const T*, const T*, int, int,  \
                                           int, int, const int*, bool, hipStream_t);             \
   template void agg8_restrict<T>(const T*, T*, const T*, int, int, int, int, int, const int*,    \
-                                 hipStream_t);
+                                 hipStream_t);                                                  \
+  template void dense_complex_pack<T>(const T*, Traits<T>::real*, int, hipStream_t);             \
+  template void dense_complex_apply<T>(const Traits<T>::real*, const T*, T*, int, int,           \
+                                       const int*, hipStream_t);
 BSR8_INST(c32)
 BSR8_INST(c64)
 template void bsr8_residual<c64, c32>(const c64*, const c64*, c32*, const c64*, int, int, int,

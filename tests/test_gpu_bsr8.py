@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 WIDTHS = [1, 7, 8, 9, 16, 17, 33]
 CASES = {  # kind, side, block, levels, n_vec: block levels of sides 8, 2; 12, 6, 3; 6; 4; ..
     "wilson_4": ("wilson2d", 32, 4, 3, 8),
+    "wilson_72": ("wilson2d", 48, 4, 3, 8),   # coarsest 72: half a chunk, an odd number of tiles
     "wilson_2": ("wilson2d", 24, 2, 4, 8),
     "wilson_3": ("wilson2d", 36, 3, 3, 4),
     "gauge_8": ("gauge2d", 48, 8, 2, 8),
@@ -30,7 +31,7 @@ def _problem(name, precision, pre=1, post=2, **kw):
     th = gauge_field(N, sigma=0.3, seed=4)
     A = operators.wilson2d(N, th, 0.2) if kind == "wilson2d" else operators.gauge_laplacian(N, th, 0.1)
     est = m.TraceEstimator(kind, N, L, L, mass=0.2 if kind == "wilson2d" else 0.1, field=th,
-                           block=blk, n_vec=nv, setup_sweeps=4, setup_seed=1, nb=max(WIDTHS),
+                           block=blk, n_vec=nv, setup_sweeps=4, setup_seed=1, nb=70,
                            precision=precision, nu_pre=pre, nu_post=post, **kw)
     As, Ps, side, dof = [sp.csr_matrix(A)], [], N, 2 if kind == "wilson2d" else 1
     for l in range(L - 1):
@@ -50,7 +51,7 @@ def _random(rng, w, n):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32_ir64"])
-@pytest.mark.parametrize("name", list(CASES))
+@pytest.mark.parametrize("name", [c for c in CASES if c != "wilson_72"])
 def test_kernels_at_every_width(name, precision):
     require_gpu()
     est, A, P = _problem(name, precision)
@@ -120,6 +121,7 @@ def _vcycle(A, P, nv, l, b, pre, post, omega):
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32_ir64"])
 @pytest.mark.parametrize("name,pre,post", [("wilson_4", 1, 1), ("wilson_4", 2, 0),
+                                           ("wilson_72", 1, 1),
                                            ("wilson_2", 1, 2), ("wilson_2", 0, 1),
                                            ("gauge_4", 1, 1), ("gauge_2", 2, 2)])
 def test_one_step_is_the_vcycle(name, pre, post, precision):
@@ -127,13 +129,14 @@ def test_one_step_is_the_vcycle(name, pre, post, precision):
     omega = 1.0 if pre == post else 1.2
     est, A, P = _problem(name, precision, pre=pre, post=post, omega=omega, krylov_restart=1,
                          solve_tol=0.9999)
+    widths = WIDTHS + ([64, 70] if name == "wilson_72" else [])
     rng = np.random.default_rng(11)
-    b = _random(rng, max(WIDTHS), A[1].shape[0]).T
+    b = _random(rng, max(widths), A[1].shape[0]).T
     z = _vcycle(A[1:], P[1:], CASES[name][4], 0, b, pre, post, omega)
     # one minimal-residual step along M b
     w = A[1] @ z
     ref = (z * ((w.conj() * b).sum(0) / (w.conj() * w).sum(0))).T
-    for width in WIDTHS:
+    for width in widths:
         Y, _ = est.solve(2, to_dev(b.T[:width]))
         err = np.max(np.abs(from_dev(Y, complex_=True) - ref[:width]), axis=1)
         # FP64: rounding through the dense inverse; FP32: of some hundred operations
