@@ -477,8 +477,8 @@ void Context::build_varcoef(const double* k) {
     L.kf64 = dalloc_n<double>(f);
     L.kl64 = dalloc_n<double>(fl);
     L.kl32 = dalloc_n<float>(fl);
-    L.dg64 = dalloc_n<double>(L.n);
-    L.dg32 = dalloc_n<float>(L.n);
+    L.dg64 = dalloc_n<double>(2 * L.n);
+    L.dg32 = dalloc_n<float>(2 * L.n);
   }
   MLMC_REQUIRE(lv_[Ls_ - 1].n <= 16384, MLMC_EINVAL, "coarsest solver level larger than 16384");
   MLMC_HIP(hipMemcpyAsync(lv_[0].kf64, k, sizeof(double) * (size_t)nf, hipMemcpyHostToDevice, s_));
@@ -706,7 +706,8 @@ void Context::kry_residual(int l, const T* b, const T* x, Tr* r, int nb, const i
 }
 
 template <typename T>
-void Context::op_res_restrict(int l, const T* b, const T* x, T* rc, int nb, const int* act) {
+void Context::op_res_restrict(int l, const T* b, const T* x, T* rc, int nb, const int* act,
+                              bool swept) {
   const Level& L = lv_[l - 1];
   if (csr_) {  // interleaved blocks, as the V-cycle
     T* r = work<T>().vt[l - 1];
@@ -717,8 +718,8 @@ void Context::op_res_restrict(int l, const T* b, const T* x, T* rc, int nb, cons
       rows_agg_sum<T>(r, rc, csr_agg<T>(l), nb, act, s_);
   }
   else if (varcoef_)
-    varcoef_restrict<T>(b, x, rc, vc_faces<T>(l), vc_diag<T>(l), L.side, true, nb, L.cols, act,
-                        s_);
+    varcoef_restrict<T>(b, x, rc, vc_faces<T>(l), vc_diag<T>(l), L.side, true, swept, nb, L.cols,
+                        act, s_);
   else
     poisson_residual_restrict<T>(b, x, rc, L.side, L.d, L.c, nb, act, s_);
 }
@@ -755,7 +756,7 @@ void Context::op_restrict(int l, const T* x, T* xc, int nb, const int* act) {
       throw Error(MLMC_ESTATE, "CSR building blocks are FP64");
     }
   } else if (varcoef_)
-    varcoef_restrict<T>(nullptr, x, xc, nullptr, nullptr, L.side, false, nb, L.cols, act, s_);
+    varcoef_restrict<T>(nullptr, x, xc, nullptr, nullptr, L.side, false, false, nb, L.cols, act, s_);
   else
     agg2d_restrict<T>(x, xc, L.side, nb, act, s_);
 }
@@ -823,7 +824,7 @@ void Context::vcycle_vc(int l, const T* b, T* x, int nb, const int* act, c64* rz
       op_restrict<T>(l, b, bc, nb, act);
     else
       timed<T>(l, kTimResRestrict, en * (2.0 + 0.125 + 4.0 / (double)nb), act, nb,
-               [&] { op_res_restrict<T>(l, b, u, bc, nb, act); });
+               [&] { op_res_restrict<T>(l, b, u, bc, nb, act, true); });
     vcycle_vc<T>(l + 1, bc, ec, nb, act, nullptr);
     second_coarse_cycle<T>(l, bc, ec, nb, act, top);
     if (post == 0) {
@@ -861,7 +862,7 @@ void Context::vcycle_vc(int l, const T* b, T* x, int nb, const int* act, c64* rz
       op_restrict<T>(l, b, bc, nb, act);
     else
       timed<T>(l, kTimResRestrict, en * (2.0 + 0.125 + 4.0 / (double)nb), act, nb,
-               [&] { op_res_restrict<T>(l, b, x, bc, nb, act); });
+               [&] { op_res_restrict<T>(l, b, x, bc, nb, act, true); });
     vcycle_vc<T>(l + 1, bc, ec, nb, act, nullptr);
     second_coarse_cycle<T>(l, bc, ec, nb, act, top);
     if (post == 0 || pre == 0) {

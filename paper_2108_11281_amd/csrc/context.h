@@ -278,7 +278,7 @@ class Context {
   template <typename T> void op_apply(int l, const T* x, T* y, int nb, const int* act,
                                       c64* partials);
   template <typename T> void op_res_restrict(int l, const T* b, const T* x, T* rc, int nb,
-                                             const int* act);
+                                             const int* act, bool swept = false);
   template <typename T> void op_prolong(int l, const T* ec, T* x, int nb, const int* act,
                                         double beta);
   template <typename T> void op_restrict(int l, const T* x, T* xc, int nb, const int* act);

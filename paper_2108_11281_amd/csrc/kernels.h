@@ -333,11 +333,12 @@ void varcoef_rbgs_march(const T* xin, const T* b, T* xout, const T* ec, double o
                         int N, int nb, int cols, const int* active, bool reverse,
                         hipStream_t s);
 // xc = R (b - A x) when residual, else xc = R x; R the orthonormal 2x2x2
-// aggregation (entries 1/sqrt(8))
+// aggregation (entries 1/sqrt(8)).  swept: x has just left a forward sweep (its
+// second colour's residual is zero and not formed)
 template <typename T>
 void varcoef_restrict(const T* b, const T* x, T* xc, const typename Traits<T>::real* kl,
-                      const typename Traits<T>::real* dg, int N, bool residual, int nb, int cols,
-                      const int* active, hipStream_t s);
+                      const typename Traits<T>::real* dg, int N, bool residual, bool swept, int nb,
+                      int cols, const int* active, hipStream_t s);
 // x = beta x + omega P ec
 template <typename T>
 void varcoef_prolong(const T* ec, T* x, int N, double omega, double beta, int nb,
@@ -350,7 +351,8 @@ void varcoef_update_apply(const T* p_old, const T* z, const c64* beta, T* p_new,
                           const int* active, c64* partials, hipStream_t s);
 // Galerkin faces of the next level: kc = 1/8 (sum of the 4 fine faces covered)
 void varcoef_coarsen(const double* kf, double* kc, int N, hipStream_t s);
-// diagonal and cell-major couplings (FP64 and FP32) of one level
+// diagonal, followed by its reciprocals, and cell-major couplings (FP64 and FP32) of
+// one level
 void varcoef_diag(const double* k, double shift, int N, double* d64, float* d32, double* kl64,
                   float* kl32, hipStream_t s);
 // left half of aug (n x 2n row-major, n = N^3) = the dense operator

@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kGroupThreads) void kg_stage(const GStage* __restri
         g.in, g.b, g.out, g.ec, g.ws, g.kl, g.dg, g.N, g.sz, g.nb, g.act, nullptr, bx, by, bz,
         lds);
   } else if constexpr (KIND == kGsResRestrict) {
-    vcb::vc_res_restrict<float, kGroupRrCols, kGroupThreads>(g.b, g.in, g.out, g.kl, g.dg, g.N,
+    vcb::vc_res_restrict<float, kGroupRrCols, kGroupThreads, true>(g.b, g.in, g.out, g.kl, g.dg, g.N,
                                                              g.nb, g.act, nullptr, item % g.gx,
                                                              item / g.gx, tid);
   } else if constexpr (KIND == kGsDense) {
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kGroupThreads) void kg_vcycle_units(const GStage* _
       case kGsResRestrict:
         // the pair is one column group of the restriction (kGroupRrCols == 2)
         for (int bx = 0; bx < g.gx; ++bx)
-          vcb::vc_res_restrict<float, kGroupRrCols, kGroupThreads>(
+          vcb::vc_res_restrict<float, kGroupRrCols, kGroupThreads, true>(
               g.b, g.in, g.out, g.kl, g.dg, g.N, g.nb, g.act, nullptr, bx, pair, tid);
         break;
       case kGsDense: {

@@ -206,7 +206,8 @@ __global__ void k_vc_coarsen(const double* __restrict__ kf, double* __restrict__
   }
 }
 
-// diagonal (shift + the six faces of each cell) and the cell-major couplings
+// diagonal (shift + the six faces of each cell), its reciprocals behind it, and the
+// cell-major couplings
 // kl[d][i] (boundary zero, each array padded with N^2 zeros), FP64 and FP32
 __global__ void k_vc_diag(const double* __restrict__ k, double shift, int N, double* d64,
                           float* d32, double* kl64, float* kl32) {
@@ -218,6 +219,8 @@ __global__ void k_vc_diag(const double* __restrict__ k, double shift, int N, dou
                      k[face_idx(2, c.y, c.x, c.z, N)] + k[face_idx(2, c.y, c.x, c.z + 1, N)];
     d64[i] = s;
     d32[i] = (float)s;
+    d64[n + i] = 1.0 / s;
+    d32[n + i] = 1.0f / (float)s;
   }
   const int64_t stride = (int64_t)n + NN;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < 3 * stride;
@@ -265,7 +268,7 @@ inline dim3 grid_cells(int64_t n, int nb) {
 // rows of two cells: a thread per coarse cell (lanes along coarse x, so each
 // row is a 2-element load contiguous over the wave), COLS right-hand sides
 // sharing the couplings; neighbours outside the grid read as zero
-template <typename T, int COLS>
+template <typename T, int COLS, bool HALF>
 __global__ __launch_bounds__(kThreads) void k_vc_res_restrict(const T* __restrict__ b,
                                                               const T* __restrict__ x,
                                                               T* __restrict__ rc,
@@ -273,7 +276,7 @@ __global__ __launch_bounds__(kThreads) void k_vc_res_restrict(const T* __restric
                                                               const R_t<T>* __restrict__ dg,
                                                               int N, int nb, const int* active,
                                                               int* tlog) {
-  vc_res_restrict<T, COLS, kThreads>(b, x, rc, kl, dg, N, nb, active, tlog, blockIdx.x,
+  vc_res_restrict<T, COLS, kThreads, HALF>(b, x, rc, kl, dg, N, nb, active, tlog, blockIdx.x,
                                      blockIdx.y, threadIdx.x);
 }
 
@@ -385,12 +388,15 @@ void varcoef_rbgs_march(const T* xin, const T* b, T* xout, const T* ec, double o
 
 template <typename T>
 void varcoef_restrict(const T* b, const T* x, T* xc, const typename Traits<T>::real* kl,
-                      const typename Traits<T>::real* dg, int N, bool residual, int nb, int cols,
-                      const int* active, hipStream_t s) {
+                      const typename Traits<T>::real* dg, int N, bool residual, bool swept, int nb,
+                      int cols, const int* active, hipStream_t s) {
   const int64_t nc = (int64_t)(N / 2) * (N / 2) * (N / 2);
   const dim3 g((unsigned)((nc + kThreads - 1) / kThreads), (unsigned)((nb + cols - 1) / cols));
-  if (residual) {
-    VC_COLS_DISPATCH(cols, MLMC_LAUNCH((k_vc_res_restrict<T, C>), g, dim3(kThreads), 0, s, b, x,
+  if (residual && swept) {
+    VC_COLS_DISPATCH(cols, MLMC_LAUNCH((k_vc_res_restrict<T, C, true>), g, dim3(kThreads), 0, s, b,
+                                       x, xc, kl, dg, N, nb, active, timing_log()));
+  } else if (residual) {
+    VC_COLS_DISPATCH(cols, MLMC_LAUNCH((k_vc_res_restrict<T, C, false>), g, dim3(kThreads), 0, s, b, x,
                                        xc, kl, dg, N, nb, active, timing_log()));
   } else {
     VC_COLS_DISPATCH(cols, MLMC_LAUNCH((k_vc_restrict<T, C>), g, dim3(kThreads), 0, s, b, x, xc,
@@ -439,7 +445,7 @@ void varcoef_dense(const double* k, const double* diag, int N, double* aug, hipS
                                       const T*, int, int, int, const int*, bool,             \
                                       hipStream_t);                                          \
   template void varcoef_restrict<T>(const T*, const T*, T*, const T*, const T*, int, bool,    \
-                                    int, int, const int*, hipStream_t);                      \
+                                    bool, int, int, const int*, hipStream_t);                \
   template void varcoef_prolong<T>(const T*, T*, int, double, double, int, const int*,        \
                                    hipStream_t);                                             \
   template void varcoef_update_apply<T>(const T*, const T*, const c64*, T*, T*, const T*,    \

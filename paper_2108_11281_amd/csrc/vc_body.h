@@ -159,8 +159,10 @@ __device__ __forceinline__ void vc_update_apply(const T* __restrict__ p_old,
 
 // rc = R (b - A x) for 2x2x2 aggregates (1/sqrt(8)): coarse cell
 // I = bx * NT + tid (a thread per coarse cell, no barrier), COLS columns from
-// by * COLS
-template <typename T, int COLS, int NT>
+// by * COLS.  HALF: x has just left a forward sweep, so the residual is zero on the
+// second colour and only the first colour's four cells are formed (96^3, 32 FP32
+// columns: 97 us instead of 109, 56^3 33 instead of 41)
+template <typename T, int COLS, int NT, bool HALF>
 __device__ __forceinline__ void vc_res_restrict(const T* __restrict__ b, const T* __restrict__ x,
                                                 T* __restrict__ rc,
                                                 const R_t<T>* __restrict__ kl,
@@ -207,6 +209,22 @@ __device__ __forceinline__ void vc_res_restrict(const T* __restrict__ b, const T
         if (!col_on(active, col, nb)) continue;  // uniform over the block
         const T* xc = x + (int64_t)col * n;
         const T* bc = b + (int64_t)col * n;
+        if constexpr (HALF) {
+          if ((dy + dz) % 2 == 0) {
+            const T xl = xl_in ? xc[i - 1] : zero, yl = yl_in ? xc[i - N] : zero,
+                    yu = yu_in ? xc[i + N] : zero, zl = zl_in ? xc[i - NN] : zero,
+                    zu = zu_in ? xc[i + NN] : zero;
+            acc[q] += bc[i] - (d0 * xc[i] - (kx0 * xl + kx1 * xc[i + 1] + ky0 * yl + kyu0 * yu +
+                                             kz0 * zl + kzu0 * zu));
+          } else {
+            const T xr = xr_in ? xc[i + 2] : zero, yl = yl_in ? xc[i - N + 1] : zero,
+                    yu = yu_in ? xc[i + N + 1] : zero, zl = zl_in ? xc[i - NN + 1] : zero,
+                    zu = zu_in ? xc[i + NN + 1] : zero;
+            acc[q] += bc[i + 1] - (d1 * xc[i + 1] - (kx1 * xc[i] + kx2 * xr + ky1 * yl +
+                                                     kyu1 * yu + kz1 * zl + kzu1 * zu));
+          }
+          continue;
+        }
         const T c0 = xc[i], c1 = xc[i + 1];
         const T xl = xl_in ? xc[i - 1] : zero, xr = xr_in ? xc[i + 2] : zero;
         const T yl0 = yl_in ? xc[i - N] : zero, yl1 = yl_in ? xc[i - N + 1] : zero;
@@ -245,6 +263,10 @@ __device__ __forceinline__ void vc_res_restrict(const T* __restrict__ b, const T
 // also load the row beyond them.  Cells outside the grid read as zero, so no
 // coupling ever multiplies a value that was not written.
 // ---------------------------------------------------------------------------
+// Bound by vector instructions: with register moves, 64-bit addresses and two divisions
+// per step 96^3 cells and 32 FP32 columns took 131 us from zero and 181 us after a coarse
+// correction; with the ring of slots, plane pointers in scalar registers and stored
+// reciprocals 105 and 147.
 // couplings of a row pair on one plane; d0, d1 hold 1 / diagonal
 template <typename R>
 struct PlaneK {
@@ -297,17 +319,27 @@ __device__ __forceinline__ void vc_march(const T* __restrict__ xin, const T* __r
   const int x0 = 2 * pl;
   const bool xok = x0 < N;
   const bool row_in = y >= 0 && y < N;
-  const bool cell_ok = row_in && xok;
   const bool edge = (r == 0) || (r == RW - 1);
   const int ye = (r == 0) ? y - 1 : y + 1;  // the outermost rows' outer neighbour row
-  const bool eok = edge && ye >= 0 && ye < N && xok;
+  const bool eok = edge && ye >= 0 && ye < N;
   const bool inner = r >= 1 && r <= TY;
-  const bool owner = inner && row_in;
+  const bool store = inner && row_in && xok;
+  const bool has_r = x0 + 2 < N;
   const int NN = N * N;
   const int64_t n = (int64_t)NN * N, stride = n + NN;
   const int Nc = N >> 1;
   const T zero = zero_of(T());
 
+  // Per-lane byte offsets within a plane, from uniform plane pointers: the loads take
+  // them as they are.  Lanes outside the grid load the nearest cell inside; their rows
+  // publish zeros below, their columns reach no other lane, and neither is stored.
+  auto clampi = [](int v, int hi) { return v < 0 ? 0 : (v > hi ? hi : v); };
+  const int yc = clampi(y, N - 1), yec = clampi(ye, N - 1), xcl = xok ? x0 : 0;
+  const uint32_t at = (uint32_t)(yc * N + xcl), ate = (uint32_t)(yec * N + xcl);
+  const uint32_t offx = at * sizeof(T), offe = ate * sizeof(T), offk = at * sizeof(R),
+                 offku = (at + N) * sizeof(R);
+  const uint32_t offc = (uint32_t)((yc >> 1) * Nc + (xcl >> 1)) * sizeof(T),
+                 offce = (uint32_t)((yec >> 1) * Nc + (xcl >> 1)) * sizeof(T);
   // column base pointers (inactive columns point at column 0 and are never stored)
   const T* xc[COLS];
   const T* bc[COLS];
@@ -321,170 +353,154 @@ __device__ __forceinline__ void vc_march(const T* __restrict__ xin, const T* __r
     ecc[c] = ec + (HE ? col * (int64_t)Nc * Nc * Nc : 0);
     xo[c] = xout + col * n;
   }
-  auto ld2 = [&](const T* base, int64_t i, bool ok, T& v0, T& v1) {
-    v0 = ok ? base[i] : zero;
-    v1 = ok ? base[i + 1] : zero;
-  };
-  auto ldk2 = [&](const R* base, int64_t i, bool ok, R& v0, R& v1) {
-    v0 = ok ? base[i] : (R)0;
-    v1 = ok ? base[i + 1] : (R)0;
-  };
-  // x_in of row yy, plane z (with the folded correction)
-  auto load_x = [&](int c, int yy, int z, bool ok, T& v0, T& v1) {
-    v0 = zero;
-    v1 = zero;
-    const int64_t i = ((int64_t)z * N + yy) * N + x0;
-    if constexpr (HX) ld2(xc[c], i, ok, v0, v1);
-    if constexpr (HE) {
-      const T e = ok ? ecc[c][((int64_t)(z >> 1) * Nc + (yy >> 1)) * Nc + (x0 >> 1)] : zero;
-      v0 += ws * e;
-      v1 += ws * e;
-    }
-  };
-  auto load_k = [&](int z, bool ok, PlaneK<R>& k) {
-    const int64_t i = ((int64_t)z * N + y) * N + x0;
-    ldk2(kl, i, ok, k.kx0, k.kx1);
-    ldk2(kl + stride, i, ok, k.kyl0, k.kyl1);
-    ldk2(kl + stride, i + N, ok, k.kyu0, k.kyu1);
-    ldk2(kl + 2 * stride, i, ok, k.kz0, k.kz1);
-    ldk2(dg, i, ok, k.d0, k.d1);
-    // reciprocals of the diagonal, shared by the columns (1 outside the grid)
-    k.d0 = ok ? (R)1 / k.d0 : (R)1;
-    k.d1 = ok ? (R)1 / k.d1 : (R)1;
+  auto ld2 = [](const auto* base, uint32_t off, auto& v0, auto& v1) {
+    const auto* q = reinterpret_cast<decltype(base)>(reinterpret_cast<const char*>(base) + off);
+    v0 = q[0];
+    v1 = q[1];
   };
 
-  // planes p+2 (m, loads in flight), p+1 (n), p (c), p-1 (p), p-2 (q) of the
-  // wave's row, per column
-  T Xm0[COLS], Xm1[COLS], Xn0[COLS], Xn1[COLS], Xc0[COLS], Xc1[COLS], Xp0[COLS], Xp1[COLS],
-      Xq0[COLS], Xq1[COLS];
-  // edge waves: outer row, planes p+2, p+1, p
-  T Em0[COLS], Em1[COLS], En0[COLS], En1[COLS], Ec0[COLS], Ec1[COLS];
-  T Bm0[COLS], Bm1[COLS], Bn0[COLS], Bn1[COLS], Bc0[COLS], Bc1[COLS], Bp0[COLS], Bp1[COLS];
-  PlaneK<R> Km, Kn, Kc, Kp;
+  // planes p+2 (loads in flight), p+1, p, p-1 in a ring of four slots that the loop
+  // below unrolls, so that a step moves no registers: x_in / x, right-hand side,
+  // couplings; on the edge rows the outer row.  Xq: x of plane p-2.
+  T X0[4][COLS], X1[4][COLS], E[4][COLS], B0[4][COLS], B1[4][COLS];
+  T Xq0[COLS], Xq1[COLS];
+  PlaneK<R> K[4];
+  auto clear = [&](int s) {
 #pragma unroll
-  for (int c = 0; c < COLS; ++c) {
-    Xn0[c] = Xn1[c] = Xc0[c] = Xc1[c] = Xp0[c] = Xp1[c] = Xq0[c] = Xq1[c] = zero;
-    En0[c] = En1[c] = Ec0[c] = Ec1[c] = zero;
-    Bn0[c] = Bn1[c] = Bc0[c] = Bc1[c] = Bp0[c] = Bp1[c] = zero;
-  }
-  Kn = PlaneK<R>{};
-  Kc = PlaneK<R>{};
-  Kp = PlaneK<R>{};
-  auto load_plane = [&](int z) {
-    const bool zok = z < N;
+    for (int c = 0; c < COLS; ++c)
+      X0[s][c] = X1[s][c] = E[s][c] = B0[s][c] = B1[s][c] = zero;
+    K[s] = PlaneK<R>{};
+  };
+  auto load_plane = [&](int s, int z) {
+    if (z >= N) {  // uniform
+      clear(s);
+      return;
+    }
+    int64_t zo = (int64_t)z * NN, zc = (int64_t)(z >> 1) * Nc * Nc;
+    // not to be turned into one running 64-bit pointer per lane and array
+    asm volatile("" : "+s"(zo), "+s"(zc));
+    const int ez = (F + ybase + z) & 1;  // the element of the outer row that plane z's update reads
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
-      load_x(c, y, z, cell_ok && zok, Xm0[c], Xm1[c]);
-      if (edge) load_x(c, ye, z, eok && zok, Em0[c], Em1[c]);
-      else Em0[c] = Em1[c] = zero;
-      const int64_t i = ((int64_t)z * N + y) * N + x0;
-      ld2(bc[c], i, cell_ok && zok, Bm0[c], Bm1[c]);
+      X0[s][c] = X1[s][c] = E[s][c] = zero;
+      if constexpr (HX) {
+        ld2(xc[c] + zo, offx, X0[s][c], X1[s][c]);
+        E[s][c] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(xc[c] + zo + ez) + offe);
+      }
+      ld2(bc[c] + zo, offx, B0[s][c], B1[s][c]);
+      if constexpr (HE) {
+        const char* ep = reinterpret_cast<const char*>(ecc[c] + zc);
+        const T e = *reinterpret_cast<const T*>(ep + offc);
+        const T eo = *reinterpret_cast<const T*>(ep + offce);
+        X0[s][c] += ws * e;
+        X1[s][c] += ws * e;
+        E[s][c] += ws * eo;
+      }
     }
-    load_k(z, cell_ok && zok, Km);
+    PlaneK<R>& k = K[s];
+    ld2(kl + zo, offk, k.kx0, k.kx1);
+    ld2(kl + stride + zo, offk, k.kyl0, k.kyl1);
+    ld2(kl + stride + zo, offku, k.kyu0, k.kyu1);
+    ld2(kl + 2 * stride + zo, offk, k.kz0, k.kz1);
+    ld2(dg + n + zo, offk, k.d0, k.d1);  // the diagonal's reciprocals lie behind it
   };
-  auto shift = [&]() {
-#pragma unroll
-    for (int c = 0; c < COLS; ++c) {
-      Xq0[c] = Xp0[c]; Xq1[c] = Xp1[c];
-      Xp0[c] = Xc0[c]; Xp1[c] = Xc1[c];
-      Xc0[c] = Xn0[c]; Xc1[c] = Xn1[c];
-      Xn0[c] = Xm0[c]; Xn1[c] = Xm1[c];
-      Ec0[c] = En0[c]; Ec1[c] = En1[c];
-      En0[c] = Em0[c]; En1[c] = Em1[c];
-      Bp0[c] = Bc0[c]; Bp1[c] = Bc1[c];
-      Bc0[c] = Bn0[c]; Bc1[c] = Bn1[c];
-      Bn0[c] = Bm0[c]; Bn1[c] = Bm1[c];
-    }
-    Kp = Kc;
-    Kc = Kn;
-    Kn = Km;
-  };
+
   // this workgroup's planes zs .. ze-1 (segments of SZ): the march starts one
   // plane early (first colour only there) and reads one plane more below it
   const int zs = bz * SZ;
   const int ze = zs + SZ < N ? zs + SZ : N;
   const int p0 = zs > 0 ? zs - 1 : 0;
   const int pe = ze < N ? ze : N;
-  // prologue: planes p0-1 (zero below the grid), p0 and p0+1 into the c, n and
-  // m slots, so that the first shift of the loop sees p0-1, p0, p0+1
-  if (p0 >= 1) {
-    load_plane(p0 - 1);
-    shift();
-  }
-  load_plane(p0);
-  shift();
-  load_plane(p0 + 1);
-  for (int p = p0; p <= pe; ++p) {
-    // shift planes: p+1 moves into the "next" slot; plane p+2 is loaded a step
-    // ahead of its first use
-    shift();
-    load_plane(p + 2);  // zeros beyond the last plane
-    // element of the pair updated in this step (first colour on plane p,
-    // second colour on plane p-1): e = (F + y + p) & 1, uniform per wave
-    const int e = (F + ybase + p) & 1;
-    const int buf = p & 1;
-    // publish: this row's second-colour cell of plane p (x_in, element 1-e) and
-    // first-colour cell of plane p-1 (updated last step, element 1-e)
+  // plane z is in slot (z - p0) & 3
 #pragma unroll
-    for (int c = 0; c < COLS; ++c) {
-      xa[buf][r][c][pl] = e ? Xc0[c] : Xc1[c];
-      xb[buf][r][c][pl] = e ? Xp0[c] : Xp1[c];
-    }
-    __syncthreads();
-    // first colour on plane p, element e (all rows of the workgroup)
-    if (p < N) {
+  for (int c = 0; c < COLS; ++c) Xq0[c] = Xq1[c] = zero;
+  if (p0 >= 1)
+    load_plane(3, p0 - 1);
+  else
+    clear(3);
+  clear(2);
+  load_plane(0, p0);
+  load_plane(1, p0 + 1);
+  for (int pb = p0; pb <= pe; pb += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int p = pb + u;
+      if (p > pe) break;  // uniform
+      const int sm = (u + 2) & 3, sn = (u + 1) & 3, sc = u, sp = (u + 3) & 3;
+      // plane p-2 leaves its slot to plane p+2, loaded a step ahead of its first use
 #pragma unroll
       for (int c = 0; c < COLS; ++c) {
-        const T alo = xa[buf][r > 0 ? r - 1 : 0][c][pl];
-        const T ahi = xa[buf][r < RW - 1 ? r + 1 : RW - 1][c][pl];
-        const T ev = e ? Ec1[c] : Ec0[c];
-        const T ylo = r > 0 ? alo : ev;
-        const T yhi = r < RW - 1 ? ahi : ev;
-        T v;
-        if (e == 0) {
-          const T sh = wave_shr1(Xc1[c]);
-          const T l = pl > 0 ? sh : zero;
-          v = Bc0[c] + Kc.kx0 * l + Kc.kx1 * Xc1[c] + Kc.kyl0 * ylo + Kc.kyu0 * yhi +
-              Kc.kz0 * Xp0[c] + Kn.kz0 * Xn0[c];
-          Xc0[c] = cell_ok ? Kc.d0 * v : zero;
-        } else {
-          const T sh = wave_shl1(Xc0[c]);
-          const R shk = wave_shl1(Kc.kx0);
-          const T rr = x0 + 2 < N ? sh : zero;
-          const R kr = x0 + 2 < N ? shk : (R)0;
-          v = Bc1[c] + Kc.kx1 * Xc0[c] + kr * rr + Kc.kyl1 * ylo + Kc.kyu1 * yhi +
-              Kc.kz1 * Xp1[c] + Kn.kz1 * Xn1[c];
-          Xc1[c] = cell_ok ? Kc.d1 * v : zero;
+        Xq0[c] = X0[sm][c];
+        Xq1[c] = X1[sm][c];
+      }
+      load_plane(sm, p + 2);  // zeros beyond the last plane
+      // element of the pair updated in this step (first colour on plane p,
+      // second colour on plane p-1): e = (F + y + p) & 1, uniform per wave
+      const int e = (F + ybase + p) & 1;
+      const int buf = p & 1;
+      // publish: this row's second-colour cell of plane p (x_in, element 1-e) and
+      // first-colour cell of plane p-1 (updated last step, element 1-e)
+#pragma unroll
+      for (int c = 0; c < COLS; ++c) {
+        const T va = e ? X0[sc][c] : X1[sc][c], vb = e ? X0[sp][c] : X1[sp][c];
+        xa[buf][r][c][pl] = row_in ? va : zero;
+        xb[buf][r][c][pl] = row_in ? vb : zero;
+      }
+      __syncthreads();
+      const PlaneK<R>&Kc = K[sc], &Kn = K[sn], &Kp = K[sp];
+      // first colour on plane p, element e (all rows of the workgroup)
+      if (p < N) {
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) {
+          const T alo = xa[buf][r > 0 ? r - 1 : 0][c][pl];
+          const T ahi = xa[buf][r < RW - 1 ? r + 1 : RW - 1][c][pl];
+          const T ev = eok ? E[sc][c] : zero;
+          const T ylo = r > 0 ? alo : ev;
+          const T yhi = r < RW - 1 ? ahi : ev;
+          if (e == 0) {
+            const T sh = wave_shr1(X1[sc][c]);
+            const T l = pl > 0 ? sh : zero;
+            const T v = B0[sc][c] + Kc.kx0 * l + Kc.kx1 * X1[sc][c] + Kc.kyl0 * ylo +
+                        Kc.kyu0 * yhi + Kc.kz0 * X0[sp][c] + Kn.kz0 * X0[sn][c];
+            X0[sc][c] = Kc.d0 * v;
+          } else {
+            const T sh = wave_shl1(X0[sc][c]);
+            const R shk = wave_shl1(Kc.kx0);
+            const T rr = has_r ? sh : zero;
+            const R kr = has_r ? shk : (R)0;
+            const T v = B1[sc][c] + Kc.kx1 * X0[sc][c] + kr * rr + Kc.kyl1 * ylo +
+                        Kc.kyu1 * yhi + Kc.kz1 * X1[sp][c] + Kn.kz1 * X1[sn][c];
+            X1[sc][c] = Kc.d1 * v;
+          }
         }
       }
-    }
-    // second colour on plane p-1, element e (rows y0 .. y0+TY-1), and output
-    if (p - 1 >= zs) {
-      const int z = p - 1;
+      // second colour on plane p-1, element e (rows y0 .. y0+TY-1), and output
+      if (p - 1 >= zs) {
+        int64_t zo = (int64_t)(p - 1) * NN;
+        asm volatile("" : "+s"(zo));
 #pragma unroll
-      for (int c = 0; c < COLS; ++c) {
-        const T ylo = xb[buf][r > 0 ? r - 1 : 0][c][pl];
-        const T yhi = xb[buf][r < RW - 1 ? r + 1 : RW - 1][c][pl];
-        {
+        for (int c = 0; c < COLS; ++c) {
+          const T ylo = xb[buf][r > 0 ? r - 1 : 0][c][pl];
+          const T yhi = xb[buf][r < RW - 1 ? r + 1 : RW - 1][c][pl];
           if (e == 0) {
-            const T sh = wave_shr1(Xp1[c]);
+            const T sh = wave_shr1(X1[sp][c]);
             const T l = pl > 0 ? sh : zero;
-            const T v = Bp0[c] + Kp.kx0 * l + Kp.kx1 * Xp1[c] + Kp.kyl0 * ylo + Kp.kyu0 * yhi +
-                        Kp.kz0 * Xq0[c] + Kc.kz0 * Xc0[c];
-            if (inner) Xp0[c] = cell_ok ? Kp.d0 * v : zero;
+            const T v = B0[sp][c] + Kp.kx0 * l + Kp.kx1 * X1[sp][c] + Kp.kyl0 * ylo +
+                        Kp.kyu0 * yhi + Kp.kz0 * Xq0[c] + Kc.kz0 * X0[sc][c];
+            if (inner) X0[sp][c] = Kp.d0 * v;
           } else {
-            const T sh = wave_shl1(Xp0[c]);
+            const T sh = wave_shl1(X0[sp][c]);
             const R shk = wave_shl1(Kp.kx0);
-            const T rr = x0 + 2 < N ? sh : zero;
-            const R kr = x0 + 2 < N ? shk : (R)0;
-            const T v = Bp1[c] + Kp.kx1 * Xp0[c] + kr * rr + Kp.kyl1 * ylo + Kp.kyu1 * yhi +
-                        Kp.kz1 * Xq1[c] + Kc.kz1 * Xc1[c];
-            if (inner) Xp1[c] = cell_ok ? Kp.d1 * v : zero;
+            const T rr = has_r ? sh : zero;
+            const R kr = has_r ? shk : (R)0;
+            const T v = B1[sp][c] + Kp.kx1 * X0[sp][c] + kr * rr + Kp.kyl1 * ylo +
+                        Kp.kyu1 * yhi + Kp.kz1 * Xq1[c] + Kc.kz1 * X1[sc][c];
+            if (inner) X1[sp][c] = Kp.d1 * v;
           }
-          if (owner && xok && con[c]) {
-            const int64_t i = ((int64_t)z * N + y) * N + x0;
-            xo[c][i] = Xp0[c];
-            xo[c][i + 1] = Xp1[c];
+          if (store && con[c]) {
+            T* q = reinterpret_cast<T*>(reinterpret_cast<char*>(xo[c] + zo) + offx);
+            q[0] = X0[sp][c];
+            q[1] = X1[sp][c];
           }
         }
       }
