@@ -370,7 +370,7 @@ void Context::cvcycle(int l, const T* b, T* x, int nb, const int* act, bool top)
     if (l == 1 && nn_use_) {
       // learned finest level: sweep, network | coarse correction | network, sweep
       T* res = w.vt[0];
-      cop_smooth<T>(l, b, x, nb, act, true, false);
+      cop_smooth_n<T>(l, b, x, nb, act, 1, true, false);
       nn_step(b, x, nb, act);
       cop_residual<T, T, T>(l, b, x, res, nb, act, nullptr);
       cop_restrict<T>(l, res, w.vb[1], nb, act);
@@ -385,14 +385,17 @@ void Context::cvcycle(int l, const T* b, T* x, int nb, const int* act, bool top)
   const int pre = opt_.nu_pre, post = opt_.nu_post;
   if (pre == 0) vec_zero<T>(x, n, nb, act, s_);
   cop_smooth_n<T>(l, b, x, nb, act, pre, true, false);
-  // block levels whose coarse sites have as many unknowns: the residual of one colour is
-  // restricted as it is formed, and the correction is added where the first half sweep
-  // reads it
+  // the residual of the colour that the pre-smoothing did not solve last is restricted as
+  // it is formed; on block levels whose coarse sites have as many unknowns the correction
+  // is added where the first half sweep reads it
   const Level& L = lv_[l - 1];
   const bool fused = !L.wilson && bsr8_ok(L.dof) && lv_[l].dof == L.dof;
   if (fused && pre > 0) {
     bsr8_residual_restrict<T>(b, x, w.vb[l], blocks<T>(l), qmat<T>(l), L.side, L.dof, L.blk, nb,
                               act, false, s_);
+  } else if (L.wilson && pre > 0 && L.blk % 2 == 0 && bsr8_ok(lv_[l].dof)) {
+    wilson_residual_restrict<T>(b, x, w.vb[l], links<T>(l), qmat<T>(l), L.side, op_.mass + 2.0,
+                                L.blk, lv_[l].dof, nb, act, false, s_);
   } else {
     T* res = w.vt[l - 1];
     cop_residual<T, T, T>(l, b, x, res, nb, act, nullptr);

@@ -430,6 +430,11 @@ void bsr8_residual(const T* b, const T* x, Tr* r, const T* B, int Nc, int dof, i
 template <typename T>
 void bsr8_residual_restrict(const T* b, const T* x, T* xc, const T* B, const T* Q, int Nc, int dof,
                             int blk, int nb, const int* active, bool reverse, hipStream_t s);
+// the same from the two-spin lattice, blk even
+template <typename T>
+void wilson_residual_restrict(const T* b, const T* x, T* xc, const T* U, const T* Q, int N,
+                              double diag, int blk, int dofC, int nb, const int* active,
+                              bool reverse, hipStream_t s);
 template <typename T>
 void agg8_restrict(const T* x, T* xc, const T* q, int Nf, int dofF, int blk, int dofC, int nb,
                    const int* active, hipStream_t s);

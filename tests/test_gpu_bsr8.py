@@ -105,14 +105,14 @@ def test_solve_of_an_8_dof_level(name, precision):
     est.close()
 
 
-def _vcycle(A, P, nv, l, b, pre, post, omega):
+def _vcycle(A, P, dofs, l, b, pre, post, omega):
     if l == len(A) - 1:
         return np.linalg.solve(A[l].toarray(), b)
-    colour = np.repeat(hierarchy.site_coloring(int(np.sqrt(A[l].shape[0] // nv))), nv)
+    colour = np.repeat(hierarchy.site_coloring(int(np.sqrt(A[l].shape[0] // dofs[l]))), dofs[l])
     X = np.zeros_like(b)
     for k in range(b.shape[1]):
         X[:, k] = hierarchy.rbgs_sweeps(A[l], b[:, k], X[:, k], colour, pre, False)
-    X = X + omega * (P[l] @ _vcycle(A, P, nv, l + 1, P[l].conj().T @ (b - A[l] @ X), pre, post,
+    X = X + omega * (P[l] @ _vcycle(A, P, dofs, l + 1, P[l].conj().T @ (b - A[l] @ X), pre, post,
                                     omega))
     for k in range(b.shape[1]):
         X[:, k] = hierarchy.rbgs_sweeps(A[l], b[:, k], X[:, k], colour, post, True)
@@ -120,24 +120,27 @@ def _vcycle(A, P, nv, l, b, pre, post, omega):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32_ir64"])
-@pytest.mark.parametrize("name,pre,post", [("wilson_4", 1, 1), ("wilson_4", 2, 0),
-                                           ("wilson_72", 1, 1),
-                                           ("wilson_2", 1, 2), ("wilson_2", 0, 1),
-                                           ("gauge_4", 1, 1), ("gauge_2", 2, 2)])
-def test_one_step_is_the_vcycle(name, pre, post, precision):
+@pytest.mark.parametrize("name,top,pre,post", [
+    ("wilson_4", 2, 1, 1), ("wilson_4", 2, 2, 0), ("wilson_72", 2, 1, 1), ("wilson_2", 2, 1, 2),
+    ("wilson_2", 2, 0, 1), ("gauge_4", 2, 1, 1), ("gauge_2", 2, 2, 2),
+    # from the fine lattice: its residual of one colour restricted directly (even blocks)
+    ("wilson_4", 1, 2, 1), ("wilson_2", 1, 1, 1), ("wilson_3", 1, 1, 1), ("gauge_8", 1, 1, 1)])
+def test_one_step_is_the_vcycle(name, top, pre, post, precision):
     require_gpu()
     omega = 1.0 if pre == post else 1.2
     est, A, P = _problem(name, precision, pre=pre, post=post, omega=omega, krylov_restart=1,
                          solve_tol=0.9999)
     widths = WIDTHS + ([64, 70] if name == "wilson_72" else [])
     rng = np.random.default_rng(11)
-    b = _random(rng, max(widths), A[1].shape[0]).T
-    z = _vcycle(A[1:], P[1:], CASES[name][4], 0, b, pre, post, omega)
+    l0 = top - 1
+    dofs = [2 if name.startswith("wilson") else 1] + [CASES[name][4]] * (len(A) - 1)
+    b = _random(rng, max(widths), A[l0].shape[0]).T
+    z = _vcycle(A[l0:], P[l0:], dofs[l0:], 0, b, pre, post, omega)
     # one minimal-residual step along M b
-    w = A[1] @ z
+    w = A[l0] @ z
     ref = (z * ((w.conj() * b).sum(0) / (w.conj() * w).sum(0))).T
     for width in widths:
-        Y, _ = est.solve(2, to_dev(b.T[:width]))
+        Y, _ = est.solve(top, to_dev(b.T[:width]))
         err = np.max(np.abs(from_dev(Y, complex_=True) - ref[:width]), axis=1)
         # FP64: rounding through the dense inverse; FP32: of some hundred operations
         tol = 1e-10 if precision == "fp64" else 1e-4
