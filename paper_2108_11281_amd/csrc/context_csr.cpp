@@ -662,15 +662,18 @@ void Context::build_small_csr() {
     d.row = up(row);
     d.off = sell(L.h_rp, L.h_ci, L.h_v, row, true, pos);
     std::vector<double> di(row.size(), 0.0), dd(row.size(), 0.0);
+    std::vector<int> dp(row.size(), 0);
     for (size_t k = 0; k < row.size(); ++k)
       if (row[k] >= 0)
         for (int64_t q = L.h_rp[row[k]]; q < L.h_rp[row[k] + 1]; ++q)
           if (L.h_ci[q] == row[k]) {
             dd[k] = L.h_v[q];
             di[k] = 1.0 / L.h_v[q];
+            dp[k] = (int)(q - L.h_rp[row[k]]);
           }
     d.di = up(to_t(di));
     d.dd = up(to_t(dd));
+    d.dp = up(dp);
     if (general_) {
       HostCsr Ph;
       Ph.n = (int)L.n;

@@ -621,6 +621,7 @@ struct SmallCsrLevel {
   const int* row = nullptr;          // natural index of a position (-1: padding)
   SellView<T> off;                   // off-diagonal part
   const T *di = nullptr, *dd = nullptr;  // 1 / a_ii and a_ii (padding: 0)
+  const int* dp = nullptr;               // off-diagonal entries before a_ii in its row
   // transfers to the next level (its positions; natural order on the coarsest):
   // aggregation (members of J in mem[mptr[J]..], scales) or, with mptr null, R and P
   const int *mptr = nullptr, *mem = nullptr, *agg = nullptr;

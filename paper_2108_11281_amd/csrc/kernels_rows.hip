@@ -343,6 +343,14 @@ __global__ __launch_bounds__(kThreads) void k_rows_agg_sum(const T* __restrict__
   ln.store(rc, (int64_t)J * W + ln.c, acc);
 }
 
+// a rounded product, not contracted with a sum: the prolongation of every form rounds
+// the correction before adding it
+template <typename T>
+__device__ __forceinline__ T product(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 // x_i = beta x_i + w s_{J(i)} ec_{J(i)}  (x_i = w s ec when beta = 0)
 template <typename T, int G, int V>
 __global__ __launch_bounds__(kThreads) void k_rows_prolong(const T* __restrict__ ec,
@@ -362,8 +370,10 @@ __global__ __launch_bounds__(kThreads) void k_rows_prolong(const T* __restrict__
   if (beta != T(0)) old = ldv<T, V>(x, at);
   T out[V];
 #pragma unroll
-  for (int v = 0; v < V; ++v)
-    out[v] = beta == T(0) ? s * e.v[v] : beta * old.v[v] + s * e.v[v];
+  for (int v = 0; v < V; ++v) {
+    const T c = product(s, e.v[v]);
+    out[v] = beta == T(0) ? c : beta * old.v[v] + c;
+  }
   ln.store(x, at, out);
 }
 

@@ -67,6 +67,44 @@ __device__ __forceinline__ T sell_sum(const SellView<T>& M, int sl, int lane, co
   return acc;
 }
 
+// a rounded product, not contracted with a sum
+template <typename T>
+__device__ __forceinline__ T product(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// the same with the diagonal d xk in its place before entry dp: the order of the full
+// row, so that the sum is that of the residual on levels with a launch per operation
+template <typename T>
+__device__ __forceinline__ T sell_sum_diag(const SellView<T>& M, int sl, int lane, const T* xs,
+                                           int dp, T d, T xk) {
+  const int p0 = uniform_at(M.ptr, sl), w = (uniform_at(M.ptr, sl + 1) - p0) >> 6;
+  int at = p0 + lane;
+  T acc = T(0);
+  for (int e = 0; e < w; e += 4, at += 256) {
+    int j[4];
+    T a[4], g[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      j[u] = e + u < w ? M.ci[at + u * 64] : 0;
+      a[u] = e + u < w ? M.v[at + u * 64] : T(0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] = xs[j[u]];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (e + u == dp) acc = fused(d, xk, acc);  // a product added under a condition is
+                                                 // not contracted
+      if (e + u < w) acc += a[u] * g[u];
+    }
+  }
+  if (dp >= ((w + 3) & ~3)) acc = fused(d, xk, acc);  // not met in the loop
+  return acc;
+}
+
 template <typename T>
 __device__ __forceinline__ void sweep(const SmallCsrLevel<T>& L, T* xs, const T* b, bool reverse,
                                       int wave, int lane) {
@@ -114,7 +152,7 @@ __global__ __launch_bounds__(kNT) void k_small_csr(const SmallCsrLevel<T>* __res
       for (int sl = wave; sl < (L.np >> 6); sl += kWaves) {
         const int k = sl * 64 + lane;
         const T xk = xs[k];
-        r[k] = b[k] - (sell_sum(L.off, sl, lane, xs) + L.dd[k] * xk);
+        r[k] = b[k] - sell_sum_diag(L.off, sl, lane, xs, L.dp[k], L.dd[k], xk);
         x[k] = xk;
       }
       __syncthreads();
@@ -137,28 +175,13 @@ __global__ __launch_bounds__(kNT) void k_small_csr(const SmallCsrLevel<T>* __res
       __syncthreads();
     }
   }
-  if (mode == kSmallCsrAll) {  // coarsest solve from the packed transposed inverse
-    using V4 = typename body::Vec4<T>::type;
-    const T* b = cs.b + (int64_t)col * cs.n;
-    T* x = cs.x + (int64_t)col * cs.n;
-    T* bs = xs;             // cs.ld values, zero padded
-    T* part = xs + cs.ld;   // 4 x cs.ld partial sums
-    for (int j = tid; j < cs.ld; j += kNT) bs[j] = j < cs.n ? b[j] : T(0);
-    __syncthreads();
-    for (int t = tid; t < 4 * cs.ld; t += kNT) {
-      const int i = t % cs.ld, p = t / cs.ld;
-      T acc = T(0);
-      for (int q = p * cs.ld / 16; q < (p + 1) * cs.ld / 16; ++q) {
-        const V4 a = *reinterpret_cast<const V4*>(cs.inv + ((int64_t)q * cs.ld + i) * 4);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) acc += a[s] * bs[4 * q + s];
-      }
-      part[t] = acc;
+  if (mode == kSmallCsrAll) {  // coarsest solve, the sums of the solver's own product
+    for (int bx = 0; bx < (cs.ld >> 4); ++bx) {
+      body::dense_apply_mfma<T, kWaves>(cs.inv, cs.b + (int64_t)col * cs.n,
+                                        cs.x + (int64_t)col * cs.n, cs.n, cs.ld, 1, nullptr, bx, 0,
+                                        true, xs, tid);
+      __syncthreads();
     }
-    __syncthreads();
-    for (int i = tid; i < cs.n; i += kNT)
-      x[i] = part[i] + part[cs.ld + i] + part[2 * cs.ld + i] + part[3 * cs.ld + i];
-    __syncthreads();
   }
   if (mode != kSmallCsrDown) {
     for (int l = nl - 1; l >= 0; --l) {
@@ -169,7 +192,8 @@ __global__ __launch_bounds__(kNT) void k_small_csr(const SmallCsrLevel<T>* __res
       const T* ec = last ? cs.x + (int64_t)col * cs.n
                          : lev[l + 1].x + (int64_t)col * lev[l + 1].np;
       if (L.mptr) {
-        for (int k = tid; k < L.np; k += kNT) xs[k] = x[k] + omega * L.fs[k] * ec[L.agg[k]];
+        for (int k = tid; k < L.np; k += kNT)
+          xs[k] = x[k] + product(omega * L.fs[k], ec[L.agg[k]]);
       } else {
         for (int sl = wave; sl < (L.np >> 6); sl += kWaves) {
           const int k = sl * 64 + lane;
@@ -194,8 +218,9 @@ __global__ __launch_bounds__(kNT) void k_small_csr(const SmallCsrLevel<T>* __res
 }  // namespace
 
 template <typename T>
-size_t small_csr_lds(int np_max, int ld) {
-  return sizeof(T) * (size_t)(np_max > 5 * ld ? np_max : 5 * ld);
+size_t small_csr_lds(int np_max, bool dense) {
+  const int parts = body::kDenseParts * 4 * 64;
+  return sizeof(T) * (size_t)(dense && np_max < parts ? parts : np_max);
 }
 
 void small_csr_setup() {
@@ -210,7 +235,7 @@ void small_csr(const SmallCsrLevel<T>* lev, int nl, int np_max, const SmallCsrCo
                const T* b, T* x, int W, int pre, int post, double omega, int mode,
                const int* active, hipStream_t s) {
   MLMC_LAUNCH(k_small_csr<T>, dim3(W), dim3(kNT),
-              small_csr_lds<T>(np_max, mode == kSmallCsrAll ? cs.ld : 0), s, lev, nl, cs, b, x, W,
+              small_csr_lds<T>(np_max, mode == kSmallCsrAll), s, lev, nl, cs, b, x, W,
               pre, post, (T)omega, mode, active, timing_log());
 }
 
