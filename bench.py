@@ -177,8 +177,8 @@ def kernel_table(est):
     return out
 
 
-CSR_SWEEP_LABEL = ("multicolour Gauss-Seidel sweep: k_csr_gs + k_csr_gs_tail<float> "
-                   "(all colour classes)")
+CSR_SWEEP_LABEL = ("multicolour Gauss-Seidel sweep: k_rows_gs<float> (one launch per large "
+                   "colour class) and k_small_csr<float> (whole V-cycles of small levels)")
 
 
 def hbm_roofline(name, stats, stride, traffic=None):
@@ -296,7 +296,7 @@ def run_poisson(args, m, torch):
     kernels = kernel_table(est)
     est.set_timing(False)
     ms_per_step = 1000.0 * elapsed / args.steps
-    roofline = hbm_roofline("rbgs_sweep<float>", gs, args.timing_stride, stored_traffic())
+    roofline = hbm_roofline("rbgs_sweep<float> (sides up to 128: k_small_vcycle, whole V-cycles)", gs, args.timing_stride, stored_traffic())
     roofline["per_level"] = per_level
     # sustained HBM rate of a plain copy (1 GiB each way): the library's
     # streaming kernel and torch's copy, beside the vendor peak
@@ -516,8 +516,8 @@ def run_wilson(args, m, torch, N, learned):
                         algorithmic_flops_per_launch=round(flops / max(launches, 1)))
     else:
         roofline = hbm_roofline("smoother sweeps: k_wilson_gs2<c32> (finest, both colours "
-                                "per pass) and k_bsr_gs / k_bsr_gs_rows<8, c32> (coarse block "
-                                "stencils)", ks,
+                                "per pass) and k_bsr8_gs<c32> (coarse block stencils, 8 "
+                                "unknowns per site)", ks,
                                 args.timing_stride)
     compare = {"learned_stats": list(est.learned_stats())} if learned else {}
     weights = est.get_nn_weights() if learned else None
@@ -903,8 +903,8 @@ def run_gauge(args, m, torch):
               "solve_tol": w["solve_tol"], "nu_pre": args.nu, "nu_post": args.nu}
     contract(args, round(ms_per_step / 1000.0, 4), "s", False, ms_per_step, "c64+c128ir",
              "synthetic (U(1) phases N(0,0.3^2), Z4 probes from Philox4x64-10)", config,
-             hbm_roofline("smoother sweeps: k_bsr_gs / k_bsr_gs_rows<1, c32> (finest, 1 x 1 "
-                          "blocks) and <n_vec, c32> (coarse block stencils)", ks,
+             hbm_roofline("smoother sweeps: k_bsr_gs_rows<1, c32> (finest, 1 x 1 "
+                          "blocks) and k_bsr8_gs<c32> (coarse block stencils)", ks,
                           args.timing_stride),
              None, accuracy={"n_samples": [r["n_samples"] for r in runs],
                              "rmsd_rel": [round(r["rmsd"] / abs(r["trace"].real), 7)

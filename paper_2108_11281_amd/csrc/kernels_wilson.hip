@@ -905,6 +905,17 @@ void wilson_rbgs_fused(const T* b, const T* xin, T* xout, const T* U, int N, dou
     default: throw Error(MLMC_EUNSUPPORTED, "unsupported number of dofs per site");   \
   }
 
+// the block kernels of this file: 4 and 8 unknowns per site run on the matrix cores
+// (kernels_bsr8.hip)
+#define BLOCK_DISPATCH(DOFV, ...)                                                       \
+  switch (DOFV) {                                                                     \
+    case 1: { constexpr int D = 1; __VA_ARGS__; break; }                              \
+    case 2: { constexpr int D = 2; __VA_ARGS__; break; }                              \
+    case 12: { constexpr int D = 12; __VA_ARGS__; break; }                            \
+    case 16: { constexpr int D = 16; __VA_ARGS__; break; }                            \
+    default: throw Error(MLMC_EUNSUPPORTED, "unsupported number of dofs per site");   \
+  }
+
 template <typename Tb, typename T, typename Tr>
 void bsr_residual(const Tb* b, const T* x, Tr* r, const T* B, int Nc, int dof, int nb,
                   const int* active, c64* partials, int form, hipStream_t s) {
@@ -916,17 +927,17 @@ void bsr_residual(const Tb* b, const T* x, Tr* r, const T* B, int Nc, int dof, i
   // partial sums (the outer residual) come from the thread-per-site form
   if (form == 1 && !partials) {
     const dim3 g = grid_waves((int64_t)Nc * Nc, nb);
-    BSR_DISPATCH(dof, hipLaunchKernelGGL((k_bsr_residual<D, Tb, T, Tr>), g, dim3(kThreads), 0, s,
+    BLOCK_DISPATCH(dof, hipLaunchKernelGGL((k_bsr_residual<D, Tb, T, Tr>), g, dim3(kThreads), 0, s,
                                           b, x, r, B, Nc, nb, active));
   } else if (!partials) {
-    BSR_DISPATCH(dof, {
+    BLOCK_DISPATCH(dof, {
       const dim3 g = grid_sites((int64_t)Nc * Nc * bsr_group<D>(), nb);
       hipLaunchKernelGGL((k_bsr_residual_rows<D, Tb, T, Tr>), g, dim3(kThreads), 0, s, b, x, r,
                          B, Nc, active);
     });
   } else {
     const dim3 g = grid_sites((int64_t)Nc * Nc, nb);
-    BSR_DISPATCH(dof, hipLaunchKernelGGL((k_bsr_residual_sites<D, Tb, T, Tr>), g, dim3(kThreads),
+    BLOCK_DISPATCH(dof, hipLaunchKernelGGL((k_bsr_residual_sites<D, Tb, T, Tr>), g, dim3(kThreads),
                                           0, s, b, x, r, B, Nc, active, partials));
   }
 }
@@ -942,12 +953,12 @@ void bsr_rbgs(const T* b, T* x, const T* B, const T* Dinv, int Nc, int dof, int 
   const int first = reverse ? 1 : 0;
   if (form == 1) {
     const dim3 g = grid_waves((int64_t)Nc * Nc / 2, nb);
-    BSR_DISPATCH(dof, MLMC_LAUNCH((k_bsr_gs<D, T>), g, dim3(kThreads), 0, s, b, x, B, Dinv, Nc,
+    BLOCK_DISPATCH(dof, MLMC_LAUNCH((k_bsr_gs<D, T>), g, dim3(kThreads), 0, s, b, x, B, Dinv, Nc,
                                    first, zero_init ? 1 : 0, nb, active, timing_log()));
-    BSR_DISPATCH(dof, MLMC_LAUNCH((k_bsr_gs<D, T>), g, dim3(kThreads), 0, s, b, x, B, Dinv, Nc,
+    BLOCK_DISPATCH(dof, MLMC_LAUNCH((k_bsr_gs<D, T>), g, dim3(kThreads), 0, s, b, x, B, Dinv, Nc,
                                    1 - first, 0, nb, active, (int*)nullptr));
   } else {
-    BSR_DISPATCH(dof, {
+    BLOCK_DISPATCH(dof, {
       const dim3 g = grid_sites((int64_t)Nc * Nc / 2 * bsr_group<D>(), nb);
       MLMC_LAUNCH((k_bsr_gs_rows<D, T>), g, dim3(kThreads), 0, s, b, x, B, Dinv, Nc, first,
                   zero_init ? 1 : 0, active, timing_log());
