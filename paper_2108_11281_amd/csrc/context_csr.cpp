@@ -798,7 +798,10 @@ void Context::vcycle_csr(int l, const T* b, T* x, int nb, const int* act, c64* r
   const int64_t n = L.n;
   const double en = (double)sizeof(T) * (double)n;
   const SmallCsr<T>& sc = small_csr_of<T>();
-  if (l < Ls_ && l >= small_csr_level(nb) && sc.lev) {
+  // a second coarse-grid cycle needs this level's coarse residual between the two, so
+  // such a top level keeps its launches; the cycles below it are the kernel's
+  const bool two = top && top_cycles_ == 2 && l + 1 < Ls_;
+  if (l < Ls_ && l >= small_csr_level(nb) && sc.lev && !two) {
     const int at = l - small_csr_level_[1], nl = Ls_ - l;
     const int np = *std::max_element(small_np_.begin() + at, small_np_.end());
     const bool all = sc.coarse.n <= kSmallCsrDense;
