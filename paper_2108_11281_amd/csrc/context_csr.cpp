@@ -735,9 +735,9 @@ void Context::build_small_csr() {
 
 // Autotuner of the CSR sweep: per smoothed level, once over all nb columns and
 // once over a narrow batch of 16, the schedule of its trailing small colour
-// classes (a launch per class, or the trailing classes of at most 256, 1024 or
-// 4096 rows in shared launches: fewer launches, fewer compute units per class; the
-// results are identical).  Each candidate is timed as the best of five sweeps
+// classes (a launch per class, or the trailing classes of at most 256 or 1024 rows
+// in shared launches: fewer launches, fewer compute units per class; the results are
+// identical; classes of 4096 rows never gained).  Each candidate is timed as the best of five sweeps
 // after a warm-up.  Runs once at setup on the library's own work vectors.
 void Context::tune_csr() {
   const bool fp32 = opt_.precision == MLMC_FP32_IR64;
@@ -768,7 +768,7 @@ void Context::tune_csr() {
       const float t_classes = time_sweep(L, ncols, 0);
       float best = t_classes;
       int best_tail = 0, last_start = csr_tail_start(off, 0);
-      for (int tail : {256, 1024, 4096}) {
+      for (int tail : {256, 1024}) {
         const int start = csr_tail_start(off, tail);
         if (start == last_start) continue;  // the same schedule as a smaller bound
         last_start = start;

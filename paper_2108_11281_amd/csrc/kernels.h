@@ -550,8 +550,8 @@ void rows_out(const Ts* src, double* dst, int64_t n, int W, hipStream_t s);
 // One Gauss-Seidel sweep in place over the colour classes (reverse: last class
 // first).  Each class is one launch, except the trailing run of classes of at
 // most tail_rows rows each (csr_tail_start; 0: none), which shares launches of up
-// to kMaxTailClasses classes: one workgroup of kTailWaves waves per column group,
-// a barrier between classes.  The rows of a class are independent, so both
+// to kMaxTailClasses classes: one workgroup of kTailWaves waves per vector, a
+// barrier between classes.  The rows of a class are independent, so both
 // schedules give the same result.
 constexpr int kTailWaves = 16;
 constexpr int kMaxTailClasses = 64;

@@ -173,23 +173,26 @@ __global__ __launch_bounds__(kThreads) void k_rows_gs(const T* b, T* x,
 }
 
 // Several consecutive colour classes of a sweep in one launch (the small classes
-// that a greedy colouring leaves at its end): a workgroup per column group runs
-// the classes one after another; the rows of a class are independent, so only the
-// class boundaries need its barrier (which also orders its waves' stores before
-// the next class's loads).
-template <typename T, int G, int V>
+// that a greedy colouring leaves at its end): a workgroup per vector runs the
+// classes one after another, a row per lane; the rows of a class are independent, so
+// only the class boundaries need its barrier (which also orders its waves' stores
+// before the next class's loads).  Bound by the chain of rounds, so rows in flight
+// count for more than wide gathers: the sweep of 20,000 rows of a geometric graph with
+// 5 of its 13 classes here, 8 / 16 / 64 FP32 vectors, takes 49 / 50 / 48 us (53 / 54 /
+// 48 with a launch per class); with the rows' lanes of the other launches it took 51 /
+// 55 / 61.
+template <typename T>
 __global__ __launch_bounds__(kTailWaves * 64) void k_rows_gs_tail(
     const T* b, T* x, const int4* __restrict__ rows, const int* __restrict__ ci,
     const T* __restrict__ a, const T* __restrict__ di, CsrTail t, int W, const int* active,
     int* tlog) {
-  const Lane<G, V> ln(W, active);
+  const Lane<1, 1> ln(W, active);
   log_columns(tlog, ln, W);
-  if (!__syncthreads_or(ln.live)) return;
-  const int grp = group_of<G>(threadIdx.x);
+  if (!ln.live) return;  // the whole workgroup: one vector
   for (int q = 0; q < t.count; ++q) {
     const int cc = t.reverse ? t.count - 1 - q : q;
-    for (int k = t.off[cc] + grp; k < t.off[cc + 1]; k += kTailWaves * 64 / G)
-      gs_row<T, G, V>(b, x, rows, ci, a, di, k, W, ln);
+    for (int k = t.off[cc] + (int)threadIdx.x; k < t.off[cc + 1]; k += kTailWaves * 64)
+      gs_row<T, 1, 1>(b, x, rows, ci, a, di, k, W, ln);
     __syncthreads();
   }
 }
@@ -625,10 +628,8 @@ void rows_gs_sweep(const T* b, T* x, const CsrSweep<T>& S, int W, int tail_rows,
     t.count = c1 - c0;
     t.reverse = reverse ? 1 : 0;
     for (int c = c0; c <= c1; ++c) t.off[c - c0] = S.off[c];
-    ROWS_LAUNCH(MLMC_LAUNCH((k_rows_gs_tail<T, G, V>),
-                            dim3(1u, (unsigned)((W + G * V - 1) / (G * V))),
-                            dim3(kTailWaves * 64), 0, s, b, x, S.rows, S.ci, S.v, S.di, t, W,
-                            active, timing_log()));
+    MLMC_LAUNCH(k_rows_gs_tail<T>, dim3(1u, (unsigned)W), dim3(kTailWaves * 64), 0, s, b, x,
+                S.rows, S.ci, S.v, S.di, t, W, active, timing_log());
   };
   if (!reverse) {
     for (int c = 0; c < tail; ++c) one_class(c);
