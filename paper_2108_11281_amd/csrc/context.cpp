@@ -1756,22 +1756,35 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
       if (csr_) rows_in<T>(src, nullptr, dst, n, nrhs, s_);
       else to_t(dst, src, m);
     };
-    in_t(bt, b);
-    if (!zero_start) in_t(xa, x);
-    else if (sweeps == 0) vec_zero<T>(xa, m, 1, nullptr, s_);
+    // CSR levels that one workgroup per vector sweeps: in the caller's blocks
+    const bool direct =
+        csr_ && csr_tail < 0 && !rc && sweeps > 0 && small_sweeps<T>(level);
+    if (!direct) {
+      in_t(bt, b);
+      if (!zero_start) in_t(xa, x);
+      else if (sweeps == 0) vec_zero<T>(xa, m, 1, nullptr, s_);
+    }
     const Level& L = lv_[level - 1];
     bool restricted = false;
-    if (complex_) {
+    if (direct) {
+      const int at = level - small_csr_level_[1];
+      small_csr_sweeps<T, double>(small_csr_of<T>().lev + at, small_np_[at], b,
+                                  zero_start ? nullptr : x, x, nrhs, 1, n, sweeps, reverse,
+                                  nullptr, s_);
+    } else if (complex_) {
       using C = typename std::conditional<sizeof(T) == 4, c32, c64>::type;
       // the V-cycle's sweep sequence (fused two-colour passes on the Wilson level;
       // from zero: the zero-start form of the first pass)
       cop_smooth_n<C>(level, reinterpret_cast<const C*>(bt), reinterpret_cast<C*>(xa), nrhs,
                       nullptr, sweeps, zero_start, reverse);
     } else if (csr_) {
-      if (zero_start) vec_zero<T>(xa, m, 1, nullptr, s_);  // as the V-cycle starts
-      for (int i = 0; i < sweeps; ++i)
-        rows_gs_sweep<T>(bt, xa, csr_sweep<T>(level), nrhs,
-                         csr_tail >= 0 ? csr_tail : this->csr_tail(L, nrhs), nullptr, reverse, s_);
+      if (csr_tail < 0) {
+        csr_sweeps<T>(level, bt, xa, nrhs, sweeps, zero_start, reverse, nullptr);
+      } else {
+        if (zero_start) vec_zero<T>(xa, m, 1, nullptr, s_);
+        for (int i = 0; i < sweeps; ++i)
+          rows_gs_sweep<T>(bt, xa, csr_sweep<T>(level), nrhs, csr_tail, nullptr, reverse, s_);
+      }
     } else if (varcoef_) {
       for (int i = 0; i < sweeps; ++i) {
         const bool z = zero_start && i == 0;
@@ -1818,7 +1831,8 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
         op_res_restrict<T>(level, bt, xa, rct, nrhs, nullptr);
       }
     }
-    if (csr_) {
+    if (direct) {
+    } else if (csr_) {
       rows_out<T>(xa, x, n, nrhs, s_);
       if (rct) rows_out<T>(rct, rc, lv_[level].n, nrhs, s_);
     } else {

@@ -208,6 +208,15 @@ class Context {
   template <typename T> const CsrAgg<T>& csr_agg(int l) const;
   template <typename T> const CsrMat<T>& csr_P(int l) const;  // given prolongation
   template <typename T> const CsrMat<T>& csr_R(int l) const;  // its transpose
+  // whether sweeps of level l alone run as one workgroup per vector: up to the bound of
+  // narrow batches, whatever the width
+  template <typename T> bool small_sweeps(int l) {
+    return l < Ls_ && l >= small_csr_level_[0] && small_csr_of<T>().lev;
+  }
+  // `sweeps` sweeps in place (zero: from a zero iterate): one launch on such levels, else
+  // the launches of the tuned schedule
+  template <typename T> void csr_sweeps(int l, const T* b, T* x, int nb, int sweeps, bool zero,
+                                        bool reverse, const int* act);
   template <typename T> void vcycle_csr(int l, const T* b, T* x, int nb, const int* act,
                                         c64* rz_partials, bool top = false);
   void tune_varcoef();

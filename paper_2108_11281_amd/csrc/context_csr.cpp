@@ -737,8 +737,9 @@ void Context::build_small_csr() {
 // once over a narrow batch of 16, the schedule of its trailing small colour
 // classes (a launch per class, or the trailing classes of at most 256 or 1024 rows
 // in shared launches: fewer launches, fewer compute units per class; the results are
-// identical; classes of 4096 rows never gained).  Each candidate is timed as the best of five sweeps
-// after a warm-up.  Runs once at setup on the library's own work vectors.
+// identical; classes of 4096 rows never gained).  Each candidate is timed as the best
+// of five sweeps after a warm-up.  Runs once at setup on the library's own work
+// vectors.
 void Context::tune_csr() {
   const bool fp32 = opt_.precision == MLMC_FP32_IR64;
   hipEvent_t a = event(), b = event();
@@ -785,6 +786,31 @@ void Context::tune_csr() {
   ev_pool_.push_back(b);
 }
 
+template <typename T>
+void Context::csr_sweeps(int l, const T* b, T* x, int nb, int sweeps, bool zero, bool reverse,
+                         const int* act) {
+  if (sweeps == 0) return;
+  const Level& L = lv_[l - 1];
+  const double n = (double)L.n, nnz = (double)L.h_rp[L.n];
+  // vectors, and the matrix (off-diagonal entries, row ids, offsets, inverted diagonal)
+  // shared by the columns
+  const double bytes = 3.0 * sizeof(T) * n +
+                       ((nnz - n) * (4.0 + sizeof(T)) + n * (8.0 + sizeof(T))) / nb;
+  if (small_sweeps<T>(l)) {
+    const int at = l - small_csr_level_[1];
+    timed<T>(l, kTimGs, sweeps * bytes, act, nb, [&] {
+      small_csr_sweeps<T, T>(small_csr_of<T>().lev + at, small_np_[at], b, zero ? nullptr : x, x,
+                             nb, nb, 1, sweeps, reverse, act, s_);
+    });
+    return;
+  }
+  if (zero) vec_zero<T>(x, L.n * nb, 1, nullptr, s_);
+  for (int i = 0; i < sweeps; ++i)
+    timed<T>(l, kTimGs, bytes, act, nb, [&] {
+      rows_gs_sweep<T>(b, x, csr_sweep<T>(l), nb, csr_tail(L, nb), act, reverse, s_);
+    });
+}
+
 // V-cycle of a CSR level on interleaved blocks: in-place multicolour Gauss-Seidel sweeps (classes in
 // ascending order before the coarse correction, descending after it, so the
 // preconditioner is symmetric), residual + restriction, prolongation +
@@ -819,20 +845,13 @@ void Context::vcycle_csr(int l, const T* b, T* x, int nb, const int* act, c64* r
     rows_dense<T>(w.ainvT, b, x, (int)n, w.ld, nb, act, s_);
   } else {
     const CsrMat<T>& A = csr_mat<T>(l);
-    const CsrSweep<T>& S = csr_sweep<T>(l);
     const CsrAgg<T>& G = csr_agg<T>(l);
     const int64_t nnz = L.h_rp[n];
-    // matrix bytes of a sweep (off-diagonal entries, row ids, offsets, inverted
-    // diagonal) and of a residual (all entries, offsets), shared by the columns
-    const double sweep_mat = (double)(nnz - n) * (4.0 + sizeof(T)) + (double)n * (8.0 + sizeof(T));
+    // matrix bytes of a residual (all entries, offsets), shared by the columns
     const double res_mat = (double)nnz * (4.0 + sizeof(T)) + 4.0 * (double)n;
     const double enc = (double)sizeof(T) * (double)lv_[l].n;
     const int pre = opt_.nu_pre, post = opt_.nu_post;
-    const int tail = csr_tail(L, nb);
-    if (pre > 0) vec_zero<T>(x, n * nb, 1, nullptr, s_);
-    for (int i = 0; i < pre; ++i)
-      timed<T>(l, kTimGs, 3.0 * en + sweep_mat / nb, act, nb,
-               [&] { rows_gs_sweep<T>(b, x, S, nb, tail, act, false, s_); });
+    csr_sweeps<T>(l, b, x, nb, pre, true, false, act);
     T* bc = w.vb[l];
     T* ec = w.vx[l];
     if (general_) {  // given P and R = P^T
@@ -866,13 +885,15 @@ void Context::vcycle_csr(int l, const T* b, T* x, int nb, const int* act, c64* r
         rows_prolong<T>(ec, x, G, (int)n, omega_, pre == 0 ? 0.0 : 1.0, nb, act, s_);
       });
     }
-    for (int i = 0; i < post; ++i)
-      timed<T>(l, kTimGs, 3.0 * en + sweep_mat / nb, act, nb,
-               [&] { rows_gs_sweep<T>(b, x, S, nb, tail, act, true, s_); });
+    csr_sweeps<T>(l, b, x, nb, post, false, true, act);
   }
   if (rz_partials) rows_dot<T>(b, x, (int)n, nb, act, rz_partials, s_);
 }
 
+template void Context::csr_sweeps<float>(int, const float*, float*, int, int, bool, bool,
+                                         const int*);
+template void Context::csr_sweeps<double>(int, const double*, double*, int, int, bool, bool,
+                                          const int*);
 template void Context::vcycle_csr<float>(int, const float*, float*, int, const int*, c64*, bool);
 template void Context::vcycle_csr<double>(int, const double*, double*, int, const int*, c64*,
                                           bool);

@@ -644,5 +644,11 @@ template <typename T>
 void small_csr(const SmallCsrLevel<T>* lev, int nl, int np_max, const SmallCsrCoarse<T>& cs,
                const T* b, T* x, int W, int pre, int post, double omega, int mode,
                const int* active, hipStream_t s);
+// `sweeps` sweeps of level *lev (np positions) alone from xin (nullptr: zero; may be x);
+// element i of vector c at [i row_stride + c col_stride]
+template <typename T, typename U>
+void small_csr_sweeps(const SmallCsrLevel<T>* lev, int np, const U* b, const U* xin, U* x, int W,
+                      int64_t row_stride, int64_t col_stride, int sweeps, bool reverse,
+                      const int* active, hipStream_t s);
 
 }  // namespace mlmc
