@@ -135,35 +135,23 @@ __global__ __launch_bounds__(kThreads) void k_csr_spmm(
   }
 }
 
-// rc_J = s_J sum_{i in J} r_i, a thread per aggregate J, members in ascending order
-template <typename T, int COLS>
+// rc_J = s_J sum_{i in J} r_i, a thread per aggregate J and vector, members in
+// ascending order
+template <typename T>
 __global__ __launch_bounds__(kThreads) void k_csr_agg_sum(
     const T* __restrict__ r, T* __restrict__ rc, const int* __restrict__ aptr,
-    const int* __restrict__ arows, const T* __restrict__ cs, int n, int nc, int nb,
-    const int* active, int* tlog) {
-  const int col0 = blockIdx.y * COLS;
-  if (tlog && blockIdx.x == 0 && threadIdx.x < COLS && col0 + (int)threadIdx.x < nb)
-    tlog[col0 + threadIdx.x] = active ? active[col0 + threadIdx.x] : 1;
+    const int* __restrict__ arows, const T* __restrict__ cs, int n, int nc, const int* active,
+    int* tlog) {
+  const int col = blockIdx.y;
+  if (tlog && blockIdx.x == 0 && threadIdx.x == 0) tlog[col] = active ? active[col] : 1;
+  if (active && !active[col]) return;
   const int J = blockIdx.x * kThreads + threadIdx.x;
   if (J >= nc) return;
-  bool on[COLS];
-  T acc[COLS];
-#pragma unroll
-  for (int q = 0; q < COLS; ++q) {
-    on[q] = col_on(active, col0 + q, nb);
-    acc[q] = T(0);
-  }
+  const T* rk = r + (int64_t)col * n;
+  T acc = T(0);
   const int m1 = aptr[J + 1];
-  for (int m = aptr[J]; m < m1; ++m) {
-    const int i = arows[m];
-#pragma unroll
-    for (int q = 0; q < COLS; ++q)
-      if (on[q]) acc[q] += r[(int64_t)(col0 + q) * n + i];
-  }
-  const T sj = cs[J];
-#pragma unroll
-  for (int q = 0; q < COLS; ++q)
-    if (on[q]) rc[(int64_t)(col0 + q) * nc + J] = sj * acc[q];
+  for (int m = aptr[J]; m < m1; ++m) acc += rk[arows[m]];
+  rc[(int64_t)col * nc + J] = cs[J] * acc;
 }
 
 // x_i = beta x_i + w s_{J(i)} ec_{J(i)}  (x_i = w s ec when beta = 0)
@@ -197,24 +185,39 @@ __global__ __launch_bounds__(kThreads) void k_csr_dense(const int* __restrict__ 
 
 int csr_blocks(int n) { return (n + kThreads - 1) / kThreads; }
 
-constexpr int kCols = 2;  // vectors per thread
+static dim3 csr_grid(int rows, int nb, int cols) {
+  return dim3((unsigned)((rows + kThreads - 1) / kThreads), (unsigned)((nb + cols - 1) / cols));
+}
 
-static dim3 csr_grid(int rows, int nb) {
-  return dim3((unsigned)((rows + kThreads - 1) / kThreads), (unsigned)((nb + kCols - 1) / kCols));
+// Vectors per thread of the products: four share a row's indices and values where that
+// leaves enough threads, from 2^19 rows x vectors on; below, one.  Measured with 1 / 2 /
+// 4 / 8, 64 vectors: 230 / 151 / 127 / 122 us for 120,000 rows of a geometric graph, 67 /
+// 57 / 53 / 51 for 255^2 rows, 32 / 29 / 29 / 30 for 127^2; 16 vectors of 3,000 rows: 21.8
+// / 22.3 / 24.2 / 27.8.  The aggregate sums share nothing between vectors and take one
+// (120,000 rows, 64 vectors: 78 / 106 / 114 / 125).
+template <typename F>
+static void csr_cols(int rows, int nb, F&& f) {
+  if ((int64_t)rows * nb >= 1 << 19)
+    f(std::integral_constant<int, 4>());
+  else
+    f(std::integral_constant<int, 1>());
 }
 
 void csr_residual(const double* b, const double* x, double* r, const CsrMat<double>& A, int nb,
                   const int* active, c64* partials, hipStream_t s) {
   if (A.n == 0) return;
-  MLMC_LAUNCH((k_csr_residual<double, kCols>), csr_grid(A.n, nb), dim3(kThreads), 0, s, b, x, r,
-              A.sptr, A.sci, A.sv, A.n, nb, active, partials, timing_log());
+  csr_cols(A.n, nb, [&](auto c) {
+    constexpr int C = decltype(c)::value;
+    MLMC_LAUNCH((k_csr_residual<double, C>), csr_grid(A.n, nb, C), dim3(kThreads), 0, s, b, x, r,
+                A.sptr, A.sci, A.sv, A.n, nb, active, partials, timing_log());
+  });
 }
 
 void csr_restrict(const double* x, double* xc, const CsrAgg<double>& G, int n, int nb,
                   const int* active, hipStream_t s) {
   if (G.nc == 0) return;
-  MLMC_LAUNCH((k_csr_agg_sum<double, kCols>), csr_grid(G.nc, nb), dim3(kThreads), 0, s, x, xc,
-              G.aptr, G.arows, G.cs, n, G.nc, nb, active, timing_log());
+  MLMC_LAUNCH(k_csr_agg_sum<double>, csr_grid(G.nc, nb, 1), dim3(kThreads), 0, s, x, xc, G.aptr,
+              G.arows, G.cs, n, G.nc, active, timing_log());
 }
 
 void csr_prolong(const double* ec, double* x, const CsrAgg<double>& G, int n, double omega,
@@ -228,8 +231,11 @@ void csr_prolong(const double* ec, double* x, const CsrAgg<double>& G, int n, do
 void csr_spmm(const double* x, double* y, const CsrMat<double>& M, double w, double beta, int nb,
               const int* active, hipStream_t s) {
   if (M.n == 0) return;
-  MLMC_LAUNCH((k_csr_spmm<double, kCols>), csr_grid(M.n, nb), dim3(kThreads), 0, s, x, y, M.sptr,
-              M.sci, M.sv, M.n, M.ncol, w, beta, nb, active, timing_log());
+  csr_cols(M.n, nb, [&](auto c) {
+    constexpr int C = decltype(c)::value;
+    MLMC_LAUNCH((k_csr_spmm<double, C>), csr_grid(M.n, nb, C), dim3(kThreads), 0, s, x, y, M.sptr,
+                M.sci, M.sv, M.n, M.ncol, w, beta, nb, active, timing_log());
+  });
 }
 
 void csr_dense(const CsrMat<double>& A, double* aug, hipStream_t s) {
