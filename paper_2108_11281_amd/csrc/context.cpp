@@ -1767,10 +1767,10 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
     const Level& L = lv_[level - 1];
     bool restricted = false;
     if (direct) {
-      const int at = level - small_csr_level_[1];
-      small_csr_sweeps<T, double>(small_csr_of<T>().lev + at, small_np_[at], b,
-                                  zero_start ? nullptr : x, x, nrhs, 1, n, sweeps, reverse,
-                                  nullptr, s_);
+      const SmallCsr<T>& sc = small_csr_of<T>();
+      const int at = level - sc.level[1];
+      small_csr_sweeps<T, double>(sc.lev + at, sc.np[at], b, zero_start ? nullptr : x, x, nrhs, 1,
+                                  n, sweeps, reverse, nullptr, s_);
     } else if (complex_) {
       using C = typename std::conditional<sizeof(T) == 4, c32, c64>::type;
       // the V-cycle's sweep sequence (fused two-colour passes on the Wilson level;

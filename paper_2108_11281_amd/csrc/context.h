@@ -211,7 +211,7 @@ class Context {
   // whether sweeps of level l alone run as one workgroup per vector: up to the bound of
   // narrow batches, whatever the width
   template <typename T> bool small_sweeps(int l) {
-    return l < Ls_ && l >= small_csr_level_[0] && small_csr_of<T>().lev;
+    return l < Ls_ && l >= small_csr_of<T>().level[0];
   }
   // `sweeps` sweeps in place (zero: from a zero iterate): one launch on such levels, else
   // the launches of the tuned schedule
@@ -431,20 +431,21 @@ class Context {
   // CSR: a solve's right-hand sides and solutions as interleaved blocks, on which
   // the Krylov and V-cycle kernels of these operators work
   double *rowsB_ = nullptr, *rowsY_ = nullptr;
-  // CSR: the levels from small_csr_level to L_s - 1 whose V-cycle one workgroup
-  // per vector runs (in the precision of the mode), device descriptors
+  // CSR: the levels up to L_s - 1 whose V-cycle one workgroup per vector runs, in the
+  // precision of the mode and, with narrow_fp64, in FP64 for batches of that width
   template <typename T> struct SmallCsr {
-    SmallCsrLevel<T>* lev = nullptr;  // one per level from small_csr_level_[1]
+    SmallCsrLevel<T>* lev = nullptr;  // device descriptors, one per level from level[1]
     SmallCsrCoarse<T> coarse;
+    std::vector<int> np;              // positions of each of these levels
+    // first such level for narrow batches (at most 16 columns) and for wide ones
+    int level[2] = {1 << 30, 1 << 30};
+    int first(int nb) const { return level[nb <= 16 ? 0 : 1]; }
   };
   SmallCsr<float> sc32_;
   SmallCsr<double> sc64_;
-  std::vector<int> small_np_;          // positions of each of these levels
-  // first such level for narrow batches (at most 16 columns) and for wide ones
-  int small_csr_level_[2] = {1 << 30, 1 << 30};
-  int small_csr_level(int nb) const { return small_csr_level_[nb <= 16 ? 0 : 1]; }
   template <typename T> SmallCsr<T>& small_csr_of();
-  template <typename T> void build_small_csr();
+  // width: the widest batch
+  template <typename T> void build_small_csr(int width);
   // learned smoother state: FP32 master weights, Adam moments, gradient, BF16
   // fragments, BF16 link features; nn_use_ is true while a solve runs with it
   bool nn_ready_ = false, nn_use_ = false;

@@ -490,9 +490,9 @@ void Context::build_csr(const mlmc_operator& A, const int32_t* const* aggs, cons
     csr_general_coarse_trace();
   }
   if (opt_.precision == MLMC_FP32_IR64)
-    build_small_csr<float>();
-  else
-    build_small_csr<double>();
+    build_small_csr<float>(nb_);
+  if (opt_.precision == MLMC_FP64 || opt_.narrow_fp64 > 0)
+    build_small_csr<double>(opt_.precision == MLMC_FP64 ? nb_ : std::min(nb_, opt_.narrow_fp64));
   tune_csr();
 }
 
@@ -572,8 +572,8 @@ template <> Context::SmallCsr<double>& Context::small_csr_of<double>() { return 
 // us for the way down against about 110 us of launches, 27,600 rows 190 us against
 // about 150.
 template <typename T>
-void Context::build_small_csr() {
-  const size_t entry = sizeof(T) + 2;
+void Context::build_small_csr(int width) {
+  SmallCsr<T>& S = small_csr_of<T>();
   auto layout = [&](const Level& L, std::vector<int>& cls, std::vector<int>& row,
                     std::vector<int>& pos) {
     const std::vector<int>& off = L.S64.off;
@@ -609,8 +609,8 @@ void Context::build_small_csr() {
     if (nnz <= 10e3 * ncls && narrow == first + 1) narrow = first;
   }
   if (first >= Ls_ || nc > 65535) return;
-  small_csr_level_[0] = narrow < Ls_ ? narrow : 1 << 30;
-  small_csr_level_[1] = first;
+  if (narrow < Ls_) S.level[0] = narrow;
+  S.level[1] = first;
   auto up = [&](const auto& h) {
     using V = typename std::decay<decltype(h)>::type::value_type;
     V* d = dalloc_n<V>(std::max<int64_t>((int64_t)h.size(), 1));
@@ -657,7 +657,7 @@ void Context::build_small_csr() {
     }
     d.np = (int)row.size();
     d.ncls = (int)cls.size() - 1;
-    small_np_.push_back(d.np);
+    S.np.push_back(d.np);
     d.cls = up(cls);
     d.row = up(row);
     d.off = sell(L.h_rp, L.h_ci, L.h_v, row, true, pos);
@@ -715,21 +715,20 @@ void Context::build_small_csr() {
       d.cs = up(to_t(cs));
       d.fs = up(to_t(fs));
     }
-    d.b = dalloc_n<T>((int64_t)d.np * nb_);
-    d.x = dalloc_n<T>((int64_t)d.np * nb_);
-    d.r = dalloc_n<T>((int64_t)d.np * nb_);
+    d.b = dalloc_n<T>((int64_t)d.np * width);
+    d.x = dalloc_n<T>((int64_t)d.np * width);
+    d.r = dalloc_n<T>((int64_t)d.np * width);
     cls = ncls_;
     row = nrow;
     pos = npos;
   }
-  SmallCsr<T>& S = small_csr_of<T>();
   Work<T>& w = work<T>();
   S.lev = up(desc);
   S.coarse.n = nc;
   S.coarse.ld = w.ld;
   S.coarse.inv = w.ainvT;
-  S.coarse.b = dalloc_n<T>((int64_t)nc * nb_);
-  S.coarse.x = dalloc_n<T>((int64_t)nc * nb_);
+  S.coarse.b = dalloc_n<T>((int64_t)nc * width);
+  S.coarse.x = dalloc_n<T>((int64_t)nc * width);
   small_csr_setup();
 }
 
@@ -759,7 +758,10 @@ void Context::tune_csr() {
     }
     return ms;
   };
-  for (int l = 1; l < Ls_ && l < small_csr_level_[0]; ++l) {
+  // levels that some precision in use sweeps by launches
+  int end = fp32 ? sc32_.level[0] : sc64_.level[0];
+  if (opt_.narrow_fp64 > 0) end = std::max(end, sc64_.level[0]);
+  for (int l = 1; l < Ls_ && l < end; ++l) {
     Level& L = lv_[l - 1];
     const std::vector<int>& off = L.S32.off;
     for (int narrow = 0; narrow < 2; ++narrow) {
@@ -797,10 +799,11 @@ void Context::csr_sweeps(int l, const T* b, T* x, int nb, int sweeps, bool zero,
   const double bytes = 3.0 * sizeof(T) * n +
                        ((nnz - n) * (4.0 + sizeof(T)) + n * (8.0 + sizeof(T))) / nb;
   if (small_sweeps<T>(l)) {
-    const int at = l - small_csr_level_[1];
+    const SmallCsr<T>& sc = small_csr_of<T>();
+    const int at = l - sc.level[1];
     timed<T>(l, kTimGs, sweeps * bytes, act, nb, [&] {
-      small_csr_sweeps<T, T>(small_csr_of<T>().lev + at, small_np_[at], b, zero ? nullptr : x, x,
-                             nb, nb, 1, sweeps, reverse, act, s_);
+      small_csr_sweeps<T, T>(sc.lev + at, sc.np[at], b, zero ? nullptr : x, x, nb, nb, 1, sweeps,
+                             reverse, act, s_);
     });
     return;
   }
@@ -827,9 +830,9 @@ void Context::vcycle_csr(int l, const T* b, T* x, int nb, const int* act, c64* r
   // a second coarse-grid cycle needs this level's coarse residual between the two, so
   // such a top level keeps its launches; the cycles below it are the kernel's
   const bool two = top && top_cycles_ == 2 && l + 1 < Ls_;
-  if (l < Ls_ && l >= small_csr_level(nb) && sc.lev && !two) {
-    const int at = l - small_csr_level_[1], nl = Ls_ - l;
-    const int np = *std::max_element(small_np_.begin() + at, small_np_.end());
+  if (l < Ls_ && l >= sc.first(nb) && !two) {
+    const int at = l - sc.level[1], nl = Ls_ - l;
+    const int np = *std::max_element(sc.np.begin() + at, sc.np.end());
     const bool all = sc.coarse.n <= kSmallCsrDense;
     auto part = [&](int mode) {
       small_csr<T>(sc.lev + at, nl, np, sc.coarse, b, x, nb, opt_.nu_pre, opt_.nu_post, omega_,
