@@ -716,12 +716,26 @@ void rows_dense(const T* Pk, const T* B, T* Z, int n, int ld, int W, const int* 
 static dim3 convert_grid(int64_t n, int W) {
   return dim3((unsigned)((n + 63) / 64), (unsigned)((W + 31) / 32));
 }
+// one vector is the same in both layouts
+template <typename To, typename Ts>
+static void copy_one(const Ts* src, To* dst, int64_t n, hipStream_t s) {
+  if constexpr (std::is_same<To, Ts>::value)
+    vec_copy<To>(src, dst, n, 1, nullptr, s);
+  else
+    vec_convert<To, Ts>(src, dst, n, 1, nullptr, s);
+}
 template <typename To>
 void rows_in(const double* src, double* dst, To* dst2, int64_t n, int W, hipStream_t s) {
+  if (W == 1) {
+    if (dst) copy_one<double, double>(src, dst, n, s);
+    if (dst2) copy_one<To, double>(src, dst2, n, s);
+    return;
+  }
   MLMC_LAUNCH(k_rows_in<To>, convert_grid(n, W), dim3(kThreads), 0, s, src, dst, dst2, n, W);
 }
 template <typename Ts>
 void rows_out(const Ts* src, double* dst, int64_t n, int W, hipStream_t s) {
+  if (W == 1) return copy_one<double, Ts>(src, dst, n, s);
   MLMC_LAUNCH(k_rows_out<Ts>, convert_grid(n, W), dim3(kThreads), 0, s, src, dst, n, W);
 }
 
