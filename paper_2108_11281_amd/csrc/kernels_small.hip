@@ -551,9 +551,9 @@ __device__ __forceinline__ double step_xr(T (&x0)[R], T (&x1)[R], T (&r0)[R], T 
   return rr;
 }
 
-// Preconditioned CG in precision T from x = 0 to |r| <= tol |b| (the recursion's
-// residual), a column per workgroup: the arithmetic and the per-column decisions
-// of the lockstep pcg, A p formed twice instead of stored.  rres: final
+// Preconditioned CG in precision T from x = 0 to |r| <= tol |b|, a column per
+// workgroup: the arithmetic and the per-column decisions of the lockstep pcg, A p
+// formed twice instead of stored.  rres: final
 // |b - A x|^2 and the iterations taken (im); bb: |b|^2; lastcorr: alpha r^T z of
 // the last step.  pbuf, rbuf: a plane per column (sides above 64 only).  64^2 in
 // FP64 (three levels, 1 + 1 sweeps): 9.4 us per iteration whatever the batch, 55 us
@@ -577,41 +577,52 @@ __global__ __launch_bounds__(kSmT) void k_small_pcg(const T* b, T* x, T* pbuf, T
 #pragma unroll
   for (int r = 0; r < R; ++r) x0[r] = x1[r] = P0[r] = P1[r] = 0;
   const double rr0 = wg_sum(sm, dot_local<R>(r0, r1, r0, r1));
-  double rz = 0.0, lc = 0.0;
+  double rz = 0.0, lc = 0.0, rr = 0.0;
   int it = 0;
-  for (;;) {
-    const Geo g = geo_of<R>(S);
-    top_cycle<R>(q, sm, g, Z0, Z1, r0, r1, true, child_cycles, it == 0 ? b + off : rbuf + off);
-    const double rzn = wg_sum(sm, dot_local<R>(r0, r1, Z0, Z1));
-    const double beta = it > 0 && rz != 0.0 ? rzn / rz : 0.0;
-    rz = rzn;
-    ++it;
-    next_direction<R>(Z0, Z1, P0, P1, (T)beta, it == 1, pbuf + off, S, sm.ed);
-    const double pq = wg_sum(sm, curvature<R>(P0, P1, d, c, g, sm.ed));
-    const double alpha = pq != 0.0 && isfinite(pq) ? rz / pq : 0.0;
-    lc = alpha * rz;
-    const double rr = wg_sum(sm, step_xr<R>(x0, x1, r0, r1, P0, P1, (T)alpha, d, c, it == 1,
-                                            x + off, rbuf + off, S, sm.ed));
-    if (rr <= tol2 * rr0 || !isfinite(rr) || it >= max_iter) break;
-  }
-  // the true residual of the result
-  if constexpr (R == 8) load_plane<R>(x0, x1, x + off, g);
-  else store_plane<R>(x0, x1, x + off, g);
-  publish<R, 0>(sm.ed, x0, x1, g);
-  publish<R, 1>(sm.ed, x0, x1, g);
-  __syncthreads();
-  double rr = 0.0;
-  neighbour_sums<R>(x0, x1, g, sm.ed, [&](int r, T s0, T s1) {
-    const bool in = g.col && g.y0 + r < g.S;
-    const Pair2<T> bv =
-        reinterpret_cast<const Pair2<T>*>(b + off)[in ? (g.y0 + r) * (g.S >> 1) + g.sub : 0];
-    const T v0 = bv.e0 - (d * x0[r] - c * s0), v1 = bv.e1 - (d * x1[r] - c * s1);
-    if (in) {
-      rr += (double)v0 * v0;
-      rr += (double)v1 * v1;
+  for (int tries = 0;; ++tries) {
+    for (;;) {
+      const Geo g = geo_of<R>(S);
+      top_cycle<R>(q, sm, g, Z0, Z1, r0, r1, true, child_cycles, it == 0 ? b + off : rbuf + off);
+      const double rzn = wg_sum(sm, dot_local<R>(r0, r1, Z0, Z1));
+      const double beta = it > 0 && rz != 0.0 ? rzn / rz : 0.0;
+      rz = rzn;
+      ++it;
+      next_direction<R>(Z0, Z1, P0, P1, (T)beta, it == 1, pbuf + off, S, sm.ed);
+      const double pq = wg_sum(sm, curvature<R>(P0, P1, d, c, g, sm.ed));
+      const double alpha = pq != 0.0 && isfinite(pq) ? rz / pq : 0.0;
+      lc = alpha * rz;
+      rr = wg_sum(sm, step_xr<R>(x0, x1, r0, r1, P0, P1, (T)alpha, d, c, it == 1, x + off,
+                                 rbuf + off, S, sm.ed));
+      if (rr <= tol2 * rr0 || !isfinite(rr) || it >= max_iter) break;
     }
-  });
-  rr = wg_sum(sm, rr);
+    const bool passed = rr <= tol2 * rr0;
+    // the true residual of the result, in place of the recursion's
+    if constexpr (R == 8) load_plane<R>(x0, x1, x + off, g);
+    publish<R, 0>(sm.ed, x0, x1, g);
+    publish<R, 1>(sm.ed, x0, x1, g);
+    __syncthreads();
+    rr = 0.0;
+    neighbour_sums<R>(x0, x1, g, sm.ed, [&](int r, T s0, T s1) {
+      const bool in = g.col && g.y0 + r < g.S;
+      const int at = in ? (g.y0 + r) * (g.S >> 1) + g.sub : 0;
+      const Pair2<T> bv = reinterpret_cast<const Pair2<T>*>(b + off)[at];
+      const T v0 = bv.e0 - (d * x0[r] - c * s0), v1 = bv.e1 - (d * x1[r] - c * s1);
+      r0[r] = in ? v0 : (T)0;
+      r1[r] = in ? v1 : (T)0;
+      if constexpr (kWide<T, R>) {
+        if (in) reinterpret_cast<Pair2<T>*>(rbuf + off)[at] = Pair2<T>{v0, v1};
+      }
+      rr += (double)r0[r] * r0[r];
+      rr += (double)r1[r] * r1[r];
+    });
+    rr = wg_sum(sm, rr);
+    // Rounding separates the two residuals by some 1e-15 of |b|, so the recursion may
+    // pass a column whose true residual misses the tolerance: that column goes on from
+    // its true residual with a new direction
+    if (!passed || rr <= tol2 * rr0 || !isfinite(rr) || it >= max_iter || tries == 2) break;
+    rz = 0.0;
+  }
+  if constexpr (R != 8) store_plane<R>(x0, x1, x + off, g);
   if (threadIdx.x == 0) {
     rres[k] = {rr, (double)it};
     bb[k] = {rr0, 0.0};
