@@ -166,7 +166,7 @@ void Context::alloc_work(Work<T>& w, int width) {
   w.z = dalloc_n<T>(n1);
   w.p = dalloc_n<T>(n1);
   w.p2 = dalloc_n<T>(n1);
-  w.q = dalloc_n<T>(n1);
+  if (kind_ != MLMC_POISSON2D) w.q = dalloc_n<T>(n1);  // whose CG stores no A p
   w.vb.assign(Ls_, nullptr);
   w.vx.assign(Ls_, nullptr);
   w.vt.assign(Ls_, nullptr);
@@ -416,7 +416,7 @@ void Context::tune_poisson() {
       float ms = 1e30f;  // best of 5 after a warm-up run (robust to noise)
       for (int rep = 0; rep < 6; ++rep) {
         MLMC_HIP(hipEventRecord(a, s_));
-        poisson_rbgs_fused<T>(w.z, w.r, w.q, w.vb[l], omega_, L.side, L.d, L.c, nb_, nullptr,
+        poisson_rbgs_fused<T>(w.z, w.r, w.p, w.vb[l], omega_, L.side, L.d, L.c, nb_, nullptr,
                               true, nullptr, rows, sw, s_);
         MLMC_HIP(hipEventRecord(b, s_));
         MLMC_HIP(hipEventSynchronize(b));
@@ -560,29 +560,9 @@ void Context::tune_varcoef() {
   ev_pool_.push_back(b);
 }
 
-// work buffers and coarsest inverses of a real symmetric positive definite
-// operator (POISSON2D, VARCOEF3D)
-void Context::finish_real_build() {
-  const int64_t n1 = lv_[0].n;
-  alloc_common();
-  // the FP64 Krylov / V-cycle vectors serve the plain FP64 mode only; the
-  // refined FP32 mode keeps its FP64 iterate in the sample-batch buffers
-  if (opt_.precision == MLMC_FP64) alloc_work(w64_);
-  MLMC_REQUIRE(opt_.narrow_fp64 >= 0, MLMC_EINVAL, "narrow_fp64 must be >= 0");
-  if (opt_.precision == MLMC_FP32_IR64 && opt_.narrow_fp64 > 0)
-    alloc_work(w64_, opt_.narrow_fp64);
-  if (opt_.precision == MLMC_FP32_IR64) {
-    alloc_work(w32_);
-    r32_ = dalloc_n<float>(n1 * nb_);
-    d32_ = dalloc_n<float>(n1 * nb_);
-    if (kind_ == MLMC_POISSON2D) b32_ = dalloc_n<float>(n1 * nb_);
-  }
-
-  // coarsest inverses (FP64 on the device), the direct trace term (Remark 4.2)
-  c64 tr_s;
-  invert_coarse(Ls_, &ainv_solver_, &tr_s);
-  // the transposed inverse, zero-padded to a multiple of 16 so that the MFMA
-  // tile kernel applies it for any coarsest size, in that kernel's layout
+// the transposed inverse, zero-padded to a multiple of 16 so that the MFMA
+// tile kernel applies it for any coarsest size, in that kernel's layout
+void Context::pack_coarse() {
   const int ns = (int)lv_[Ls_ - 1].n;
   const int ld = (ns + 15) / 16 * 16;
   double* plain = dalloc_n<double>((int64_t)ld * ld);
@@ -606,6 +586,31 @@ void Context::finish_real_build() {
     w32_.ainvT = dalloc_n<float>((int64_t)ld * ld);
     vec_convert<float, double>(w64_.ainvT, w32_.ainvT, (int64_t)ld * ld, 1, nullptr, s_);
   }
+}
+
+// work buffers and coarsest inverses of a real symmetric positive definite
+// operator (POISSON2D, VARCOEF3D)
+void Context::finish_real_build() {
+  const int64_t n1 = lv_[0].n;
+  alloc_common();
+  // the FP64 Krylov / V-cycle vectors serve the plain FP64 mode only; the
+  // refined FP32 mode keeps its FP64 iterate in the sample-batch buffers
+  if (opt_.precision == MLMC_FP64) alloc_work(w64_);
+  MLMC_REQUIRE(opt_.narrow_fp64 >= 0, MLMC_EINVAL, "narrow_fp64 must be >= 0");
+  if (opt_.precision == MLMC_FP32_IR64 && opt_.narrow_fp64 > 0)
+    alloc_work(w64_, opt_.narrow_fp64);
+  if (opt_.precision == MLMC_FP32_IR64) {
+    alloc_work(w32_);
+    r32_ = dalloc_n<float>(n1 * nb_);
+    d32_ = dalloc_n<float>(n1 * nb_);
+    if (kind_ == MLMC_POISSON2D) b32_ = dalloc_n<float>(n1 * nb_);
+  }
+
+  // coarsest inverses (FP64 on the device), the direct trace term (Remark 4.2)
+  c64 tr_s;
+  invert_coarse(Ls_, &ainv_solver_, &tr_s);
+  // 2D Poisson hierarchies solve a small coarsest grid in the sine basis
+  if (kind_ != MLMC_POISSON2D || lv_[Ls_ - 1].side > kSmallCoarse) pack_coarse();
   if (L_ == Ls_) {
     coarse_trace_ = tr_s;
   } else {

@@ -239,6 +239,7 @@ class Context {
     return lv_[l - 1].gs_rows[sizeof(typename Traits<T>::real) == 8 ? 1 : 0];
   }
   void finish_real_build();
+  void pack_coarse();
   void build_wilson(const double* theta);
   void nn_alloc();
   void defl_require() const;
