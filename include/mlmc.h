@@ -253,7 +253,9 @@ int mlmc_default_options(mlmc_options* opt);
  * mlmc_destroy.  Errors: EINVAL for inconsistent sizes (a grid side that is not
  * divisible by the aggregate side at every level, L > L_s, nb out of range, a
  * coarsest operator with a zero pivot in its partially pivoted Gauss-Jordan
- * inverse), EDEVICE/ENOMEM from the runtime. */
+ * inverse), EDEVICE/ENOMEM from the runtime.  Beside the work vectors a CSR
+ * context holds two FP64 blocks of n x nb (a solve's right-hand sides and
+ * solutions in the order of its kernels) and three blocks per small level. */
 int mlmc_setup(const mlmc_operator* A, const mlmc_hierarchy* h,
                const mlmc_options* opt, void* hip_stream, mlmc_ctx** out_ctx);
 
@@ -465,8 +467,13 @@ int mlmc_set_timing(mlmc_ctx* ctx, int mask, int stride);
  * learned-smoother network (counts FLOPs, not bytes: 2 x 4032 per site and
  * column), 6 FP64 refinement fold y += x32 with
  * its b^T x32 partial sums and x32 = 0 (32 bytes: FP64 y, b and FP32 x32 in; y
- * and x32 out; fp64 slot), 7 FP64 refinement residual (20 bytes: FP64 b and y
- * in, FP32 r out; fp64 slot).  fp64 = 0 selects the FP32/complex64
+ * and x32 out; 8 fewer on a solve's first fold, which does not read y; fp64 slot),
+ * 7 FP64 refinement residual (20 bytes: FP64 b and y in, FP32 r out; fp64 slot).
+ * 2D Poisson solves launch no fold of their own: id 6 stays empty there, and id 7
+ * is the fold and the residual in one pass (28 bytes: y, FP32 x32 and b in, y and
+ * FP32 r out; 32 where b has entries that are not FP32 numbers; 8 fewer on the
+ * first).  Levels of a CSR hierarchy that one workgroup per vector runs report each
+ * part of a whole V-cycle under id 0 with 2e.  fp64 = 0 selects the FP32/complex64
  * instantiation, 1 the FP64 one.  out: launches, total milliseconds, total
  * algorithmic bytes (active columns only). */
 int mlmc_kernel_stats(mlmc_ctx* ctx, int kernel, int fp64, double* out);
