@@ -210,6 +210,19 @@ def per_level_fractions(est, kernel, levels, fp64=False):
     return out
 
 
+def poisson_one_launch(N, L, level):
+    """Whether level's V-cycles run as one launch of k_small_vcycle, which the library
+    reports under the sweep's id (sides up to 128 above a coarsest side up to 64)."""
+    return N >> (level - 1) <= 128 and N >> (L - 1) <= 64
+
+
+def poisson_sweep_stats(est, N, L):
+    """Launches, time and bytes of the sweep kernels on the levels that launch them."""
+    stats = [est.kernel_stats("rbgs_sweep", level=l) for l in range(1, L + 1)
+             if not poisson_one_launch(N, L, l)]
+    return tuple(sum(v) for v in zip(*stats)) if stats else (0, 0.0, 0.0)
+
+
 def copy_bandwidth(torch, mib=1024, reps=20, library=False):
     """Measured device-to-device copy rate (read + write bytes per second) on
     this GPU, beside the 8 TB/s vendor peak: torch's copy kernel, or (library)
@@ -288,15 +301,19 @@ def run_poisson(args, m, torch):
                [round(v, 3) for v in r["level_seconds"]]))
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
-    gs = est.kernel_stats("rbgs_sweep")
+    gs = poisson_sweep_stats(est, N, L)
     per_level = per_level_fractions(est, "rbgs_sweep", L)
+    for d in per_level:
+        if poisson_one_launch(N, L, d["level"]):  # the rate would be of whole V-cycles
+            d.update(gbs=None, frac=None, whole_vcycles=True)
     est.set_timing(True)
     est.reset_kernel_stats()
     est.trace(args.eps, 777)
     kernels = kernel_table(est)
     est.set_timing(False)
     ms_per_step = 1000.0 * elapsed / args.steps
-    roofline = hbm_roofline("rbgs_sweep<float> (sides up to 128: k_small_vcycle, whole V-cycles)", gs, args.timing_stride, stored_traffic())
+    roofline = hbm_roofline("rbgs_sweep<float> (sides above 128)", gs, args.timing_stride,
+                            stored_traffic())
     roofline["per_level"] = per_level
     # sustained HBM rate of a plain copy (1 GiB each way): the library's
     # streaming kernel and torch's copy, beside the vendor peak
