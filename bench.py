@@ -322,7 +322,7 @@ def run_poisson(args, m, torch):
     roofline["copy_torch_gbs"] = copy_bandwidth(torch)
     roofline["frac_of_copy"] = round(roofline["achieved"] / copy_gbs, 4)
     for d in per_level:
-        d["frac_of_copy"] = round(d["gbs"] / copy_gbs, 4)
+        d["frac_of_copy"] = round(d["gbs"] / copy_gbs, 4) if d["gbs"] is not None else None
     log("per-level sweep fractions %s; copy kernel %.1f GB/s (torch copy %.1f)" % (
         [(d["level"], d["frac"]) for d in per_level], copy_gbs, roofline["copy_torch_gbs"]))
 
