@@ -1469,7 +1469,6 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
     MLMC_HIP(hipStreamSynchronize(s_));
     if (!complex_ && small(l) && l != Ls_) count_small(l, nb);
     ok = true;
-    double worst = 0.0;
     col_ok_.assign((size_t)nb, 1);
     for (int k = 0; k < nb; ++k) {
       const double bn = host_c64_[nb + k].re;
@@ -1478,10 +1477,9 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
       if (!(rel <= tol)) {
         ok = false;
         col_ok_[(size_t)k] = 0;
-        if (std::isfinite(rel)) worst = std::max(worst, rel);
       }
     }
-    if (ok || !plain || pass == 2 || !correct_missed(l, y, nb, 0.5 * tol / worst)) break;
+    if (ok || !plain || pass == 2 || !correct_missed(l, y, nb, tol)) break;
     op_residual<double, double, double>(l, b, y, r64_, nb, nullptr, partials_);
     finish_sums(partials_, nblk_pts, nb, rres, s_);
   }
@@ -1490,19 +1488,20 @@ void Context::solve(int l, const double* b, double* y, int nb, c64* err, double*
 
 // Rounding separates the residual of the CG recursion from the true one by some 1e-15 of
 // |b| (more for large |A| |y| / |b|), so the recursion may pass a column that then misses
-// solve_tol (256^2, 128 columns at 1e-13: 11 of them).  Solves A e = r64_ = b - A y for
-// these columns to the factor `reduce`, y += e; act_inner_: the flags that pcg left (0:
-// passed), col_ok_: the verdicts.  false: there are none.
-bool Context::correct_missed(int l, double* y, int nb, double reduce) {
+// tol (256^2, 128 columns at 1e-13: 11 of them).  Solves A e = r64_ = b - A y for these
+// columns to half of what they miss, y += e; act_inner_: the flags that pcg left (0:
+// passed), col_ok_ and host_c64_: the verdicts, |r|^2 and |b|^2.  false: there are none.
+bool Context::correct_missed(int l, double* y, int nb, double tol) {
   std::vector<int> act((size_t)nb);
   MLMC_HIP(hipMemcpyAsync(act.data(), act_inner_, sizeof(int) * nb, hipMemcpyDeviceToHost, s_));
   MLMC_HIP(hipStreamSynchronize(s_));
-  bool any = false;
+  double worst = 0.0;  // relative residual of these columns
   for (int k = 0; k < nb; ++k) {
     act[k] = !act[k] && !col_ok_[(size_t)k] && std::isfinite(host_c64_[k].re);
-    any = any || act[k];
+    if (act[k]) worst = std::max(worst, std::sqrt(host_c64_[k].re / host_c64_[nb + k].re));
   }
-  if (!any) return false;
+  if (worst == 0.0) return false;
+  const double reduce = 0.5 * tol / worst;
   MLMC_HIP(hipMemcpyAsync(act_inner_, act.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s_));
   MLMC_HIP(hipStreamSynchronize(s_));
   const int64_t n = lv_[l - 1].n;
@@ -1804,8 +1803,7 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
       else to_t(dst, src, m);
     };
     // CSR levels that one workgroup per vector sweeps: in the caller's blocks
-    const bool direct =
-        csr_ && csr_tail < 0 && !rc && sweeps > 0 && small_sweeps<T>(level);
+    const bool direct = csr_ && csr_tail < 0 && !rc && sweeps > 0 && small_sweeps<T>(level);
     if (!direct) {
       in_t(bt, b);
       if (!zero_start) in_t(xa, x);
@@ -1878,13 +1876,12 @@ void Context::smooth_fp64(int level, int nrhs, int sweeps, bool reverse, bool ze
         op_res_restrict<T>(level, bt, xa, rct, nrhs, nullptr);
       }
     }
-    if (direct) {
-    } else if (csr_) {
-      rows_out<T>(xa, x, n, nrhs, s_);
-      if (rct) rows_out<T>(rct, rc, lv_[level].n, nrhs, s_);
-    } else {
+    if (!csr_) {
       from_t(xa, x, m);
       if (rct) from_t(rct, rc, mc);
+    } else if (!direct) {
+      rows_out<T>(xa, x, n, nrhs, s_);
+      if (rct) rows_out<T>(rct, rc, lv_[level].n, nrhs, s_);
     }
     MLMC_HIP(hipGetLastError());
     if (ws) return;  // the caller's workspace: no stream synchronisation needed

@@ -351,7 +351,7 @@ class Context {
   template <typename T> int pcg(int l, const T* b, T* x, int nb, int* act, double tol,
                                 c64* lastcorr);
   void pcg_refined(int l, const double* b, double* y, int nb, double tol, c64* err);
-  bool correct_missed(int l, double* y, int nb, double reduce);
+  bool correct_missed(int l, double* y, int nb, double tol);
   // Launches the HIP graph of `body`, captured on the context stream at the
   // key's first use; the host-side counters the body advances (recorded while
   // capturing) advance by the same amounts at every launch.  Keys: {0, level,
