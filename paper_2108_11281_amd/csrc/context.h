@@ -97,7 +97,8 @@ struct Work {
   // and CSR kinds only: the 2D Poisson V-cycle starts that cycle from ec)
   std::vector<T*> vr2, ve2;
   // transposed inverse of the solver's coarsest operator: real operators in
-  // the MFMA tile kernel's layout (dense_pack4), complex ones plain row-major
+  // the MFMA tile kernel's layout (dense_pack4), complex ones plain row-major; none
+  // for 2D Poisson above a small coarsest grid (SmallGrid)
   T* ainvT = nullptr;
   int ld = 0;               // its leading dimension (n rounded up to 16, zero padded)
   // complex operators: the inverse in the order of dense_complex_pack (n a multiple of 8)
